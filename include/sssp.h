@@ -294,13 +294,14 @@ typedef struct {
                                when each scan block owns at most 16384 vertices (n <= 4096 *
                                scan_blocks * 4), else the dense scan runs. Ignored by every other
                                criterion and solver. Values above 2: SSSP_ERR_INVALID. */
-    uint32_t single;        /* 1: sssp_solve with a criterion made of DIJK, IN_STATIC and OUT_STATIC
-                               runs the whole solve in one workgroup of the batched kernel
-                               (sssp_solve_batch with one query): no kernel launch per phase, for
-                               graphs whose phases settle few vertices each (grids). Same
-                               distances and phase count; no per-kernel timing is recorded
-                               (sssp_profile_get keeps the previous figures). sssp_solve_ex and
-                               every other solver ignore it. */
+    uint32_t single;        /* how sssp_solve runs a criterion made of DIJK, IN_STATIC and OUT_STATIC.
+                               0 (default): resident, the whole solve in one cooperative launch whose
+                               workgroups meet at a barrier once per phase (graphs of at most 2^24
+                               vertices; larger ones, and solves with per-kernel timing on, use the
+                               phase kernels, whose shape the fields above give). 1: in one workgroup
+                               of the batched kernel (sssp_solve_batch with one query). 2: the phase
+                               kernels. Same distances and phase count. sssp_solve_ex and every other
+                               solver ignore it. Values above 2 mean 2. */
 } sssp_launch_cfg;
 
 /* Read the launch shape used by later solves on g. */
@@ -314,8 +315,8 @@ int sssp_set_launch(sssp_graph *g, const sssp_launch_cfg *cfg);
  * Autotuner for the plain solver: times sssp_solve(g, source, criterion) with
  * HIP events for a set of launch shapes (scan grid, relax grid, chunk size,
  * graph replay, the dense scan or queue arrays; for static criteria also keyed
- * queue arrays and the one-workgroup option), keeps the fastest on g and
- * returns it in best (may be NULL)
+ * queue arrays, the one-workgroup option and the resident solve), keeps the
+ * fastest on g and returns it in best (may be NULL)
  * with its time in best_ms (may be NULL). Distances are never affected.
  */
 int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion, sssp_launch_cfg *best,

@@ -14,7 +14,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsssp.so")
-SOURCES = ["graph.hip", "phased.hip", "batch.hip", "tune.hip", "mlp.hip"]
+SOURCES = ["graph.hip", "phased.hip", "resident.hip", "batch.hip", "tune.hip", "mlp.hip"]
 ARCH = os.environ.get("SSSP_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [

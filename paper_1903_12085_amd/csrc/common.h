@@ -338,6 +338,7 @@ struct LaunchCfg {
     int chunk;          // edges per relax chunk (256, 512 or 1024)
     int use_graph;      // replay phases from a captured HIP graph
     int queue;          // static criteria: per-block queue arrays instead of the dense scan (2: keyed)
-    int single;         // sssp_solve with static criteria: the whole solve in one workgroup
+    int single;         // sssp_solve with static criteria: 0 resident, 1 in one workgroup, kPhaseKernels
 };
+constexpr int kPhaseKernels = 2;     // LaunchCfg::single: a launch per kernel and phase
 constexpr int kMaxChunk = 2048;

@@ -19,6 +19,7 @@ struct sssp_graph {
     uint2 *in_edges = nullptr;     // CSC (source, weight), rows sorted by weight (lazy)
     uint64_t precompute_ns = 0;
     uint64_t sum_w = 0;            // exact sum of edge weights (selector feature scale)
+    uint32_t max_deg = 0;          // longest row
     uint32_t wmax = 0;             // some edge weighs 2^32 - 1 (a stored minimum INF32 is then ambiguous)
     LaunchCfg cfg{};
     // per-solve scratch, allocated on first use and kept
@@ -45,6 +46,9 @@ struct sssp_graph {
     uint32_t *one_fl = nullptr;    // two fringe lists and the settled list, 3 * n
     uint2 *one_fm = nullptr;       // (minIn, minOut) of the two fringe lists' entries, 2 * n
     void *one_aux = nullptr;       // query record, order, phase count, work-queue control
+    // resident solves: barrier words and group marks
+    void *res = nullptr;
+    uint64_t res_bytes = 0;
 };
 
 DevGraph dev_view(const sssp_graph *g);
@@ -55,3 +59,17 @@ int solve_bufs_ensure(sssp_graph *g, bool cursors, bool stamps, bool queue, bool
 void solve_bufs_free(sssp_graph *g);
 int batch_solve_one(sssp_graph *g, uint32_t source, int in, bool out_static, uint64_t *dist_out,
                     uint32_t *phases_out);
+
+// Shape of a resident solve (resident.hip).
+struct ResShape {
+    uint32_t W;           // workgroups (a power of two)
+    uint32_t lgK;         // vertices per group: 8 or 16
+    uint32_t slots;       // vertex groups a workgroup can hold
+    uint32_t one_xcd;     // all workgroups on one XCD
+    int bs;               // threads per workgroup
+    bool fits;            // the graph can be solved resident
+    uint64_t bytes;       // device scratch
+};
+ResShape resident_shape(const sssp_graph *g);
+int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static,
+                   uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran);

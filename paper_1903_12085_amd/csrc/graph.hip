@@ -153,10 +153,15 @@ __global__ void k_emin(uint64_t m, const uint2 *__restrict__ edges, const uint2 
 }
 
 // Exact sum of all edge weights (one block-level sum and one atomic per block);
-// out[1] counts the edges of weight 2^32 - 1.
-__global__ void k_sum_w(uint64_t m, const uint2 *__restrict__ edges, unsigned long long *__restrict__ out) {
+// out[1] counts the edges of weight 2^32 - 1, out[2] is the longest row.
+__global__ void k_sum_w(uint32_t n, uint64_t m, const uint32_t *__restrict__ rp, const uint2 *__restrict__ edges,
+                        unsigned long long *__restrict__ out) {
     __shared__ unsigned long long sh[4], shx[4];
+    __shared__ uint32_t shd[4];
     unsigned long long t = 0, x = 0;
+    uint32_t dmax = 0;
+    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (uint64_t)gridDim.x * blockDim.x)
+        dmax = max(dmax, rp[v + 1] - rp[v]);
     for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t w = edges[e].y;
         t += w;
@@ -165,16 +170,19 @@ __global__ void k_sum_w(uint64_t m, const uint2 *__restrict__ edges, unsigned lo
     for (int o = 32; o > 0; o >>= 1) {
         t += __shfl_xor(t, o, 64);
         x += __shfl_xor(x, o, 64);
+        dmax = max(dmax, (uint32_t)__shfl_xor((int)dmax, o, 64));
     }
     if ((threadIdx.x & 63) == 0) {
         sh[threadIdx.x >> 6] = t;
         shx[threadIdx.x >> 6] = x;
+        shd[threadIdx.x >> 6] = dmax;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         atomicAdd(out, sh[0] + sh[1] + sh[2] + sh[3]);
         const unsigned long long nx = shx[0] + shx[1] + shx[2] + shx[3];
         if (nx) atomicAdd(out + 1, nx);
+        atomicMax(out + 2, (unsigned long long)max(max(shd[0], shd[1]), max(shd[2], shd[3])));
     }
 }
 
@@ -281,15 +289,16 @@ static int create_impl(uint32_t n, uint64_t m, const uint64_t *row_ptr, const ui
         TRY(hipEventSynchronize(e1));
         if (m) {  // weight sum for the selector's feature scale and the 2^32 - 1 flag (not timed)
             unsigned long long *dsum = nullptr;
-            TRY(hipMalloc(&dsum, 2 * sizeof(unsigned long long)));
-            TRY(hipMemsetAsync(dsum, 0, 2 * sizeof(unsigned long long), s));
-            hipLaunchKernelGGL(k_sum_w, dim3(grid_for(m, 256, 1024)), dim3(256), 0, s, m, g->edges, dsum);
-            unsigned long long hs[2] = {0, 0};
+            TRY(hipMalloc(&dsum, 4 * sizeof(unsigned long long)));
+            TRY(hipMemsetAsync(dsum, 0, 4 * sizeof(unsigned long long), s));  // whole 16-byte words: one fill
+            hipLaunchKernelGGL(k_sum_w, dim3(grid_for(m, 256, 1024)), dim3(256), 0, s, n, m, g->rp, g->edges, dsum);
+            unsigned long long hs[4] = {0, 0, 0, 0};
             TRY(hipMemcpyAsync(hs, dsum, sizeof hs, hipMemcpyDeviceToHost, s));
             TRY(hipStreamSynchronize(s));
             sssp_free(dsum);
             g->sum_w = hs[0];
             g->wmax = hs[1] != 0;
+            g->max_deg = (uint32_t)hs[2];
         }
         float ms = 0;
         TRY(hipEventElapsedTime(&ms, e0, e1));
@@ -340,6 +349,7 @@ extern "C" int sssp_graph_destroy(sssp_graph *g) {
     if (!g) return SSSP_OK;
     sssp_free(g->rp); sssp_free(g->edges); sssp_free(g->vmin); sssp_free(g->emin);
     sssp_free(g->ip); sssp_free(g->in_edges);
+    sssp_free(g->res);
     sssp_free(g->one_fm);  // the one-workgroup scratch's other buffers go with solve_bufs_free
     solve_bufs_free(g);
     delete g;

@@ -3160,16 +3160,41 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     return rc;
 }
 
+// The graph's scratch for resident solves, kept between them.
+static int resident_scratch(sssp_graph *g, const ResShape &r) {
+    if (g->res_bytes >= r.bytes) return SSSP_OK;
+    sssp_free(g->res);
+    g->res = nullptr;
+    g->res_bytes = 0;
+    HIP_OK(hipMalloc(&g->res, r.bytes));
+    g->res_bytes = r.bytes;
+    return SSSP_OK;
+}
+
 extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, uint64_t *dist_out,
                           uint32_t *phases_out) {
-    if (g && g->cfg.single && criterion != 0 && !(criterion & ~SSSP_CRIT_ALL)) {
+    if (g && g->cfg.single != kPhaseKernels && criterion != 0 && !(criterion & ~SSSP_CRIT_ALL)) {
         int in = IN_NONE, out = OUT_NONE;
         crit_modes(criterion, &in, &out);
-        if (static_modes(in, out)) {  // the whole solve in one workgroup (the batched kernel)
+        if (static_modes(in, out)) {
             if (!dist_out) return sssp_set_error(SSSP_ERR_INVALID, "dist_out is NULL");
             if (source >= g->n) return sssp_set_error(SSSP_ERR_INVALID, "source %u >= n = %u", source, g->n);
             HIP_OK(hipSetDevice(g->device));
-            return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
+            // the whole solve in one workgroup (the batched kernel)
+            if (g->cfg.single) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
+            const ResShape r = resident_shape(g);
+            if (r.fits && !g->prof) {  // per-kernel timing is about the phase kernels
+                bool ran = false;
+                uint32_t phases = 0;
+                int rc = resident_scratch(g, r);
+                if (rc == SSSP_OK)
+                    rc = resident_solve(g, r, source, in, out == OUT_STATIC_M, dist_out, g->res, &phases, &ran);
+                if (rc) return rc;
+                if (ran) {
+                    if (phases_out) *phases_out = phases;
+                    return SSSP_OK;
+                }
+            }
         }
     }
     sssp_stats st;
@@ -3255,7 +3280,7 @@ extern "C" int sssp_set_launch(sssp_graph *g, const sssp_launch_cfg *cfg) {
     g->cfg.chunk = (int)cfg->chunk;
     g->cfg.use_graph = cfg->use_graph != 0;
     g->cfg.queue = (int)cfg->queue;
-    g->cfg.single = cfg->single != 0;
+    g->cfg.single = cfg->single < kPhaseKernels ? (int)cfg->single : kPhaseKernels;
     return SSSP_OK;
 }
 
@@ -3417,6 +3442,17 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
     unsigned char *base = nullptr;
     int rc = noalloc_scratch(g->device, &base);
     if (rc) return rc;
+    const ResShape r = resident_shape(g);
+    if (r.fits && r.bytes <= kNoAllocBytes) {
+        bool ran = false;
+        uint32_t phases = 0;
+        rc = resident_solve(g, r, source, in, out == OUT_STATIC_M, dist_out, base, &phases, &ran);
+        if (rc) return rc;
+        if (ran) {
+            if (phases_out) *phases_out = phases;
+            return SSSP_OK;
+        }
+    }
     KArgs a;
     memset(&a, 0, sizeof a);
     a.g = dev_view(g);

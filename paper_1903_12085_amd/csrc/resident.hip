@@ -1,0 +1,711 @@
+// Resident phased solver (static criteria): the whole solve of one query in one
+// cooperative launch, for sssp_solve and sssp_solve_noalloc.
+//
+// W workgroups (a power of two) stay on the device for the whole solve. The
+// vertices are cut into groups of K = 8 (16) consecutive ones; every group has an
+// owner, one wavefront of one workgroup, that keeps in LDS the minima over the
+// group's queued vertices of the IN-STATIC key d - minIn, of d and of d + minOut,
+// and which of its vertices have settled. A phase (Section 3) then is, for a
+// wavefront:
+//   1. select   a lane per group: it is active if a relax of the last phase marked
+//               it, or if its minima pass the phase's thresholds. Every other group
+//               can neither settle a vertex nor change its minima.
+//   2. identify a row of K lanes per active group: load the vertices' distances,
+//               what the last phase delivered, and static minima; certify (eq.
+//               crit:instatic, crit:outstatic), refresh the group's minima, cut
+//               the out-edges of the settled vertices into segments of 16.
+//   3. relax    a row of 16 lanes per segment: edge, target, 64-bit atomicMin into
+//               the target's box; a mark on the target's group; fold into the next
+//               minD / threshold.
+//   4. combine  each workgroup publishes its next minD and threshold; reading
+//               everybody's is both the reduction and the phase's only barrier.
+// A phase must not see what the same phase delivers: a fast workgroup relaxes
+// while a slow one still identifies. Each vertex therefore has two boxes, and
+// each group two marks: relax of phase k writes those of parity k + 1, identify
+// of phase k reads those of parity k and keeps the distance itself, which nobody
+// else writes. Boxes and marks need no clearing: box values only fall, and a
+// mark is the number of the phase it is for.
+//
+// Skewed graphs (a row over kShareDeg edges): one workgroup's segments would
+// hold up all, so its segments form one list, and rows past a quota, or longer
+// than kHubEdges, become records in device memory that all workgroups relax. A
+// second barrier, awaited after the own segments, tells how many there are.
+//
+// What bounds a phase is a chain of dependent round trips (mark, distance, edge,
+// target, atomic and mark, barrier) and the skew between workgroups, not bytes:
+// of the 10.4 us of a phase on the 2^22-vertex random graph about 2 are the
+// barrier. The phase kernels need two launches a phase and about ten round
+// trips: 24.9 us there, 15.9 on a 1023 x 997 grid (5.0 here), 25.9 on R-MAT 22
+// (15.4 here), 18.0 on 16384 vertices of degree 8 (4.8 here).
+//
+// Values that several workgroups touch go through device-scope atomics, loads
+// and stores; everything a workgroup wrote has completed when it publishes.
+#include <string.h>
+
+#include "common.h"
+#include "graph.h"
+
+constexpr uint32_t kSegEdges = 16;     // edges per segment = lanes per row in relax
+constexpr uint32_t kResMaxW = 256;
+constexpr uint32_t kMaxJ = 4;          // slots per thread
+constexpr uint32_t kSlotStride = 8;    // u64 between two workgroups' barrier words (64 bytes)
+constexpr uint32_t kWaveSegs = 64;     // segments a wavefront holds in LDS; further settled vertices stay pending
+constexpr uint32_t kHubEdges = 1024;   // longer rows are cut by the whole wavefront
+constexpr uint32_t kShareEdges = 256;  // edges of a shared record (more for a hub past kShareCap / 2 records)
+constexpr uint32_t kShareCap = 1024;   // shared records per workgroup and phase
+constexpr uint32_t kShareDeg = 128;    // graphs with a longer row share records (see `share` in ResArgs)
+constexpr uint32_t kQuota = 64;        // segments a list takes in a phase before further rows are shared
+constexpr uint32_t kResSpin = 1u << 21;
+// Barrier word: tag (4 bits) and value (all ones: infinity; distances and thresholds stay below
+// 2^58 + 2^32).
+constexpr unsigned long long kVal = (1ull << 60) - 1, kTag = ~kVal;
+
+struct ResCtl {
+    unsigned long long a[2][kResMaxW * kSlotStride];  // by barrier parity: tagged minD, tagged threshold
+    unsigned long long b[2][kResMaxW * kSlotStride];  // by phase parity: tagged count of shared records
+    unsigned int rank[16 * 32];                       // arrivals per XCD
+    unsigned int team;                                // 1 + the XCD whose workgroups form the team
+    unsigned int error;
+    unsigned int phases;
+};
+
+struct ResArgs {
+    const uint32_t *rp;
+    const uint2 *edges;
+    const uint2 *vmin;
+    const uint32_t *emin;
+    unsigned long long *dist;  // owners' distances; the output
+    unsigned long long *box;   // per vertex, by phase parity: the lowest candidate relaxes delivered
+    uint8_t *mark;       // by phase parity, W rows of mstride bytes: the phase tag each slot was last marked for
+    unsigned long long *rec;    // W rows of kShareCap records (first edge and count, distance)
+    ResCtl *ctl;
+    uint32_t n, src, wmax;
+    uint32_t W, lgW;     // workgroups
+    uint32_t lgWv;       // wavefronts per workgroup
+    uint32_t wslots;     // slots per wavefront, a multiple of 64
+    uint32_t mstride;    // slots per workgroup
+    uint32_t one_xcd;    // the W workgroups are taken from one XCD
+    uint32_t quota;      // segments a wavefront keeps for itself in a phase
+    uint32_t share;      // rows beyond the quota become records relaxed by all workgroups
+    uint32_t lgK;        // vertices per group
+};
+
+__device__ __forceinline__ unsigned long long ld64(const unsigned long long *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void st_agent(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t umin32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+// Minimum over K = 8 or 16 consecutive lanes.
+template <int K>
+__device__ __forceinline__ unsigned long long row_min64(unsigned long long x) {
+    x = umin64(x, dpp64<kDppQuadSwap1>(x));
+    x = umin64(x, dpp64<kDppQuadSwap2>(x));
+    x = umin64(x, dpp64<kDppHalfMirror>(x));
+    return K == 16 ? umin64(x, dpp64<kDppMirror>(x)) : x;
+}
+template <int K>
+__device__ __forceinline__ uint32_t row_min32(uint32_t x) {
+    x = umin32(x, dpp32<kDppQuadSwap1>(x));
+    x = umin32(x, dpp32<kDppQuadSwap2>(x));
+    if (K >= 8) x = umin32(x, dpp32<kDppHalfMirror>(x));
+    return K >= 16 ? umin32(x, dpp32<kDppMirror>(x)) : x;
+}
+// Minima of values that are INF64 or at least `base` (everything a phase keeps lies above its minD):
+// the distances from the base mostly fit in 32 bits, which takes a quarter of the instructions.
+__device__ __forceinline__ uint32_t rel32(unsigned long long x, unsigned long long base) {
+    const unsigned long long r = x - base;
+    return r >> 32 ? INF32 : (uint32_t)r;
+}
+template <int K>
+__device__ __forceinline__ unsigned long long row_min_rel(unsigned long long x, unsigned long long base) {
+    const uint32_t m = row_min32<K>(rel32(x, base));
+    if (__ballot(m == INF32 && x != INF64)) return row_min64<K>(x);  // wavefront-uniform
+    return m == INF32 ? INF64 : base + m;
+}
+__device__ __forceinline__ unsigned long long wave_min_rel(unsigned long long x, unsigned long long base) {
+    const uint32_t r = row_min32<16>(rel32(x, base));
+    const uint32_t m = umin32(umin32((uint32_t)__builtin_amdgcn_readlane((int)r, 0), (uint32_t)__builtin_amdgcn_readlane((int)r, 16)),
+                              umin32((uint32_t)__builtin_amdgcn_readlane((int)r, 32), (uint32_t)__builtin_amdgcn_readlane((int)r, 48)));
+    if (m != INF32) return base + m;
+    return __ballot(x != INF64) ? wave_min64(x) : INF64;
+}
+// a / b rounded up, for any a (a row may hold nearly 2^32 edges)
+__device__ __forceinline__ uint32_t ceil_div(uint32_t a, uint32_t b) { return a / b + (a % b != 0); }
+__device__ __forceinline__ uint32_t phase_tag(uint32_t k) { return k % 255u + 1u; }
+__device__ __forceinline__ unsigned long long bar_tag(uint32_t b) { return (unsigned long long)((b >> 1) % 15u + 1u) << 60; }
+
+// Group g belongs to workgroup g mod W, there to wavefront (g / W) mod (wavefronts), as that
+// wavefront's slot: neighbouring groups are spread over workgroups first, then over wavefronts.
+__device__ __forceinline__ uint64_t mark_of(const ResArgs &a, uint32_t g) {
+    const uint32_t t = g >> a.lgW;
+    return (uint64_t)(g & (a.W - 1)) * a.mstride + (t & ((1u << a.lgWv) - 1u)) * a.wslots + (t >> a.lgWv);
+}
+
+__global__ void k_res_init(ResArgs a) {
+    const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t v = t0; v < a.n; v += stride) {
+        const unsigned long long x = v == a.src ? 0ull : INF64;
+        a.dist[v] = x;
+        a.box[2 * v] = x;
+        a.box[2 * v + 1] = x;
+    }
+    const uint64_t src_mark = mark_of(a, a.src >> a.lgK);
+    uint32_t *mw = reinterpret_cast<uint32_t *>(a.mark);
+    for (uint64_t i = t0; i < (uint64_t)a.W * a.mstride / 2; i += stride)
+        mw[i] = i == src_mark / 4 ? phase_tag(0) << (8 * (src_mark & 3)) : 0u;
+    uint32_t *c = reinterpret_cast<uint32_t *>(a.ctl);
+    for (uint64_t i = t0; i < sizeof(ResCtl) / 4; i += stride) c[i] = 0;
+}
+
+struct Seg {
+    uint32_t e, len;
+    unsigned long long d;
+};
+
+static size_t res_lds(uint32_t slots, int bs) {
+    return (size_t)bs / 64 * kWaveSegs * sizeof(Seg) + (size_t)slots * (3 * 8 + 3 * 2);
+}
+
+__device__ __forceinline__ void wave_fence() {  // LDS values pass between lanes of one wavefront
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int BS, int K, int IN, bool OUT>
+__global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
+    extern __shared__ unsigned long long dyn[];
+    constexpr uint32_t kWv = BS / 64, kR = 64 / K;
+    __shared__ unsigned long long s_red[2 * kWv];
+    __shared__ unsigned long long s_all[2 * (kResMaxW / 64)];
+    __shared__ uint32_t s_wn[kWv], s_wl[kWv];  // per list: segments reserved, first reservation that failed
+    __shared__ uint32_t s_pend, s_nsh, s_shlim, s_flags, s_wg;
+    __shared__ uint32_t s_sh[kResMaxW + 1];    // exclusive prefix of the workgroups' shared records
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t li = lane & (K - 1);        // the lane's vertex in its row's group
+    const uint32_t W = a.W, NS = a.mstride, n = a.n, nj = a.wslots / 64, ws0 = wave * a.wslots;
+    ResCtl *ctl = a.ctl;
+    // segments: each wavefront cuts and relaxes its own; with `share`, all go to one list whose
+    // segments the workgroup's rows take in turn
+    const uint32_t lw = a.share ? 0u : wave, rows = a.share ? BS / kSegEdges : 64 / kSegEdges;
+    const uint32_t row0 = (a.share ? tid : lane) / kSegEdges, room = a.share ? kWv * kWaveSegs : kWaveSegs;
+    Seg *seg = reinterpret_cast<Seg *>(dyn) + lw * kWaveSegs;
+    unsigned long long *gk = dyn + 2 * kWv * kWaveSegs, *gd = gk + NS, *go = gd + NS;
+    uint16_t *sset = reinterpret_cast<uint16_t *>(go + NS), *pend = sset + NS;
+    uint16_t *lst = pend + NS + ws0;  // the wavefront's active slots
+
+    // the workgroup's rank in the team
+    uint32_t wg = blockIdx.x;
+    if (a.one_xcd) {  // the others leave: an L2 of its own serves the whole team
+        // the first XCD on which W workgroups have arrived is the team's; the launch holds 8 W
+        // workgroups, so one of the eight gets there whatever their placement
+        if (tid == 0) {
+            const uint32_t x = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xfu;  // HW_REG_XCC_ID
+            const uint32_t r = atomicAdd(&ctl->rank[x * 32], 1u);
+            if (r == W - 1) atomicCAS(&ctl->team, 0u, x + 1);
+            uint32_t t = 0, spins = 0;
+            while (!(t = __hip_atomic_load(&ctl->team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < kResSpin)
+                __builtin_amdgcn_s_sleep(1);
+            if (!t) atomicOr(&ctl->error, 1u);
+            s_wg = t == x + 1 && r < W ? r : INF32;
+        }
+        __syncthreads();
+        wg = s_wg;
+        if (wg == INF32) return;
+    }
+    for (uint32_t s = tid; s < NS; s += BS) {
+        gk[s] = gd[s] = go[s] = INF64;
+        sset[s] = pend[s] = 0;
+    }
+    if (tid == 0) {
+        s_pend = s_nsh = s_flags = 0;
+        s_shlim = kShareCap;
+    }
+    if (lane == 0) {
+        s_wn[wave] = 0;
+        s_wl[wave] = a.quota;
+    }
+    const uint64_t mall = (uint64_t)W * a.mstride;  // marks of one parity
+    const uint8_t *mk = a.mark + (uint64_t)wg * a.mstride + ws0;
+    gk += ws0;  // from here on the wavefront's own slots only
+    gd += ws0;
+    go += ws0;
+    sset += ws0;
+    pend += ws0;
+    auto first_vertex = [&](uint32_t s) { return ((((s * kWv + wave) << a.lgW) | wg)) * K; };
+    unsigned long long *myshare = a.rec + 2ull * kShareCap * wg;
+    unsigned long long minD = 0, T = OUT ? min_out64(a.vmin[a.src].y, a.wmax, a.rp, a.src) : 0ull;
+    __syncthreads();
+
+    // Cuts the row [r0, r0 + deg) of a settled vertex at distance d into segments of this
+    // wavefront's list; false when they do not fit in cap.
+    auto push_own = [&](uint32_t r0, uint32_t deg, unsigned long long d, uint32_t cap) {
+        const uint32_t ns = ceil_div(deg, kSegEdges), p = atomicAdd(&s_wn[lw], ns);
+        if (p + ns > cap) {
+            atomicMin(&s_wl[lw], p);  // reservations only grow, so every later one fails too
+            return false;
+        }
+        for (uint32_t i = 0; i < ns; ++i)
+            seg[p + i] = Seg{r0 + i * kSegEdges, umin32(deg - i * kSegEdges, kSegEdges), d};
+        return true;
+    };
+    // Reserves nr shared records; their index, or kShareCap when there is no room.
+    auto reserve_shared = [&](uint32_t nr) {
+        const uint32_t q = atomicAdd(&s_nsh, nr);
+        if (q < kShareCap && nr <= kShareCap - q) return q;
+        atomicMin(&s_shlim, q);
+        return kShareCap;
+    };
+    auto write_shared = [&](uint32_t q, uint32_t e, uint32_t len, unsigned long long d) {
+        st_agent(&myshare[2 * q], ((unsigned long long)len << 32) | e);
+        st_agent(&myshare[2 * q + 1], d);
+    };
+
+    for (uint32_t k = 0; minD != INF64; ++k) {
+        const uint32_t par = k & 1;
+        const unsigned long long tag = bar_tag(k);
+        // 1. the wavefront's active groups
+        const uint8_t pt = (uint8_t)phase_tag(k);
+        uint32_t na = 0;  // wavefront-uniform
+        {
+            uint8_t m[kMaxJ];
+#pragma unroll
+            for (uint32_t j = 0; j < kMaxJ; ++j) {
+                m[j] = 0;
+                if (j < nj) m[j] = __hip_atomic_load(mk + par * mall + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < kMaxJ; ++j) {
+                if (j >= nj) break;  // block-uniform
+                const uint32_t s = j * 64 + lane;
+                const unsigned long long d = gd[s];
+                const bool act = m[j] == pt || (IN != IN_NONE && gk[s] <= minD) || (OUT && d != INF64 && d <= T);
+                const unsigned long long mask = __ballot(act);
+                if (act) lst[na + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)s;
+                na += (uint32_t)__popcll(mask);
+            }
+        }
+        wave_fence();
+        // 2. identify: kR groups per step, the next step's loads issued before this one's work
+        struct Cand {
+            uint32_t s, v, r0, r1;
+            unsigned long long d, x;
+            uint2 mm;
+        };
+        auto load = [&](uint32_t i0) {
+            Cand c{INF32, 0u, 0u, 0u, INF64, INF64, make_uint2(INF32, INF32)};
+            const uint32_t i = i0 + lane / K;
+            if (i < na) {
+                c.s = lst[i];
+                c.v = first_vertex(c.s) + li;
+                if (c.v < n) {
+                    c.d = a.dist[c.v];
+                    c.x = ld64(&a.box[2ull * c.v + par]);
+                    c.mm = a.vmin[c.v];
+                    c.r0 = a.rp[c.v];
+                    c.r1 = a.rp[c.v + 1];
+                }
+            }
+            return c;
+        };
+        bool waiting = false;  // wavefront-uniform: some settled rows found no room
+        Cand nxt = load(0);
+        for (uint32_t i0 = 0; i0 < na; i0 += kR) {
+            Cand c = nxt;
+            if (i0 + kR < na) nxt = load(i0 + kR);
+            if (c.x < c.d) {  // the last phase's relaxes lowered it
+                c.d = c.x;
+                a.dist[c.v] = c.x;
+            }
+            const bool q = c.d != INF64 && !((uint32_t)sset[c.s] >> li & 1u);  // d is INF64 without a group
+            const unsigned long long mi = min_in_test(c.mm.x);
+            const unsigned long long key = IN == IN_DIJK ? c.d : c.d > mi ? c.d - mi : 0ull;  // d - minIn
+            bool ok = false;
+            if (IN != IN_NONE) ok = key <= minD;  // eq. crit:instatic
+            if (OUT) ok = ok || c.d <= T;         // eq. crit:outstatic
+            ok = ok && q;
+            const uint32_t deg = c.r1 - c.r0;
+            bool wait = false;
+            const unsigned long long okm = __ballot(ok);
+            if (okm) {
+                if (ok && deg > 0 && deg <= kHubEdges) {
+                    if (!push_own(c.r0, deg, c.d, a.quota)) {
+                        const uint32_t nr = ceil_div(deg, kShareEdges), qi = a.share ? reserve_shared(nr) : kShareCap;
+                        wait = qi == kShareCap;
+                        if (!wait)
+                            for (uint32_t i = 0; i < nr; ++i)
+                                write_shared(qi + i, c.r0 + i * kShareEdges,
+                                             umin32(deg - i * kShareEdges, kShareEdges), c.d);
+                    }
+                }
+                for (unsigned long long hm = __ballot(ok && deg > kHubEdges); hm; hm &= hm - 1) {
+                    const int l = __ffsll((long long)hm) - 1;
+                    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)c.r0, l);
+                    const uint32_t dg = (uint32_t)__builtin_amdgcn_readlane((int)deg, l);
+                    const unsigned long long hd = readlane64(c.d, l);
+                    uint32_t len = kShareEdges;
+                    while (ceil_div(dg, len) > kShareCap / 2) len *= 2;
+                    const uint32_t nr = ceil_div(dg, len);
+                    uint32_t qi = 0;
+                    if (lane == 0) qi = a.share ? reserve_shared(nr) : kShareCap;
+                    qi = (uint32_t)__builtin_amdgcn_readlane((int)qi, 0);
+                    if (qi == kShareCap) wait = wait || (int)lane == l;
+                    else
+                        for (uint32_t i = lane; i < nr; i += 64) write_shared(qi + i, e + i * len, umin32(dg - i * len, len), hd);
+                }
+            }
+            const bool keep = q && !ok;
+            const unsigned long long rk = IN != IN_NONE ? row_min_rel<K>(keep ? key : INF64, minD) : INF64;
+            const unsigned long long rd = row_min_rel<K>(keep ? c.d : INF64, minD);
+            const unsigned long long ro =
+                OUT ? row_min_rel<K>(keep ? sadd64(c.d, min_out64(c.mm.y, a.wmax, a.rp, c.v)) : INF64, minD) : INF64;
+            const unsigned long long wm = __ballot(wait);
+            waiting = waiting || wm != 0;
+            if (c.s != INF32 && li == 0) {
+                const uint32_t sh = lane & ~(K - 1u), low = (1u << K) - 1u;
+                if (IN != IN_NONE) gk[c.s] = rk;
+                gd[c.s] = rd;
+                if (OUT) go[c.s] = ro;
+                if (okm >> sh & low) sset[c.s] |= (uint16_t)(okm >> sh & low);
+                if (wm >> sh & low) pend[c.s] = (uint16_t)(wm >> sh & low);
+            }
+        }
+        if (a.share) {
+            if (waiting && lane == 0) s_pend = 1;
+            __builtin_amdgcn_s_waitcnt(0);  // this wavefront's records are written
+            __syncthreads();
+            if (tid == 0) st_agent(&ctl->b[par][wg * kSlotStride], tag | umin32(s_nsh, s_shlim));
+        }
+        wave_fence();
+        uint32_t nseg = umin32(s_wn[lw], s_wl[lw]);
+        // 3. relax. A candidate below both of its target's boxes passes. Together they hold the target's
+        // distance at phase start (and perhaps lower candidates of this phase), so none passes towards
+        // a settled target. Folding one that another candidate of this phase undercuts changes no
+        // minimum, since the lower one is folded too, so the atomic returns nothing.
+        unsigned long long fm = INF64, ft = INF64;
+        const uint8_t nt = (uint8_t)phase_tag(k + 1);
+        auto apply = [&](uint2 ed, uint32_t em, unsigned long long cur, unsigned long long d) {
+            const unsigned long long cand = d + ed.y;
+            if (cand >= cur) return;
+            (void)__hip_atomic_fetch_min(&a.box[2ull * ed.x + (par ^ 1)], cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            st_agent(a.mark + (par ^ 1) * mall + mark_of(a, ed.x / K), nt);
+            fm = umin64(fm, cand);
+            if (OUT) ft = umin64(ft, sadd64(cand, min_out64(em, a.wmax, a.rp, ed.x)));
+        };
+        auto target = [&](uint32_t v) { return umin64(ld64(&a.box[2ull * v]), ld64(&a.box[2ull * v + 1])); };
+        // relaxes edges [e, e + len) at distance d by the wavefront
+        auto relax_range = [&](uint32_t e, uint32_t len, unsigned long long d) {
+            for (uint64_t j0 = lane; j0 < len; j0 += 256) {
+                uint2 he[4];
+                uint32_t hm[4];
+                unsigned long long hc[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    he[j] = make_uint2(0u, 0u);
+                    hm[j] = INF32;
+                    if (j0 + j * 64 < len) {
+                        he[j] = a.edges[e + j0 + j * 64];
+                        if (OUT) hm[j] = a.emin[e + j0 + j * 64];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) hc[j] = j0 + j * 64 < len ? target(he[j].x) : 0ull;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) apply(he[j], hm[j], hc[j], d);
+            }
+        };
+        uint2 ed = make_uint2(0u, 0u);
+        uint32_t em = INF32;
+        unsigned long long cur = 0, sd = 0;
+        auto fetch = [&](uint32_t i) {  // lane l of a row of 16: edge l of segment i
+            cur = 0;
+            if (i < nseg) {
+                const Seg sg = seg[i];
+                const uint32_t l = lane & (kSegEdges - 1);
+                if (l < sg.len) {
+                    ed = a.edges[sg.e + l];
+                    if (OUT) em = a.emin[sg.e + l];
+                    sd = sg.d;
+                    cur = target(ed.x);
+                }
+            }
+        };
+        auto relax_own = [&]() {  // the first step's edges are fetched
+            for (uint32_t i = row0; __ballot(i < nseg); i += rows) {
+                const uint2 ped = ed;
+                const uint32_t pem = em;
+                const unsigned long long pcur = cur, psd = sd;
+                fetch(i + rows);  // before this step's atomics, so that its loads do not queue behind them
+                apply(ped, pem, pcur, psd);
+            }
+        };
+        fetch(row0);
+        // the workgroup's minima over what it keeps
+#pragma unroll
+        for (uint32_t j = 0; j < kMaxJ; ++j)
+            if (j < nj) {
+                fm = umin64(fm, gd[j * 64 + lane]);
+                if (OUT) ft = umin64(ft, go[j * 64 + lane]);
+            }
+        relax_own();
+        // Rows that found no room, as many as fit: segments of this wavefront's pending vertices
+        // (hubs are relaxed at once). True if some are left.
+        auto refill = [&]() {
+            bool full = false, left = false;
+            for (uint32_t j = 0; j < nj; ++j) {
+                const uint32_t s = j * 64 + lane;
+                uint32_t p = pend[s];
+                while (!full && __ballot(p != 0)) {
+                    uint32_t r0 = 0, deg = 0;
+                    unsigned long long d = 0;
+                    if (p) {
+                        const uint32_t v = first_vertex(s) + __ffs(p) - 1;
+                        r0 = a.rp[v];
+                        deg = a.rp[v + 1] - r0;
+                        d = a.dist[v];
+                    }
+                    const bool hub = deg > kHubEdges;
+                    const bool took = hub || (p && push_own(r0, deg, d, room));
+                    for (unsigned long long hm = __ballot(hub); hm; hm &= hm - 1) {
+                        const int l = __ffsll((long long)hm) - 1;
+                        relax_range((uint32_t)__builtin_amdgcn_readlane((int)r0, l),
+                                    (uint32_t)__builtin_amdgcn_readlane((int)deg, l), readlane64(d, l));
+                    }
+                    full = __ballot(p && !took) != 0;
+                    if (took) p &= p - 1;
+                }
+                pend[s] = (uint16_t)p;
+                left = left || __ballot(p != 0) != 0;
+            }
+            return left;
+        };
+        while (!a.share && waiting) {  // wavefront-uniform
+            wave_fence();
+            if (lane == 0) {
+                s_wn[wave] = 0;
+                s_wl[wave] = room;
+            }
+            wave_fence();
+            waiting = refill();
+            wave_fence();
+            nseg = umin32(s_wn[wave], s_wl[wave]);
+            fetch(row0);
+            relax_own();
+        }
+        if (a.share) {
+            if (tid < W) {
+                uint32_t spins = 0;
+                unsigned long long v;
+                while (((v = ld64(&ctl->b[par][tid * kSlotStride])) & kTag) != tag && ++spins < kResSpin) {}
+                s_sh[tid] = (uint32_t)v;
+                if ((v & kTag) != tag) atomicOr(&s_flags, 1u);
+                else if (v & kVal) atomicOr(&s_flags, 2u);
+            }
+            __syncthreads();
+            uint32_t pending = s_pend;
+            if (s_flags == 2u) {  // block-uniform
+                if (wave == 0) {  // counts to an exclusive prefix, four per lane
+                    uint32_t c[4], sum = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        c[j] = 4 * lane + j < W ? s_sh[4 * lane + j] : 0u;
+                        sum += c[j];
+                    }
+                    const uint32_t incl = wave_incl_scan(sum);
+                    uint32_t o = incl - sum;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (4 * lane + j < W) s_sh[4 * lane + j] = o;
+                        o += c[j];
+                    }
+                    if (lane == 63) s_sh[W] = incl;
+                }
+                __syncthreads();
+                const uint32_t shared = s_sh[W];
+                // one record per wavefront, spread over the workgroups first
+                for (uint32_t r = wg + W * wave; r < shared; r += W * kWv) {
+                    uint32_t lo = 0;  // last workgroup whose first record is <= r
+                    for (uint32_t st = W / 2; st > 0; st >>= 1)
+                        if (s_sh[lo + st] <= r) lo += st;
+                    const unsigned long long *rec = a.rec + 2ull * (kShareCap * lo + (r - s_sh[lo]));
+                    const unsigned long long x = ld64(rec), d = ld64(rec + 1);
+                    relax_range((uint32_t)x, (uint32_t)(x >> 32), d);
+                }
+            }
+            while (pending) {  // block-uniform
+                __syncthreads();
+                if (tid == 0) {
+                    s_pend = s_wn[0] = 0;
+                    s_wl[0] = room;
+                }
+                __syncthreads();
+                if (refill() && lane == 0) s_pend = 1;
+                __syncthreads();
+                pending = s_pend;
+                nseg = umin32(s_wn[0], s_wl[0]);
+                fetch(row0);
+                relax_own();
+            }
+        }
+        // 4. combine: publish this workgroup's minima and read everybody's
+        fm = wave_min_rel(fm, minD);
+        if (OUT) ft = wave_min_rel(ft, minD);
+        if (lane == 0) {
+            s_red[wave] = fm;
+            if (OUT) s_red[kWv + wave] = ft;
+        }
+        __builtin_amdgcn_s_waitcnt(0);  // this thread's atomics and marks have completed
+        __syncthreads();
+        if (lane == 0) {
+            s_wn[wave] = 0;
+            s_wl[wave] = a.quota;
+        }
+        if (tid == 0) {
+            s_pend = s_nsh = 0;
+            s_flags &= 1u;
+            s_shlim = kShareCap;
+        }
+        if (wave == 0) {  // lanes below kWv: the minima, the next kWv: the thresholds
+            unsigned long long x = lane < (OUT ? 2 * kWv : kWv) ? s_red[lane] : INF64;
+            x = umin64(x, dpp64<kDppQuadSwap1>(x));
+            x = umin64(x, dpp64<kDppQuadSwap2>(x));
+            if (kWv >= 8) x = umin64(x, dpp64<kDppHalfMirror>(x));
+            if (kWv >= 16) x = umin64(x, dpp64<kDppMirror>(x));
+            if (lane == 0 || (OUT && lane == kWv))
+                st_agent(&ctl->a[par][wg * kSlotStride + (lane ? 1 : 0)], tag | umin64(x, kVal));
+        }
+        unsigned long long pm = kVal, pt2 = kVal;
+        if (tid < W) {
+            const unsigned long long *w = &ctl->a[par][tid * kSlotStride];
+            uint32_t spins = 0;
+            for (;;) {
+                pm = ld64(w);
+                if (OUT) pt2 = ld64(w + 1);
+                if ((pm & kTag) == tag && (!OUT || (pt2 & kTag) == tag)) break;
+                if (++spins >= kResSpin) {
+                    atomicOr(&s_flags, 1u);
+                    break;
+                }
+            }
+            pm &= kVal;
+            if (OUT) pt2 &= kVal;
+        }
+        if (wave * 64 < W) {
+            pm = wave_min_rel(pm == kVal ? INF64 : pm, minD);
+            if (OUT) pt2 = wave_min_rel(pt2 == kVal ? INF64 : pt2, minD);
+            if (lane == 0) {
+                s_all[wave] = pm;
+                s_all[kResMaxW / 64 + wave] = pt2;
+            }
+        }
+        __syncthreads();
+        if (s_flags & 1u) {  // block-uniform
+            if (tid == 0) atomicOr(&ctl->error, 1u);
+            return;
+        }
+        pm = s_all[0];
+        pt2 = s_all[kResMaxW / 64];
+        for (uint32_t i = 1; i * 64 < W; ++i) {
+            pm = umin64(pm, s_all[i]);
+            pt2 = umin64(pt2, s_all[kResMaxW / 64 + i]);
+        }
+        minD = readlane64(pm, 0);
+        if (OUT) T = readlane64(pt2, 0);
+        if (k > n) {  // a phase settles at least the queue minimum
+            if (tid == 0) atomicOr(&ctl->error, 2u);
+            return;
+        }
+        if (minD == INF64 && wg == 0 && tid == 0) st_agent(&ctl->phases, k + 1);
+    }
+}
+
+typedef void (*rfn)(ResArgs);
+
+template <int BS, int K>
+static rfn pick_res_bs(int in, bool out) {
+    if (in == IN_DIJK) return out ? k_resident<BS, K, IN_DIJK, true> : k_resident<BS, K, IN_DIJK, false>;
+    if (in == IN_STATIC_M) return out ? k_resident<BS, K, IN_STATIC_M, true> : k_resident<BS, K, IN_STATIC_M, false>;
+    return k_resident<BS, K, IN_NONE, true>;
+}
+
+static rfn pick_res(int bs, int lgK, int in, bool out) {
+    if (bs == 512) return lgK == 3 ? pick_res_bs<512, 8>(in, out) : pick_res_bs<512, 16>(in, out);
+    return lgK == 3 ? pick_res_bs<1024, 8>(in, out) : pick_res_bs<1024, 16>(in, out);
+}
+// Shape by the number of edges, measured on MI355X (us per phase; random, R-MAT and grid graphs):
+//   below 2^20 edges one XCD: its workgroups share an L2, so barriers and marks stay in it (grid of
+//   249 k vertices: 4.4 on 32 workgroups of one XCD, 4.8 on 128 of all; R-MAT 16: 8.0 against 8.3);
+//   512 threads while phases are so small that a wavefront's instructions count (below 2^18 edges).
+//   Up to 2^23 edges 128 workgroups (random, 1 M vertices of degree 4: 6.3 against 6.7 on 256 and 7.1
+//   on 64; grid of 1 M vertices: 5.0, 5.8 and 5.0), then one on every CU (random, 1 M vertices of
+//   degree 16: 7.4 against 8.5 on 64).
+// Groups of 8 vertices move half the bytes of groups of 16, which only graphs of more than 2^23
+// vertices need to fit their slots into LDS. Where the slots still do not fit, the next shape is taken.
+ResShape resident_shape(const sssp_graph *g) {
+    struct Shape { uint64_t max_m; uint32_t W; int bs; uint32_t one_xcd, lgK; };
+    static const Shape shapes[] = {{1ull << 18, 32, 512, 1, 3},   {1ull << 20, 32, 1024, 1, 3},
+                                   {1ull << 23, 128, 1024, 0, 3}, {UINT64_MAX, 256, 1024, 0, 3},
+                                   {UINT64_MAX, 256, 1024, 0, 4}};
+    ResShape r{};
+    for (const Shape &s : shapes) {
+        if (g->m >= s.max_m) continue;
+        const uint32_t groups = ((g->n - 1) >> s.lgK) + 1;
+        r.W = s.W;
+        while (r.W > 1 && r.W / 2 >= groups) r.W /= 2;
+        r.bs = s.bs;
+        r.lgK = s.lgK;
+        r.one_xcd = r.W > 1 ? s.one_xcd : 0;
+        const uint32_t per = r.W * r.bs, nj = (groups - 1) / per + 1;  // slots of every thread
+        r.slots = nj * r.bs;
+        r.fits = nj <= kMaxJ;
+        if (r.fits) break;
+    }
+    r.bytes = ((sizeof(ResCtl) + 255) & ~255ull) + (uint64_t)r.W * (kShareCap * 16 + 2ull * r.slots) + 16ull * g->n;
+    return r;
+}
+
+// Runs a resident solve with `scratch` (r.bytes, 256-byte aligned). *ran = false: a workgroup waited
+// too long for another (the device is shared with other work); the distances are unfinished.
+int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static,
+                   uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran) {
+    hipStream_t s = g->stream;
+    ResArgs a;
+    a.rp = g->rp;
+    a.edges = g->edges;
+    a.vmin = g->vmin;
+    a.emin = g->emin;
+    a.dist = (unsigned long long *)dist_out;
+    a.ctl = (ResCtl *)scratch;
+    a.rec = (unsigned long long *)((uint8_t *)scratch + ((sizeof(ResCtl) + 255) & ~255ull));
+    a.box = a.rec + 2ull * kShareCap * r.W;
+    a.mark = (uint8_t *)(a.box + 2ull * g->n);
+    a.share = g->max_deg > kShareDeg;
+    a.quota = kQuota;
+    a.n = g->n;
+    a.src = source;
+    a.wmax = g->wmax;
+    a.W = r.W;
+    a.lgW = (uint32_t)__builtin_ctz(r.W);
+    a.lgK = r.lgK;
+    a.lgWv = (uint32_t)__builtin_ctz((uint32_t)r.bs / 64);
+    a.wslots = r.slots >> a.lgWv;
+    a.mstride = r.slots;
+    a.one_xcd = r.one_xcd;
+    const uint64_t ib = ((uint64_t)g->n + 255) / 256;
+    hipLaunchKernelGGL(k_res_init, dim3((uint32_t)(ib > 2048 ? 2048 : ib < 64 ? 64 : ib)), dim3(256), 0, s, a);
+    rfn k = pick_res(r.bs, r.lgK, in, out_static);
+    const size_t lds = res_lds(r.slots, r.bs);
+    if (lds > 65536) HIP_OK(hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    void *args[] = {&a};
+    HIP_OK(hipLaunchCooperativeKernel((const void *)k, dim3(r.one_xcd ? 8 * r.W : r.W), dim3(r.bs), args, (uint32_t)lds, s));
+    unsigned int h[2];
+    static_assert(offsetof(ResCtl, phases) == offsetof(ResCtl, error) + 4, "one copy");
+    HIP_OK(hipMemcpyAsync(h, &a.ctl->error, sizeof h, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    *phases = h[1];
+    *ran = h[0] == 0;
+    return SSSP_OK;
+}
