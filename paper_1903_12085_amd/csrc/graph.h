@@ -71,5 +71,5 @@ struct ResShape {
     uint64_t bytes;       // device scratch
 };
 ResShape resident_shape(const sssp_graph *g);
-int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static,
+int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran);

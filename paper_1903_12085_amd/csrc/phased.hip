@@ -3160,15 +3160,25 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     return rc;
 }
 
-// The graph's scratch for resident solves, kept between them.
-static int resident_scratch(sssp_graph *g, const ResShape &r) {
-    if (g->res_bytes >= r.bytes) return SSSP_OK;
-    sssp_free(g->res);
-    g->res = nullptr;
-    g->res_bytes = 0;
-    HIP_OK(hipMalloc(&g->res, r.bytes));
-    g->res_bytes = r.bytes;
-    return SSSP_OK;
+// A resident solve where the graph and the launch options allow one, with the graph's scratch
+// (kept between solves). *ran = false: not run, or not finished; the phase kernels then do it
+// (they also do timed solves: per-kernel timing is about them).
+static int resident_try(sssp_graph *g, uint32_t source, int in, bool out_static, uint64_t delta, uint64_t *dist_out,
+                        uint32_t *phases_out, bool *ran) {
+    *ran = false;
+    const ResShape r = resident_shape(g);
+    if (!r.fits || g->prof) return SSSP_OK;
+    if (g->res_bytes < r.bytes) {
+        sssp_free(g->res);
+        g->res = nullptr;
+        g->res_bytes = 0;
+        HIP_OK(hipMalloc(&g->res, r.bytes));
+        g->res_bytes = r.bytes;
+    }
+    uint32_t phases = 0;
+    const int rc = resident_solve(g, r, source, in, out_static, delta, dist_out, g->res, &phases, ran);
+    if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
+    return rc;
 }
 
 extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, uint64_t *dist_out,
@@ -3182,19 +3192,9 @@ extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, ui
             HIP_OK(hipSetDevice(g->device));
             // the whole solve in one workgroup (the batched kernel)
             if (g->cfg.single) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
-            const ResShape r = resident_shape(g);
-            if (r.fits && !g->prof) {  // per-kernel timing is about the phase kernels
-                bool ran = false;
-                uint32_t phases = 0;
-                int rc = resident_scratch(g, r);
-                if (rc == SSSP_OK)
-                    rc = resident_solve(g, r, source, in, out == OUT_STATIC_M, dist_out, g->res, &phases, &ran);
-                if (rc) return rc;
-                if (ran) {
-                    if (phases_out) *phases_out = phases;
-                    return SSSP_OK;
-                }
-            }
+            bool ran = false;
+            const int rc = resident_try(g, source, in, out == OUT_STATIC_M, 0, dist_out, phases_out, &ran);
+            if (rc || ran) return rc;
         }
     }
     sssp_stats st;
@@ -3212,6 +3212,12 @@ extern "C" int sssp_solve_ex(sssp_graph *g, uint32_t source, uint32_t criterion,
 extern "C" int sssp_delta_step(sssp_graph *g, uint32_t source, uint64_t delta, uint64_t *dist_out,
                                uint32_t *phases_out) {
     if (delta == 0) return sssp_set_error(SSSP_ERR_INVALID, "delta must be >= 1");
+    if (g && dist_out && source < g->n && g->cfg.single != kPhaseKernels) {
+        HIP_OK(hipSetDevice(g->device));
+        bool ran = false;
+        const int rc = resident_try(g, source, IN_NONE, false, delta, dist_out, phases_out, &ran);
+        if (rc || ran) return rc;
+    }
     sssp_stats st;
     int rc = solve_common(g, source, true, 0, &delta, 1, dist_out, &st, nullptr, nullptr, 0);
     if (rc == SSSP_OK && phases_out) *phases_out = st.phases;
@@ -3446,7 +3452,7 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
     if (r.fits && r.bytes <= kNoAllocBytes) {
         bool ran = false;
         uint32_t phases = 0;
-        rc = resident_solve(g, r, source, in, out == OUT_STATIC_M, dist_out, base, &phases, &ran);
+        rc = resident_solve(g, r, source, in, out == OUT_STATIC_M, 0, dist_out, base, &phases, &ran);
         if (rc) return rc;
         if (ran) {
             if (phases_out) *phases_out = phases;

@@ -1,5 +1,5 @@
-// Resident phased solver (static criteria): the whole solve of one query in one
-// cooperative launch, for sssp_solve and sssp_solve_noalloc.
+// Resident solver: the whole solve of one query in one cooperative launch, for
+// sssp_solve and sssp_solve_noalloc with static criteria, and for sssp_delta_step.
 //
 // W workgroups (a power of two) stay on the device for the whole solve. The
 // vertices are cut into groups of K = 8 (16) consecutive ones; every group has an
@@ -25,6 +25,13 @@
 // of phase k reads those of parity k and keeps the distance itself, which nobody
 // else writes. Boxes and marks need no clearing: box values only fall, and a
 // mark is the number of the phase it is for.
+//
+// Delta-stepping (Section 5) runs on the same structure, a round in the place of a
+// phase: the first light round of a bucket relaxes the queued vertices inside the
+// window, a further one those the last round lowered inside it (an owner sees that
+// a box undercuts its distance), the heavy round those the bucket removed. The
+// barrier carries whether anything was lowered inside the window, and after a
+// heavy round the smallest queued distance.
 //
 // Skewed graphs (a row over kShareDeg edges): one workgroup's segments would
 // hold up all, so its segments form one list, and rows past a quota, or longer
@@ -88,6 +95,7 @@ struct ResArgs {
     uint32_t quota;      // segments a wavefront keeps for itself in a phase
     uint32_t share;      // rows beyond the quota become records relaxed by all workgroups
     uint32_t lgK;        // vertices per group
+    unsigned long long delta;  // Delta-stepping: bucket width
 };
 
 __device__ __forceinline__ unsigned long long ld64(const unsigned long long *p) {
@@ -175,7 +183,7 @@ __device__ __forceinline__ void wave_fence() {  // LDS values pass between lanes
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int BS, int K, int IN, bool OUT>
+template <int BS, int K, int IN, bool OUT, bool DELTA = false>
 __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
     extern __shared__ unsigned long long dyn[];
     constexpr uint32_t kWv = BS / 64, kR = 64 / K;
@@ -195,6 +203,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
     Seg *seg = reinterpret_cast<Seg *>(dyn) + lw * kWaveSegs;
     unsigned long long *gk = dyn + 2 * kWv * kWaveSegs, *gd = gk + NS, *go = gd + NS;
     uint16_t *sset = reinterpret_cast<uint16_t *>(go + NS), *pend = sset + NS;
+    uint16_t *rset = reinterpret_cast<uint16_t *>(gk);  // Delta-stepping: vertices the bucket removed
     uint16_t *lst = pend + NS + ws0;  // the wavefront's active slots
 
     // the workgroup's rank in the team
@@ -220,6 +229,10 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
         gk[s] = gd[s] = go[s] = INF64;
         sset[s] = pend[s] = 0;
     }
+    if (DELTA) {
+        __syncthreads();  // rset lies in gk
+        for (uint32_t s = tid; s < NS; s += BS) rset[s] = 0;
+    }
     if (tid == 0) {
         s_pend = s_nsh = s_flags = 0;
         s_shlim = kShareCap;
@@ -234,6 +247,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
     gd += ws0;
     go += ws0;
     sset += ws0;
+    rset += ws0;
     pend += ws0;
     auto first_vertex = [&](uint32_t s) { return ((((s * kWv + wave) << a.lgW) | wg)) * K; };
     unsigned long long *myshare = a.rec + 2ull * kShareCap * wg;
@@ -264,6 +278,10 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
         st_agent(&myshare[2 * q + 1], d);
     };
 
+    // Delta-stepping: minD is the window's lower end, hi its upper one; round kinds 0 = first
+    // light round of a bucket, 1 = later light round, 2 = heavy round
+    int kind = 0;
+    unsigned long long hi = a.delta;
     for (uint32_t k = 0; minD != INF64; ++k) {
         const uint32_t par = k & 1;
         const unsigned long long tag = bar_tag(k);
@@ -282,7 +300,8 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
                 if (j >= nj) break;  // block-uniform
                 const uint32_t s = j * 64 + lane;
                 const unsigned long long d = gd[s];
-                const bool act = m[j] == pt || (IN != IN_NONE && gk[s] <= minD) || (OUT && d != INF64 && d <= T);
+                const bool act = m[j] == pt || (IN != IN_NONE && gk[s] <= minD) || (OUT && d != INF64 && d <= T) ||
+                                 (DELTA && (kind == 0 ? d < hi : kind == 2 && rset[s] != 0));
                 const unsigned long long mask = __ballot(act);
                 if (act) lst[na + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)s;
                 na += (uint32_t)__popcll(mask);
@@ -316,16 +335,19 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
         for (uint32_t i0 = 0; i0 < na; i0 += kR) {
             Cand c = nxt;
             if (i0 + kR < na) nxt = load(i0 + kR);
-            if (c.x < c.d) {  // the last phase's relaxes lowered it
+            const bool lowered = c.x < c.d;  // by the last phase's relaxes
+            if (lowered) {
                 c.d = c.x;
                 a.dist[c.v] = c.x;
             }
+            const bool removed = DELTA && c.s != INF32 && ((uint32_t)rset[c.s] >> li & 1u);
             const bool q = c.d != INF64 && !((uint32_t)sset[c.s] >> li & 1u);  // d is INF64 without a group
             const unsigned long long mi = min_in_test(c.mm.x);
             const unsigned long long key = IN == IN_DIJK ? c.d : c.d > mi ? c.d - mi : 0ull;  // d - minIn
             bool ok = false;
             if (IN != IN_NONE) ok = key <= minD;  // eq. crit:instatic
             if (OUT) ok = ok || c.d <= T;         // eq. crit:outstatic
+            if (DELTA) ok = kind == 2 ? removed : c.d < hi && (kind == 0 || lowered);
             ok = ok && q;
             const uint32_t deg = c.r1 - c.r0;
             bool wait = false;
@@ -357,7 +379,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
                         for (uint32_t i = lane; i < nr; i += 64) write_shared(qi + i, e + i * len, umin32(dg - i * len, len), hd);
                 }
             }
-            const bool keep = q && !ok;
+            const bool keep = q && !ok && !removed;
             const unsigned long long rk = IN != IN_NONE ? row_min_rel<K>(keep ? key : INF64, minD) : INF64;
             const unsigned long long rd = row_min_rel<K>(keep ? c.d : INF64, minD);
             const unsigned long long ro =
@@ -369,7 +391,10 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
                 if (IN != IN_NONE) gk[c.s] = rk;
                 gd[c.s] = rd;
                 if (OUT) go[c.s] = ro;
-                if (okm >> sh & low) sset[c.s] |= (uint16_t)(okm >> sh & low);
+                if (okm >> sh & low) {
+                    if (!DELTA || kind == 2) sset[c.s] |= (uint16_t)(okm >> sh & low);
+                    if (DELTA) rset[c.s] = kind == 2 ? 0 : (uint16_t)(rset[c.s] | (okm >> sh & low));
+                }
                 if (wm >> sh & low) pend[c.s] = (uint16_t)(wm >> sh & low);
             }
         }
@@ -392,9 +417,11 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
             if (cand >= cur) return;
             (void)__hip_atomic_fetch_min(&a.box[2ull * ed.x + (par ^ 1)], cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             st_agent(a.mark + (par ^ 1) * mall + mark_of(a, ed.x / K), nt);
-            fm = umin64(fm, cand);
+            if (!DELTA || kind == 2 || cand < hi) fm = umin64(fm, cand);
             if (OUT) ft = umin64(ft, sadd64(cand, min_out64(em, a.wmax, a.rp, ed.x)));
         };
+        // Delta-stepping: light rounds take edges below the width, the heavy round the others
+        auto takes = [&](uint32_t w) { return !DELTA || (w < a.delta) == (kind != 2); };
         auto target = [&](uint32_t v) { return umin64(ld64(&a.box[2ull * v]), ld64(&a.box[2ull * v + 1])); };
         // relaxes edges [e, e + len) at distance d by the wavefront
         auto relax_range = [&](uint32_t e, uint32_t len, unsigned long long d) {
@@ -412,7 +439,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) hc[j] = j0 + j * 64 < len ? target(he[j].x) : 0ull;
+                for (int j = 0; j < 4; ++j) hc[j] = j0 + j * 64 < len && takes(he[j].y) ? target(he[j].x) : 0ull;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) apply(he[j], hm[j], hc[j], d);
             }
@@ -429,7 +456,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
                     ed = a.edges[sg.e + l];
                     if (OUT) em = a.emin[sg.e + l];
                     sd = sg.d;
-                    cur = target(ed.x);
+                    if (takes(ed.y)) cur = target(ed.x);
                 }
             }
         };
@@ -446,7 +473,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
         // the workgroup's minima over what it keeps
 #pragma unroll
         for (uint32_t j = 0; j < kMaxJ; ++j)
-            if (j < nj) {
+            if (j < nj && (!DELTA || kind == 2)) {
                 fm = umin64(fm, gd[j * 64 + lane]);
                 if (OUT) ft = umin64(ft, go[j * 64 + lane]);
             }
@@ -612,9 +639,19 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
             pm = umin64(pm, s_all[i]);
             pt2 = umin64(pt2, s_all[kResMaxW / 64 + i]);
         }
-        minD = readlane64(pm, 0);
-        if (OUT) T = readlane64(pt2, 0);
-        if (k > n) {  // a phase settles at least the queue minimum
+        pm = readlane64(pm, 0);
+        if (!DELTA) {
+            minD = pm;
+            if (OUT) T = readlane64(pt2, 0);
+        } else if (kind != 2) {
+            kind = pm != INF64 ? 1 : 2;
+        } else {
+            kind = 0;
+            minD = pm != INF64 ? pm / a.delta * a.delta : INF64;
+            hi = sadd64(minD, a.delta);
+        }
+        // a phase settles at least the queue minimum; a bucket's light rounds each remove or lower
+        if (DELTA ? k / 4 > n + 16 : k > n) {
             if (tid == 0) atomicOr(&ctl->error, 2u);
             return;
         }
@@ -631,7 +668,11 @@ static rfn pick_res_bs(int in, bool out) {
     return k_resident<BS, K, IN_NONE, true>;
 }
 
-static rfn pick_res(int bs, int lgK, int in, bool out) {
+static rfn pick_res(int bs, int lgK, int in, bool out, bool delta) {
+    if (delta) {
+        if (bs == 512) return lgK == 3 ? k_resident<512, 8, IN_NONE, false, true> : k_resident<512, 16, IN_NONE, false, true>;
+        return lgK == 3 ? k_resident<1024, 8, IN_NONE, false, true> : k_resident<1024, 16, IN_NONE, false, true>;
+    }
     if (bs == 512) return lgK == 3 ? pick_res_bs<512, 8>(in, out) : pick_res_bs<512, 16>(in, out);
     return lgK == 3 ? pick_res_bs<1024, 8>(in, out) : pick_res_bs<1024, 16>(in, out);
 }
@@ -667,9 +708,10 @@ ResShape resident_shape(const sssp_graph *g) {
     return r;
 }
 
-// Runs a resident solve with `scratch` (r.bytes, 256-byte aligned). *ran = false: a workgroup waited
-// too long for another (the device is shared with other work); the distances are unfinished.
-int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static,
+// Runs a resident solve (delta > 0: Delta-stepping) with `scratch` (r.bytes, 256-byte aligned).
+// *ran = false: the device cannot hold the workgroups at once, or one waited too long for another
+// (the device is shared with other work); the distances are unfinished.
+int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran) {
     hipStream_t s = g->stream;
     ResArgs a;
@@ -694,13 +736,21 @@ int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int 
     a.wslots = r.slots >> a.lgWv;
     a.mstride = r.slots;
     a.one_xcd = r.one_xcd;
+    a.delta = delta;
     const uint64_t ib = ((uint64_t)g->n + 255) / 256;
     hipLaunchKernelGGL(k_res_init, dim3((uint32_t)(ib > 2048 ? 2048 : ib < 64 ? 64 : ib)), dim3(256), 0, s, a);
-    rfn k = pick_res(r.bs, r.lgK, in, out_static);
+    rfn k = pick_res(r.bs, r.lgK, in, out_static, delta != 0);
     const size_t lds = res_lds(r.slots, r.bs);
     if (lds > 65536) HIP_OK(hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *args[] = {&a};
-    HIP_OK(hipLaunchCooperativeKernel((const void *)k, dim3(r.one_xcd ? 8 * r.W : r.W), dim3(r.bs), args, (uint32_t)lds, s));
+    const hipError_t e = hipLaunchCooperativeKernel((const void *)k, dim3(r.one_xcd ? 8 * r.W : r.W), dim3(r.bs), args,
+                                                    (uint32_t)lds, s);
+    if (e == hipErrorCooperativeLaunchTooLarge) {
+        (void)hipGetLastError();
+        *ran = false;
+        return SSSP_OK;
+    }
+    HIP_OK(e);
     unsigned int h[2];
     static_assert(offsetof(ResCtl, phases) == offsetof(ResCtl, error) + 4, "one copy");
     HIP_OK(hipMemcpyAsync(h, &a.ctl->error, sizeof h, hipMemcpyDeviceToHost, s));

@@ -1,5 +1,5 @@
-"""Resident solves (sssp_solve and sssp_solve_noalloc with static criteria) against the CPU oracle:
-distances bit-exact, phase counts equal, where the resident kernel's cuts can go wrong: vertex
+"""Resident solves (sssp_solve and sssp_solve_noalloc with static criteria, sssp_delta_step) against
+the CPU oracle: distances bit-exact, phase and round counts equal, where the resident kernel's cuts can go wrong: vertex
 counts at the edges of its groups, every launch shape its rule picks, rows long enough to be shared
 between workgroups, phases that settle more vertices than its lists hold, and weights so large that
 values of one phase differ by more than 32 bits."""
@@ -71,6 +71,22 @@ def test_resident_matches_oracle(B, name):
     dg.close()
 
 
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_resident_delta_matches_oracle(B, name):
+    """Widths from one that makes nearly every edge heavy to one window over all distances."""
+    g = GRAPHS[name]()
+    dg = B.DeviceGraph.from_graph(g)
+    wmax = int(g.w.max()) if g.m else 1
+    src = 0 if g.m == 0 else int(G.sources(g, 1, 331)[0])
+    for delta in sorted({max(1, wmax // 16), max(1, wmax // 3), wmax, (1 << 64) - 1}):
+        print(name, delta, src, flush=True)
+        ref = O.delta_step(g, src, [delta])
+        r = B.delta_step(dg, src, delta)
+        assert np.array_equal(r.dist_u64(), ref.dist), (name, delta)
+        assert r.phases == ref.rounds, (name, delta, r.phases, ref.rounds)
+    dg.close()
+
+
 def test_resident_more_than_2_23_vertices(B):
     """The larger groups: a star's distances are its weights and it takes two phases (also one more
     vertex, reached in a third phase)."""
@@ -86,6 +102,8 @@ def test_resident_more_than_2_23_vertices(B):
     want = np.concatenate([[0], w, [w[-1] + np.uint64(9000)]]).astype(np.uint64)
     assert np.array_equal(r.dist_u64(), want)
     assert r.phases == 3
+    r = B.delta_step(dg, 0, 16384)           # one window: three light rounds and a heavy one
+    assert np.array_equal(r.dist_u64(), want) and r.phases == 4
     dg.close()
 
 
@@ -100,4 +118,6 @@ def test_launch_option_single_selects_the_solver(B):
         assert dg.launch()["single"] == kept
         r = B.solve(dg, 0, B.STATIC_OR)
         assert np.array_equal(r.dist_u64(), ref.dist) and r.phases == ref.phases
+        r = B.delta_step(dg, 0, 100)
+        assert np.array_equal(r.dist_u64(), ref.dist) and r.phases == O.delta_step(g, 0, [100]).rounds
     dg.close()
