@@ -170,17 +170,23 @@ int sssp_delta_step_ex(sssp_graph *g, uint32_t source, const uint64_t *deltas, u
  *   dist_outs  HOST array of nq DEVICE pointers, each with room for
  *              graphs[i]->n uint64; the buffers must not overlap.
  *   phases_out HOST, nq entries, may be NULL.
- * Runs on graphs[0]'s stream. The call allocates about 29 bytes of device
- * scratch per vertex of each query (a state byte, two fringe lists holding each
- * entry's vertex and static minima, a settled list) and frees it before
- * returning. Errors: SSSP_ERR_INVALID for nq = 0, a NULL pointer, a bad source
+ * Runs on graphs[0]'s stream. In the default form each query of at most 2^19
+ * vertices runs on a team of 1 to 32 workgroups (more for larger graphs, and
+ * when there are few queries), all of them in one cooperative launch; a larger
+ * graph, or a query alone, is solved on the whole device as by sssp_solve. The
+ * call allocates about 16 bytes of device scratch per vertex that its
+ * workgroups can hold (at most 16384 each), with a launch shape given about 29
+ * bytes per vertex of each query, and frees it before returning. Errors: SSSP_ERR_INVALID for nq = 0, a NULL pointer, a bad source
  * or criterion; SSSP_ERR_UNSUPPORTED for the dynamic criteria; SSSP_ERR_OOM
  * when the scratch does not fit.
  */
 int sssp_solve_batch(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq,
                      uint32_t criterion, uint64_t *const *dist_outs, uint32_t *phases_out);
 
-/* Launch shape of the batched solver. A zero field means the default.
+/* Launch shape of the batched solver. All fields zero but for a block of 0 or
+ * 512: the default form described above, whose workgroups have 512 threads.
+ * Otherwise the shape of one persistent launch of a workgroup
+ * per query, in which a zero field means the default.
  * Queries on graphs with at least team_edges edges each run on a team of
  * team_size workgroups that share its fringe and settled lists and meet at a
  * barrier twice per phase, while the other resident workgroups take the other
@@ -324,7 +330,7 @@ int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion, sssp_launc
                   float *best_ms);
 
 /*
- * Autotuner for the batched solver: times the batch for workgroup sizes,
+ * Autotuner for the batched solver: times the default form and the batch for workgroup sizes,
  * degree-split thresholds, workgroup counts and team thresholds (no teams,
  * 2^20 or 2^22 edges; automatic team size or teams of two), makes the fastest
  * the process-wide default and returns it. dist_outs are overwritten with the

@@ -740,6 +740,30 @@ extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *so
     crit_modes(criterion, &in, &out);
     if (in > IN_STATIC_M || out > OUT_STATIC_M)
         return sssp_set_error(SSSP_ERR_UNSUPPORTED, "the batched solver evaluates DIJK, IN-STATIC and OUT-STATIC");
+    if ((!cfg.block || cfg.block == 512) && !cfg.split && !cfg.blocks && !cfg.team_edges && !cfg.team_size) {
+        // the default form: resident teams (resident.hip), a graph too large for one, or a query
+        // alone, on the whole device; what neither takes is left to the launch below
+        for (uint32_t i = 0; i < nq; ++i) {
+            if (!graphs[i] || !dist_outs[i]) return sssp_set_error(SSSP_ERR_INVALID, "query %u: NULL graph or output", i);
+            if (sources[i] >= graphs[i]->n) return sssp_set_error(SSSP_ERR_INVALID, "query %u: source %u >= n", i, sources[i]);
+        }
+        HIP_OK(hipSetDevice(graphs[0]->device));
+        std::vector<uint32_t> ids, rest;
+        for (uint32_t i = 0; i < nq; ++i) (nq > 1 && resident_batch_takes(graphs[i]) ? ids : rest).push_back(i);
+        bool ran = true;
+        if (!ids.empty()) {
+            const int rc = resident_batch(graphs, sources, ids.data(), (uint32_t)ids.size(), in, out == OUT_STATIC_M,
+                                          dist_outs, phases_out, graphs[0]->stream, &ran);
+            if (rc) return rc;
+        }
+        for (size_t j = 0; ran && j < rest.size(); ++j) {
+            const uint32_t i = rest[j];
+            const int rc = resident_try(graphs[i], graphs[0]->stream, sources[i], in, out == OUT_STATIC_M, 0, dist_outs[i],
+                                        phases_out ? phases_out + i : nullptr, &ran);
+            if (rc) return rc;
+        }
+        if (ran) return SSSP_OK;
+    }
     std::vector<BatchQuery> hq(nq);
     std::vector<uint64_t> st_off(nq), fl_off(nq), fm_off(nq);
     uint64_t st_total = 0, fl_total = 0, fm_total = 0;

@@ -3163,8 +3163,8 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
 // A resident solve where the graph and the launch options allow one, with the graph's scratch
 // (kept between solves). *ran = false: not run, or not finished; the phase kernels then do it
 // (they also do timed solves: per-kernel timing is about them).
-static int resident_try(sssp_graph *g, uint32_t source, int in, bool out_static, uint64_t delta, uint64_t *dist_out,
-                        uint32_t *phases_out, bool *ran) {
+int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
+                 uint64_t *dist_out, uint32_t *phases_out, bool *ran) {
     *ran = false;
     const ResShape r = resident_shape(g);
     if (!r.fits || g->prof) return SSSP_OK;
@@ -3176,7 +3176,7 @@ static int resident_try(sssp_graph *g, uint32_t source, int in, bool out_static,
         g->res_bytes = r.bytes;
     }
     uint32_t phases = 0;
-    const int rc = resident_solve(g, r, source, in, out_static, delta, dist_out, g->res, &phases, ran);
+    const int rc = resident_solve(g, r, s, source, in, out_static, delta, dist_out, g->res, &phases, ran);
     if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
     return rc;
 }
@@ -3193,7 +3193,7 @@ extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, ui
             // the whole solve in one workgroup (the batched kernel)
             if (g->cfg.single) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
             bool ran = false;
-            const int rc = resident_try(g, source, in, out == OUT_STATIC_M, 0, dist_out, phases_out, &ran);
+            const int rc = resident_try(g, g->stream, source, in, out == OUT_STATIC_M, 0, dist_out, phases_out, &ran);
             if (rc || ran) return rc;
         }
     }
@@ -3215,7 +3215,7 @@ extern "C" int sssp_delta_step(sssp_graph *g, uint32_t source, uint64_t delta, u
     if (g && dist_out && source < g->n && g->cfg.single != kPhaseKernels) {
         HIP_OK(hipSetDevice(g->device));
         bool ran = false;
-        const int rc = resident_try(g, source, IN_NONE, false, delta, dist_out, phases_out, &ran);
+        const int rc = resident_try(g, g->stream, source, IN_NONE, false, delta, dist_out, phases_out, &ran);
         if (rc || ran) return rc;
     }
     sssp_stats st;
@@ -3452,7 +3452,7 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
     if (r.fits && r.bytes <= kNoAllocBytes) {
         bool ran = false;
         uint32_t phases = 0;
-        rc = resident_solve(g, r, source, in, out == OUT_STATIC_M, 0, dist_out, base, &phases, &ran);
+        rc = resident_solve(g, r, g->stream, source, in, out == OUT_STATIC_M, 0, dist_out, base, &phases, &ran);
         if (rc) return rc;
         if (ran) {
             if (phases_out) *phases_out = phases;

@@ -1,5 +1,6 @@
 // Resident solver: the whole solve of one query in one cooperative launch, for
-// sssp_solve and sssp_solve_noalloc with static criteria, and for sssp_delta_step.
+// sssp_solve and sssp_solve_noalloc with static criteria, and for sssp_delta_step;
+// and batches of queries, each by a team of workgroups (at the end of this file).
 //
 // W workgroups (a power of two) stay on the device for the whole solve. The
 // vertices are cut into groups of K = 8 (16) consecutive ones; every group has an
@@ -49,6 +50,9 @@
 // and stores; everything a workgroup wrote has completed when it publishes.
 #include <string.h>
 
+#include <algorithm>
+#include <vector>
+
 #include "common.h"
 #include "graph.h"
 
@@ -68,8 +72,7 @@ constexpr uint32_t kResSpin = 1u << 21;
 constexpr unsigned long long kVal = (1ull << 60) - 1, kTag = ~kVal;
 
 struct ResCtl {
-    unsigned long long a[2][kResMaxW * kSlotStride];  // by barrier parity: tagged minD, tagged threshold
-    unsigned long long b[2][kResMaxW * kSlotStride];  // by phase parity: tagged count of shared records
+    unsigned long long bar[4 * kResMaxW * kSlotStride];  // see ResArgs::bar
     unsigned int rank[16 * 32];                       // arrivals per XCD
     unsigned int team;                                // 1 + the XCD whose workgroups form the team
     unsigned int error;
@@ -85,13 +88,15 @@ struct ResArgs {
     unsigned long long *box;   // per vertex, by phase parity: the lowest candidate relaxes delivered
     uint8_t *mark;       // by phase parity, W rows of mstride bytes: the phase tag each slot was last marked for
     unsigned long long *rec;    // W rows of kShareCap records (first edge and count, distance)
-    ResCtl *ctl;
+    // barrier words, by barrier parity, a slot per workgroup: tagged minD and tagged threshold;
+    // then likewise the tagged counts of shared records
+    unsigned long long *bar;
+    unsigned int *error;
     uint32_t n, src, wmax;
     uint32_t W, lgW;     // workgroups
     uint32_t lgWv;       // wavefronts per workgroup
     uint32_t wslots;     // slots per wavefront, a multiple of 64
     uint32_t mstride;    // slots per workgroup
-    uint32_t one_xcd;    // the W workgroups are taken from one XCD
     uint32_t quota;      // segments a wavefront keeps for itself in a phase
     uint32_t share;      // rows beyond the quota become records relaxed by all workgroups
     uint32_t lgK;        // vertices per group
@@ -152,7 +157,7 @@ __device__ __forceinline__ uint64_t mark_of(const ResArgs &a, uint32_t g) {
     return (uint64_t)(g & (a.W - 1)) * a.mstride + (t & ((1u << a.lgWv) - 1u)) * a.wslots + (t >> a.lgWv);
 }
 
-__global__ void k_res_init(ResArgs a) {
+__global__ void k_res_init(ResArgs a, ResCtl *ctl) {
     const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t v = t0; v < a.n; v += stride) {
         const unsigned long long x = v == a.src ? 0ull : INF64;
@@ -164,7 +169,7 @@ __global__ void k_res_init(ResArgs a) {
     uint32_t *mw = reinterpret_cast<uint32_t *>(a.mark);
     for (uint64_t i = t0; i < (uint64_t)a.W * a.mstride / 2; i += stride)
         mw[i] = i == src_mark / 4 ? phase_tag(0) << (8 * (src_mark & 3)) : 0u;
-    uint32_t *c = reinterpret_cast<uint32_t *>(a.ctl);
+    uint32_t *c = reinterpret_cast<uint32_t *>(ctl);
     for (uint64_t i = t0; i < sizeof(ResCtl) / 4; i += stride) c[i] = 0;
 }
 
@@ -183,19 +188,22 @@ __device__ __forceinline__ void wave_fence() {  // LDS values pass between lanes
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int BS, int K, int IN, bool OUT, bool DELTA = false>
-__global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
+// One solve by a team of a.W workgroups, this one the wg-th. Boxes, marks and distances are set up
+// and visible to the team; nb counts the team's barriers. Returns the number of phases (rounds), or
+// INF32 when a workgroup did not arrive in time (a.error is set).
+template <int BS, int K, int IN, bool OUT, bool DELTA>
+__device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, uint32_t &nb) {
     extern __shared__ unsigned long long dyn[];
     constexpr uint32_t kWv = BS / 64, kR = 64 / K;
     __shared__ unsigned long long s_red[2 * kWv];
     __shared__ unsigned long long s_all[2 * (kResMaxW / 64)];
     __shared__ uint32_t s_wn[kWv], s_wl[kWv];  // per list: segments reserved, first reservation that failed
-    __shared__ uint32_t s_pend, s_nsh, s_shlim, s_flags, s_wg;
+    __shared__ uint32_t s_pend, s_nsh, s_shlim, s_flags;
     __shared__ uint32_t s_sh[kResMaxW + 1];    // exclusive prefix of the workgroups' shared records
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t li = lane & (K - 1);        // the lane's vertex in its row's group
     const uint32_t W = a.W, NS = a.mstride, n = a.n, nj = a.wslots / 64, ws0 = wave * a.wslots;
-    ResCtl *ctl = a.ctl;
+    const uint32_t bstride = W * kSlotStride;
     // segments: each wavefront cuts and relaxes its own; with `share`, all go to one list whose
     // segments the workgroup's rows take in turn
     const uint32_t lw = a.share ? 0u : wave, rows = a.share ? BS / kSegEdges : 64 / kSegEdges;
@@ -206,25 +214,6 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
     uint16_t *rset = reinterpret_cast<uint16_t *>(gk);  // Delta-stepping: vertices the bucket removed
     uint16_t *lst = pend + NS + ws0;  // the wavefront's active slots
 
-    // the workgroup's rank in the team
-    uint32_t wg = blockIdx.x;
-    if (a.one_xcd) {  // the others leave: an L2 of its own serves the whole team
-        // the first XCD on which W workgroups have arrived is the team's; the launch holds 8 W
-        // workgroups, so one of the eight gets there whatever their placement
-        if (tid == 0) {
-            const uint32_t x = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xfu;  // HW_REG_XCC_ID
-            const uint32_t r = atomicAdd(&ctl->rank[x * 32], 1u);
-            if (r == W - 1) atomicCAS(&ctl->team, 0u, x + 1);
-            uint32_t t = 0, spins = 0;
-            while (!(t = __hip_atomic_load(&ctl->team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < kResSpin)
-                __builtin_amdgcn_s_sleep(1);
-            if (!t) atomicOr(&ctl->error, 1u);
-            s_wg = t == x + 1 && r < W ? r : INF32;
-        }
-        __syncthreads();
-        wg = s_wg;
-        if (wg == INF32) return;
-    }
     for (uint32_t s = tid; s < NS; s += BS) {
         gk[s] = gd[s] = go[s] = INF64;
         sset[s] = pend[s] = 0;
@@ -284,7 +273,9 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
     unsigned long long hi = a.delta;
     for (uint32_t k = 0; minD != INF64; ++k) {
         const uint32_t par = k & 1;
-        const unsigned long long tag = bar_tag(k);
+        const unsigned long long tag = bar_tag(nb);
+        unsigned long long *bar_a = a.bar + (nb & 1) * bstride, *bar_b = bar_a + 2 * bstride;
+        ++nb;
         // 1. the wavefront's active groups
         const uint8_t pt = (uint8_t)phase_tag(k);
         uint32_t na = 0;  // wavefront-uniform
@@ -402,7 +393,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
             if (waiting && lane == 0) s_pend = 1;
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's records are written
             __syncthreads();
-            if (tid == 0) st_agent(&ctl->b[par][wg * kSlotStride], tag | umin32(s_nsh, s_shlim));
+            if (tid == 0) st_agent(&bar_b[wg * kSlotStride], tag | umin32(s_nsh, s_shlim));
         }
         wave_fence();
         uint32_t nseg = umin32(s_wn[lw], s_wl[lw]);
@@ -526,7 +517,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
             if (tid < W) {
                 uint32_t spins = 0;
                 unsigned long long v;
-                while (((v = ld64(&ctl->b[par][tid * kSlotStride])) & kTag) != tag && ++spins < kResSpin) {}
+                while (((v = ld64(&bar_b[tid * kSlotStride])) & kTag) != tag && ++spins < kResSpin) {}
                 s_sh[tid] = (uint32_t)v;
                 if ((v & kTag) != tag) atomicOr(&s_flags, 1u);
                 else if (v & kVal) atomicOr(&s_flags, 2u);
@@ -602,11 +593,11 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
             if (kWv >= 8) x = umin64(x, dpp64<kDppHalfMirror>(x));
             if (kWv >= 16) x = umin64(x, dpp64<kDppMirror>(x));
             if (lane == 0 || (OUT && lane == kWv))
-                st_agent(&ctl->a[par][wg * kSlotStride + (lane ? 1 : 0)], tag | umin64(x, kVal));
+                st_agent(&bar_a[wg * kSlotStride + (lane ? 1 : 0)], tag | umin64(x, kVal));
         }
         unsigned long long pm = kVal, pt2 = kVal;
         if (tid < W) {
-            const unsigned long long *w = &ctl->a[par][tid * kSlotStride];
+            const unsigned long long *w = &bar_a[tid * kSlotStride];
             uint32_t spins = 0;
             for (;;) {
                 pm = ld64(w);
@@ -630,8 +621,8 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
         }
         __syncthreads();
         if (s_flags & 1u) {  // block-uniform
-            if (tid == 0) atomicOr(&ctl->error, 1u);
-            return;
+            if (tid == 0) atomicOr(a.error, 1u);
+            return INF32;
         }
         pm = s_all[0];
         pt2 = s_all[kResMaxW / 64];
@@ -652,14 +643,42 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a) {
         }
         // a phase settles at least the queue minimum; a bucket's light rounds each remove or lower
         if (DELTA ? k / 4 > n + 16 : k > n) {
-            if (tid == 0) atomicOr(&ctl->error, 2u);
-            return;
+            if (tid == 0) atomicOr(a.error, 2u);
+            return INF32;
         }
-        if (minD == INF64 && wg == 0 && tid == 0) st_agent(&ctl->phases, k + 1);
+        if (minD == INF64) return k + 1;
     }
+    return 0;  // not reached: the first phase settles the source
 }
 
-typedef void (*rfn)(ResArgs);
+template <int BS, int K, int IN, bool OUT, bool DELTA = false>
+__global__ __launch_bounds__(BS) void k_resident(ResArgs a, ResCtl *ctl, uint32_t one_xcd) {
+    __shared__ uint32_t s_wg;
+    // the workgroup's rank in the team
+    uint32_t wg = blockIdx.x;
+    if (one_xcd) {  // the others leave: an L2 of its own serves the whole team
+        // the first XCD on which W workgroups have arrived is the team's; the launch holds 8 W
+        // workgroups, so one of the eight gets there whatever their placement
+        if (threadIdx.x == 0) {
+            const uint32_t x = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xfu;  // HW_REG_XCC_ID
+            const uint32_t r = atomicAdd(&ctl->rank[x * 32], 1u);
+            if (r == a.W - 1) atomicCAS(&ctl->team, 0u, x + 1);
+            uint32_t t = 0, spins = 0;
+            while (!(t = __hip_atomic_load(&ctl->team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < kResSpin)
+                __builtin_amdgcn_s_sleep(1);
+            if (!t) atomicOr(a.error, 1u);
+            s_wg = t == x + 1 && r < a.W ? r : INF32;
+        }
+        __syncthreads();
+        wg = s_wg;
+        if (wg == INF32) return;
+    }
+    uint32_t nb = 0;
+    const uint32_t phases = resident_run<BS, K, IN, OUT, DELTA>(a, wg, nb);
+    if (wg == 0 && threadIdx.x == 0 && phases != INF32) st_agent(&ctl->phases, phases);
+}
+
+typedef void (*rfn)(ResArgs, ResCtl *, uint32_t);
 
 template <int BS, int K>
 static rfn pick_res_bs(int in, bool out) {
@@ -711,16 +730,17 @@ ResShape resident_shape(const sssp_graph *g) {
 // Runs a resident solve (delta > 0: Delta-stepping) with `scratch` (r.bytes, 256-byte aligned).
 // *ran = false: the device cannot hold the workgroups at once, or one waited too long for another
 // (the device is shared with other work); the distances are unfinished.
-int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int in, bool out_static, uint64_t delta,
+int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran) {
-    hipStream_t s = g->stream;
     ResArgs a;
     a.rp = g->rp;
     a.edges = g->edges;
     a.vmin = g->vmin;
     a.emin = g->emin;
     a.dist = (unsigned long long *)dist_out;
-    a.ctl = (ResCtl *)scratch;
+    ResCtl *ctl = (ResCtl *)scratch;
+    a.bar = ctl->bar;
+    a.error = &ctl->error;
     a.rec = (unsigned long long *)((uint8_t *)scratch + ((sizeof(ResCtl) + 255) & ~255ull));
     a.box = a.rec + 2ull * kShareCap * r.W;
     a.mark = (uint8_t *)(a.box + 2ull * g->n);
@@ -735,14 +755,14 @@ int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int 
     a.lgWv = (uint32_t)__builtin_ctz((uint32_t)r.bs / 64);
     a.wslots = r.slots >> a.lgWv;
     a.mstride = r.slots;
-    a.one_xcd = r.one_xcd;
     a.delta = delta;
     const uint64_t ib = ((uint64_t)g->n + 255) / 256;
-    hipLaunchKernelGGL(k_res_init, dim3((uint32_t)(ib > 2048 ? 2048 : ib < 64 ? 64 : ib)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_res_init, dim3((uint32_t)(ib > 2048 ? 2048 : ib < 64 ? 64 : ib)), dim3(256), 0, s, a, ctl);
     rfn k = pick_res(r.bs, r.lgK, in, out_static, delta != 0);
     const size_t lds = res_lds(r.slots, r.bs);
     if (lds > 65536) HIP_OK(hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    void *args[] = {&a};
+    uint32_t one_xcd = r.one_xcd;
+    void *args[] = {&a, &ctl, &one_xcd};
     const hipError_t e = hipLaunchCooperativeKernel((const void *)k, dim3(r.one_xcd ? 8 * r.W : r.W), dim3(r.bs), args,
                                                     (uint32_t)lds, s);
     if (e == hipErrorCooperativeLaunchTooLarge) {
@@ -753,9 +773,278 @@ int resident_solve(const sssp_graph *g, const ResShape &r, uint32_t source, int 
     HIP_OK(e);
     unsigned int h[2];
     static_assert(offsetof(ResCtl, phases) == offsetof(ResCtl, error) + 4, "one copy");
-    HIP_OK(hipMemcpyAsync(h, &a.ctl->error, sizeof h, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipMemcpyAsync(h, &ctl->error, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     *phases = h[1];
     *ran = h[0] == 0;
+    return SSSP_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Batches: gangs of kGang workgroups of one XCD, each first one team of kGang for the largest
+// queries; when those are taken it splits into teams of half the size for the next class, down to
+// single workgroups. The smallest class whose lists fit LDS is the cheapest per query (a random
+// graph of 16384 vertices, degree 16: 1.9 ms on one workgroup, 1.2 on two, 0.8 on four), so queries
+// take it while there are more of them than workgroups, and larger teams when there is room. The
+// longest query bounds a batch (a grid of 2^17 vertices takes 13.8 ms on eight workgroups, 12.5 on
+// sixteen; giving such grids sixteen makes a batch of 192 queries 7 % faster and one of 512 14 %
+// slower). 192 queries over 24 graphs up to 2^17 vertices: 18.2 ms, against 45.1 with one workgroup
+// of 512 threads per query (batch.hip); 512 over 64 up to 2^18: 43.8 against 79.2.
+constexpr uint32_t kGangLog = 5, kGang = 1u << kGangLog;
+constexpr int kBatchBs = 512;                    // threads: two workgroups per CU
+constexpr uint32_t kBatchNj = 4;                 // slots per thread of a batch workgroup at most
+constexpr uint32_t kWgVertices = 8u * kBatchBs * kBatchNj;  // vertices per workgroup at most
+constexpr uint32_t kTeamBar = 4 * kGang * kSlotStride + kSlotStride;  // u64 of a team: barrier words, query word
+
+struct ResQuery {
+    const uint32_t *rp;
+    const uint2 *edges;
+    const uint2 *vmin;
+    const uint32_t *emin;
+    unsigned long long *dist;
+    uint32_t n, src, wmax, share;
+};
+
+struct ResBatch {
+    const ResQuery *q;
+    const uint32_t *order;            // queries by class, the costliest first
+    uint32_t first[kGangLog + 1], count[kGangLog + 1];
+    uint32_t *heads;                  // queries taken, by class
+    uint32_t *phases;
+    unsigned int *error;
+    unsigned long long *bar;          // 2 * kGang teams per gang
+    unsigned long long *rec, *box;    // per workgroup: kShareCap records, 2 * wgv boxes
+    uint8_t *mark;                    // per workgroup: 2 * slots
+    uint32_t wgv, slots;
+};
+
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p) {
+    const unsigned long long x = (unsigned long long)p;
+    return (T *)(((unsigned long long)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x));
+}
+
+template <int IN, bool OUT>
+__global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
+    constexpr uint32_t BS = kBatchBs, K = 8, lgWv = 3;
+    static_assert(BS / 64 == 1u << lgWv, "wavefronts");
+    __shared__ uint32_t s_q, s_bad;
+    const uint32_t tid = threadIdx.x;
+    // workgroups are dealt out to the XCDs in turn: a gang's lie 8 apart, on one XCD
+    const uint32_t gang = blockIdx.x / (8 * kGang) * 8 + blockIdx.x % 8, member = blockIdx.x / 8 % kGang;
+    for (int cls = kGangLog; cls >= 0; --cls) {
+        const uint32_t count = b.count[cls];
+        if (count == 0) continue;  // grid-uniform
+        const uint32_t W = 1u << cls, wg = member & (W - 1), m0 = member - wg;
+        const uint64_t g0 = (uint64_t)gang * kGang + m0;  // the team's first workgroup
+        unsigned long long *bar = b.bar + ((uint64_t)gang * 2 * kGang + (kGang >> cls) + (member >> cls)) * kTeamBar;
+        unsigned long long *qword = bar + 4 * kGang * kSlotStride;
+        uint32_t nb = 0;
+        for (uint32_t turn = 1;; ++turn) {
+            // the team's first workgroup takes the next query and tells the others
+            if (tid == 0) {
+                uint32_t q = INF32;
+                if (wg == 0) {
+                    q = umin32(atomicAdd(&b.heads[cls], 1u), count);
+                    if (W > 1) st_agent(qword, ((unsigned long long)turn << 32) | q);
+                } else {
+                    unsigned long long x = 0;
+                    for (uint32_t spins = 0; spins < kResSpin; ++spins) {
+                        x = ld64(qword);
+                        if ((uint32_t)(x >> 32) == turn) { q = (uint32_t)x; break; }
+                        __builtin_amdgcn_s_sleep(1);
+                    }
+                }
+                s_q = q;
+                s_bad = 0;
+            }
+            __syncthreads();
+            const uint32_t qi = uniform(s_q);
+            if (qi == INF32) {
+                if (tid == 0) atomicOr(b.error, 1u);
+                return;
+            }
+            if (qi >= count) break;
+            const uint32_t id = uniform(b.order[b.first[cls] + qi]);
+            const ResQuery &rq = b.q[id];
+            ResArgs a;
+            a.rp = uniform(rq.rp);
+            a.edges = uniform(rq.edges);
+            a.vmin = uniform(rq.vmin);
+            a.emin = uniform(rq.emin);
+            a.dist = uniform(rq.dist);
+            a.n = uniform(rq.n);
+            a.src = uniform(rq.src);
+            a.wmax = uniform(rq.wmax);
+            a.share = uniform(rq.share);
+            a.box = b.box + g0 * 2 * b.wgv;
+            a.rec = b.rec + g0 * 2 * kShareCap;
+            a.mark = b.mark + g0 * 2 * b.slots;
+            a.bar = bar;
+            a.error = b.error;
+            a.W = W;
+            a.lgW = (uint32_t)cls;
+            a.lgWv = lgWv;
+            a.lgK = 3;
+            a.quota = kQuota;
+            a.delta = 0;
+            const uint32_t groups = (a.n - 1) / K + 1;
+            a.wslots = 64 * ((groups - 1) / (W * BS) + 1);
+            a.mstride = a.wslots << lgWv;
+            // this workgroup's groups: distances, boxes and marks
+            for (uint32_t i = tid; i < a.mstride * K; i += BS) {
+                const uint32_t v = (((i / K) << a.lgW) | wg) * K + i % K;
+                if (v >= a.n) continue;
+                const unsigned long long x = v == a.src ? 0ull : INF64;
+                a.dist[v] = x;
+                st_agent(&a.box[2ull * v], x);
+                st_agent(&a.box[2ull * v + 1], x);
+            }
+            const uint64_t ms = mark_of(a, a.src / K);
+            uint32_t *mw = reinterpret_cast<uint32_t *>(a.mark);
+            for (uint32_t p = 0; p < 2; ++p)
+                for (uint32_t i = tid; i < a.mstride / 4; i += BS) {
+                    const uint64_t w = ((uint64_t)p * W + wg) * a.mstride / 4 + i;
+                    st_agent(&mw[w], w == ms / 4 ? phase_tag(0) << (8 * (ms & 3)) : 0u);
+                }
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (W > 1) {  // the team's set-up is done
+                unsigned long long *words = bar + (nb & 1) * W * kSlotStride;
+                const unsigned long long tag = bar_tag(nb);
+                ++nb;
+                if (tid == 0) st_agent(&words[wg * kSlotStride], tag | kVal);
+                if (tid < W) {
+                    uint32_t spins = 0;
+                    while ((ld64(&words[tid * kSlotStride]) & kTag) != tag && ++spins < kResSpin) {}
+                    if (spins >= kResSpin) s_bad = 1;
+                }
+                __syncthreads();
+                if (s_bad) {  // block-uniform
+                    if (tid == 0) atomicOr(b.error, 1u);
+                    return;
+                }
+            }
+            const uint32_t phases = resident_run<BS, K, IN, OUT, false>(a, wg, nb);
+            if (phases == INF32) return;
+            if (wg == 0 && tid == 0) b.phases[id] = phases;
+            __syncthreads();  // LDS is set up anew for the next query
+        }
+        __syncthreads();
+    }
+}
+
+typedef void (*bafn)(ResBatch);
+
+static bafn pick_res_batch(int in, bool out) {
+    if (in == IN_DIJK) return out ? k_resident_batch<IN_DIJK, true> : k_resident_batch<IN_DIJK, false>;
+    if (in == IN_STATIC_M) return out ? k_resident_batch<IN_STATIC_M, true> : k_resident_batch<IN_STATIC_M, false>;
+    return k_resident_batch<IN_NONE, true>;
+}
+
+static uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
+
+bool resident_batch_takes(const sssp_graph *g) { return g->n <= (uint64_t)kGang * kWgVertices; }
+
+// Solves the queries ids[0 .. nq) (each of a graph that resident_batch_takes) in one cooperative
+// launch on stream s. *ran = false: as in resident_solve.
+int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
+                   bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, hipStream_t s, bool *ran) {
+    *ran = false;
+    const bafn k = pick_res_batch(in, out_static);
+    int dev = 0, cus = 0, per_cu = 0;
+    HIP_OK(hipGetDevice(&dev));
+    HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    // classes: the least team whose lists hold the graph, doubled while all queries fit at once
+    std::vector<uint32_t> cls(nq);
+    uint64_t wgs = 0;
+    uint32_t slots = 0, wgv = 0;
+    for (uint32_t i = 0; i < nq; ++i) {
+        while (((uint64_t)kWgVertices << cls[i]) < graphs[ids[i]]->n) ++cls[i];
+        wgs += 1u << cls[i];
+    }
+    auto lds_slots = [&](uint32_t n, uint32_t c) { return kBatchBs * ((((n - 1) / 8 + 1) - 1) / (kBatchBs << c) + 1); };
+    for (uint32_t i = 0; i < nq; ++i) slots = std::max(slots, lds_slots(graphs[ids[i]]->n, cls[i]));
+    HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k, kBatchBs, res_lds(slots, kBatchBs)));
+    const uint64_t resident = (uint64_t)per_cu * cus / (8 * kGang) * (8 * kGang);
+    if (resident == 0) return SSSP_OK;
+    for (bool grown = true; grown && 2 * wgs <= resident;) {
+        grown = false;
+        for (uint32_t i = 0; i < nq; ++i)
+            // at least a slot per thread of work
+            if (cls[i] < kGangLog && (4096u << cls[i]) <= graphs[ids[i]]->n) {
+                wgs += 1u << cls[i]++;
+                grown = true;
+            }
+    }
+    slots = 0;
+    for (uint32_t i = 0; i < nq; ++i) {
+        slots = std::max(slots, lds_slots(graphs[ids[i]]->n, cls[i]));
+        wgv = std::max(wgv, 8 * ((((graphs[ids[i]]->n - 1) / 8 + 1) - 1) / (1u << cls[i]) + 1));
+    }
+    const uint64_t blocks = std::min(resident, (wgs + 8 * kGang - 1) / (8 * kGang) * (8 * kGang));
+    const uint64_t gangs = blocks / kGang;
+    // costliest first: a graph of low degree takes the most phases for its size (a grid of 2^17
+    // vertices 2946, a random graph of degree 16 207)
+    auto cost = [&](uint32_t i) {
+        const sssp_graph *g = graphs[ids[i]];
+        return g->m < 6ull * g->n ? 16ull * g->n : (uint64_t)g->n + g->m / 8;
+    };
+    std::vector<uint32_t> order(nq);
+    for (uint32_t i = 0; i < nq; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) {
+        return cls[x] != cls[y] ? cls[x] > cls[y] : cost(x) > cost(y);
+    });
+    ResBatch b;
+    memset(&b, 0, sizeof b);
+    for (uint32_t i = 0; i < nq; ++i) ++b.count[cls[i]];
+    for (int c = kGangLog - 1; c >= 0; --c) b.first[c] = b.first[c + 1] + b.count[c + 1];
+    // one buffer: [queries, order | heads, error | phases | barrier words | records | boxes | marks]
+    const uint64_t o_order = up256(nq * sizeof(ResQuery)), o_heads = up256(o_order + 4ull * nq),
+                   o_phases = up256(o_heads + 4 * (kGangLog + 2)), o_bar = up256(o_phases + 4ull * nq),
+                   o_rec = up256(o_bar + gangs * 2 * kGang * kTeamBar * 8), o_box = up256(o_rec + blocks * kShareCap * 16),
+                   o_mark = up256(o_box + blocks * wgv * 16), total = o_mark + blocks * 2 * slots;
+    CallBuffer buf;
+    HIP_OK(hipMalloc(&buf.p, total));
+    uint8_t *base = (uint8_t *)buf.p;
+    std::vector<uint8_t> up(o_heads);
+    ResQuery *hq = (ResQuery *)up.data();
+    for (uint32_t i = 0; i < nq; ++i) {
+        const sssp_graph *g = graphs[ids[i]];
+        hq[i] = ResQuery{g->rp, g->edges, g->vmin, g->emin, (unsigned long long *)dist_outs[ids[i]],
+                         g->n, sources[ids[i]], g->wmax, g->max_deg > kShareDeg};
+    }
+    memcpy(up.data() + o_order, order.data(), 4ull * nq);
+    HIP_OK(hipMemcpyAsync(base, up.data(), o_heads, hipMemcpyHostToDevice, s));
+    HIP_OK(hipMemsetAsync(base + o_heads, 0, o_rec - o_heads, s));
+    b.q = (const ResQuery *)base;
+    b.order = (const uint32_t *)(base + o_order);
+    b.heads = (uint32_t *)(base + o_heads);
+    b.error = b.heads + kGangLog + 1;
+    b.phases = (uint32_t *)(base + o_phases);
+    b.bar = (unsigned long long *)(base + o_bar);
+    b.rec = (unsigned long long *)(base + o_rec);
+    b.box = (unsigned long long *)(base + o_box);
+    b.mark = base + o_mark;
+    b.wgv = wgv;
+    b.slots = slots;
+    const size_t lds = res_lds(slots, kBatchBs);
+    if (lds > 65536) HIP_OK(hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    void *args[] = {&b};
+    const hipError_t e = hipLaunchCooperativeKernel((const void *)k, dim3((uint32_t)blocks), dim3(kBatchBs), args,
+                                                    (uint32_t)lds, s);
+    if (e == hipErrorCooperativeLaunchTooLarge) {
+        (void)hipGetLastError();
+        return SSSP_OK;
+    }
+    HIP_OK(e);
+    std::vector<uint32_t> down((o_bar - o_heads) / 4);
+    HIP_OK(hipMemcpyAsync(down.data(), base + o_heads, o_bar - o_heads, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    if (down[kGangLog + 1]) return SSSP_OK;
+    if (phases_out)
+        for (uint32_t i = 0; i < nq; ++i) phases_out[ids[i]] = down[(o_phases - o_heads) / 4 + i];
+    *ran = true;
     return SSSP_OK;
 }

@@ -121,8 +121,12 @@ extern "C" int sssp_autotune_batch(sssp_graph *const *graphs, const uint32_t *so
                                    float *best_ms) {
     if (nq == 0 || !graphs || !graphs[0]) return sssp_set_error(SSSP_ERR_INVALID, "empty batch");
     const int cus = device_cus();
-    sssp_batch_cfg win = {0, 0, 0, 0, 0};
+    sssp_batch_cfg win = {512, 0, 0, 0, 0};  // the default form
     float win_ms = 1e30f;
+    int rc0 = time_call(graphs[0]->stream, 2, [&] {
+        return sssp_solve_batch_ex(graphs, sources, nq, criterion, dist_outs, nullptr, &win);
+    }, &win_ms);
+    if (rc0) return rc0;
     for (uint32_t bs : {256u, 512u, 1024u})
         for (uint32_t split : {16u, 64u, 256u})
             for (uint32_t per_cu : {1u, 2u, 4u})

@@ -1,5 +1,5 @@
-"""Resident solves (sssp_solve and sssp_solve_noalloc with static criteria, sssp_delta_step) against
-the CPU oracle: distances bit-exact, phase and round counts equal, where the resident kernel's cuts can go wrong: vertex
+"""Resident solves (sssp_solve and sssp_solve_noalloc with static criteria, sssp_delta_step, default
+batches) against the CPU oracle: distances bit-exact, phase and round counts equal, where the resident kernel's cuts can go wrong: vertex
 counts at the edges of its groups, every launch shape its rule picks, rows long enough to be shared
 between workgroups, phases that settle more vertices than its lists hold, and weights so large that
 values of one phase differ by more than 32 bits."""
@@ -85,6 +85,45 @@ def test_resident_delta_matches_oracle(B, name):
         assert np.array_equal(r.dist_u64(), ref.dist), (name, delta)
         assert r.phases == ref.rounds, (name, delta, r.phases, ref.rounds)
     dg.close()
+
+
+@pytest.mark.parametrize("crit", [O.STATIC_OR, O.IN_STATIC, O.OUT_STATIC, O.DIJK])
+def test_resident_batch_matches_oracle(B, crit):
+    """One batch of every graph above and of random graphs at the edges of the team classes, with more
+    queries than workgroups (the small ones repeated), and the same batch with a launch shape given."""
+    graphs = [f() for name, f in GRAPHS.items() if name not in ("star",)]
+    graphs += [G.er(n, 3, 1, 300, 350 + n) for n in (16384, 16385, 32768, 32769)]
+    if crit == O.STATIC_OR:
+        graphs.append(GRAPHS["star"]())
+    handles, sources, refs = [], [], []
+    for g in graphs:
+        if crit == O.DIJK and g.n > 10000:
+            continue
+        dg = B.DeviceGraph.from_graph(g)
+        for s in [0] if g.m == 0 else [int(x) for x in G.sources(g, 2, 351)]:
+            ref = O.phased(g, s, crit)
+            for _ in range(60 if g.n <= 65 else 1):
+                handles.append(dg)
+                sources.append(s)
+                refs.append(ref)
+    assert len(handles) > 512
+    for cfg in (None, dict(block=256)):
+        print("batch", crit, len(handles), cfg, flush=True)
+        dists, phases = B.solve_batch(handles, sources, crit, cfg=cfg)
+        for dg, d, p, ref in zip(handles, dists, phases, refs):
+            assert np.array_equal(B.to_u64(d), ref.dist) and p == ref.phases, (dg.n, p, ref.phases, cfg)
+
+
+def test_resident_batch_team_sizes(B):
+    """Few queries get larger teams, up to a whole gang, and a graph beyond a gang's reach the device."""
+    graphs = [G.er(3000, 5, 1, 500, 360), G.er(200003, 4, 1, 1 << 20, 361), G.grid(61, 47, 1, 1000, 362),
+              G.er(530000, 3, 1, 1 << 20, 363)]
+    dgs = [B.DeviceGraph.from_graph(g) for g in graphs]
+    refs = [O.phased(g, 1, O.STATIC_OR) for g in graphs]
+    for pick in ([0, 2], [1], [0, 1, 2], [3, 0], [0, 1, 2, 3, 0, 2]):
+        dists, phases = B.solve_batch([dgs[i] for i in pick], [1] * len(pick), B.STATIC_OR)
+        for i, d, p in zip(pick, dists, phases):
+            assert np.array_equal(B.to_u64(d), refs[i].dist) and p == refs[i].phases, (pick, i)
 
 
 def test_resident_more_than_2_23_vertices(B):
