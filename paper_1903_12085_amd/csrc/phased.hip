@@ -48,6 +48,7 @@ struct KArgs {
     const unsigned long long *ref;  // ORACLE mode: dist(s, .) of this source (device)
     uint32_t mark;       // stored full terms: identify and relax flag state changes (ST_CHG)
     uint32_t fresh_at;   // stored full terms: the phase at which every queued vertex computes them
+    uint32_t win;        // vertices in a window of the term and dirty-set passes (see term_window)
 };
 
 // The selector's three criteria: IN-STATIC|OUT-STATIC, IN-SIMPLE|OUT-SIMPLE, IN-SIMPLE|OUT-STATIC.
@@ -371,8 +372,7 @@ __device__ __forceinline__ uint32_t load_st4(const uint8_t *st, uint32_t q, uint
 // ---------------------------------------------------------------------------
 // term pass (dynamic criteria)
 
-// Consecutive vertices in one window: a queue-array scan block owns such windows
-// (one per grid step), the term and dirty-set passes take one per block.
+// Consecutive vertices in one window of a queue-array scan block (one per grid step).
 constexpr uint32_t kOwnSpan = 16 * kBlock;
 
 // Minimum weight of an out-edge of an unexplored x towards a non-settled vertex
@@ -610,9 +610,21 @@ __device__ __forceinline__ void mark_in_edge(const KArgs &a, uint2 ie, bool sett
     }
 }
 
+// This thread's state bytes of the window [vb, vb + win): four consecutive ones, or one of a short
+// window (bytes past n read as unexplored), and their place in LDS.
+__device__ __forceinline__ uint32_t load_window(const KArgs &a, uint64_t vb) {
+    if (a.win == kBlock) return vb + threadIdx.x < a.g.n ? a.b.st[vb + threadIdx.x] : 0u;
+    const uint64_t q = vb / 4 + threadIdx.x;
+    return 4 * q < a.g.n ? load_st4(a.b.st, (uint32_t)q, a.g.n) : 0u;
+}
+__device__ __forceinline__ void store_window(const KArgs &a, uint32_t *s_st, uint32_t x) {
+    if (a.win == kBlock) reinterpret_cast<uint8_t *>(s_st)[threadIdx.x] = (uint8_t)x;
+    else s_st[threadIdx.x] = x;
+}
+
 template <bool IN_ON, int OUT_M>
 __global__ __launch_bounds__(kBlock) void k_mark(KArgs a, int par) {
-    __shared__ uint4 s_st[kOwnSpan / 16];
+    __shared__ uint32_t s_st[kBlock];
     __shared__ RowList L;
     __shared__ RowList L2[1];  // OUT (full): in-rows to flag
     Ctl *ctl = a.b.ctl;
@@ -622,26 +634,17 @@ __global__ __launch_bounds__(kBlock) void k_mark(KArgs a, int par) {
     const unsigned long long reached = wave_sum64(r0);
     if (reached == settled_cnt) return;
     const uint8_t *sw = reinterpret_cast<const uint8_t *>(s_st);
-    for (uint64_t vb = (uint64_t)blockIdx.x * kOwnSpan; vb < n; vb += (uint64_t)gridDim.x * kOwnSpan) {
-        const uint64_t v0 = vb + 16u * threadIdx.x;
-        uint4 x = make_uint4(0u, 0u, 0u, 0u);
-        if (v0 + 16 <= n) {
-            x = *reinterpret_cast<const uint4 *>(a.b.st + v0);
-        } else if (v0 < n) {
-            uint32_t q[4] = {0u, 0u, 0u, 0u};
-            for (uint32_t j = 0; v0 + j < n; ++j) q[j >> 2] |= (uint32_t)a.b.st[v0 + j] << (8 * (j & 3));
-            x = make_uint4(q[0], q[1], q[2], q[3]);
-        }
-        const bool any = ((x.x | x.y | x.z | x.w) & 0x80808080u) != 0;
+    for (uint64_t vb = (uint64_t)blockIdx.x * a.win; vb < n; vb += (uint64_t)gridDim.x * a.win) {
+        const uint32_t x = load_window(a, vb);
+        const bool any = (x & 0x80808080u) != 0;
         __syncthreads();  // the previous window's LDS reads are done
-        s_st[threadIdx.x] = x;
+        store_window(a, s_st, x);
         if (threadIdx.x == 0) {
             L.cnt = 0;
             if (OUT_M == OUT_FULL_M) L2[0].cnt = 0;
         }
         if (!__syncthreads_or(any)) continue;  // block-uniform
-        for (uint32_t r = 0; r < kOwnSpan / kBlock; ++r) {
-            const uint32_t i = r * kBlock + threadIdx.x;
+        for (uint32_t i = threadIdx.x; i < a.win; i += kBlock) {
             const uint32_t sb = sw[i];
             if (!(sb & ST_CHG)) continue;
             const uint32_t w = (uint32_t)vb + i;
@@ -1522,11 +1525,11 @@ __global__ __launch_bounds__(kBlock) void k_identify_queue(KArgs a, int par) {
 }
 
 // Term pass of the plain solvers (dynamic criteria): block b evaluates the
-// terms of the queued vertices among kOwnSpan consecutive vertices (b + k G) *
-// kOwnSpan + [0, kOwnSpan), k = 0, 1, ...; the host launches enough blocks for
+// terms of the queued vertices among a.win consecutive vertices (b + k G) *
+// a.win + [0, a.win), k = 0, 1, ...; the host launches enough blocks for
 // one window each, independent of the scan grid, so that the dependent loads of
 // the cursor walks are spread over as many threads as the device holds. A
-// window's state bytes are loaded with one 16-byte load per thread, issued with
+// window's state bytes are loaded with one load per thread, issued with
 // the control-slot loads for the first window, and staged in LDS; a window
 // without a queued vertex is skipped, and the queued vertices are taken one per
 // thread in vertex order, so that a wavefront's distance, cursor and cache loads
@@ -1541,7 +1544,7 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
     constexpr bool kStoreIn = IN == IN_FULL_M, kStoreOut = OUT == OUT_WEAK_M || OUT == OUT_FULL_M;
     constexpr bool kStore = kStoreIn || kStoreOut;
     __shared__ unsigned long long sh[8 * kWaves];
-    __shared__ uint4 s_st[kOwnSpan / 16];
+    __shared__ uint32_t s_st[kBlock];
     // stored terms: the vertices computed in full in this window, and their minima
     __shared__ RowList L;
     __shared__ unsigned long long s_ti[kStore ? kListCap : 1], s_to[kStore ? kListCap : 1];
@@ -1551,15 +1554,9 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
     const unsigned long long settled = ctl->h.settled;
     const bool fresh_all = kStore && ctl->h.pnum[par & 1] == a.fresh_at;
     const uint32_t n = a.g.n;
-    auto load16 = [&](uint64_t v0) {
-        if (v0 + 16 <= n) return *reinterpret_cast<const uint4 *>(a.b.st + v0);
-        uint32_t q[4] = {0u, 0u, 0u, 0u};
-        for (uint32_t j = 0; v0 + j < n; ++j) q[j >> 2] |= (uint32_t)a.b.st[v0 + j] << (8 * (j & 3));
-        return make_uint4(q[0], q[1], q[2], q[3]);
-    };
-    const uint64_t step = (uint64_t)gridDim.x * kOwnSpan;
-    uint64_t vb = (uint64_t)blockIdx.x * kOwnSpan;
-    uint4 x = vb < n ? load16(vb + 16u * threadIdx.x) : make_uint4(0u, 0u, 0u, 0u);
+    const uint64_t step = (uint64_t)gridDim.x * a.win;
+    uint64_t vb = (uint64_t)blockIdx.x * a.win;
+    uint32_t x = load_window(a, vb);
     const unsigned long long reached = wave_sum64(r0);
     if (reached == settled) return;
     const unsigned long long minD = wave_min64(m0);
@@ -1575,16 +1572,14 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
     };
     for (; vb < n; vb += step) {  // block-uniform
         bool any = false;
-        const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-        for (int j = 0; j < 16; ++j) any |= ((xs[j >> 2] >> (8 * (j & 3))) & ST_SET) == ST_F;
+        for (int j = 0; j < 4; ++j) any |= ((x >> (8 * j)) & ST_SET) == ST_F;
         __syncthreads();  // the previous window's LDS reads are done
-        s_st[threadIdx.x] = x;
+        store_window(a, s_st, x);
         if (kStore && threadIdx.x == 0) L.cnt = 0;
         if (__syncthreads_or(any)) {  // block-uniform
 #pragma unroll 2
-            for (uint32_t r = 0; r < kOwnSpan / kBlock; ++r) {
-                const uint32_t i = r * kBlock + threadIdx.x;
+            for (uint32_t i = threadIdx.x; i < a.win; i += kBlock) {
                 const uint32_t sb = sw[i];
                 if ((sb & ST_SET) != ST_F) continue;
                 const uint32_t v = (uint32_t)vb + i;
@@ -1686,7 +1681,7 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
                 }
             }
         }
-        if (vb + step < n) x = load16(vb + step + 16u * threadIdx.x);
+        if (vb + step < n) x = load_window(a, vb + step);
     }
     if (OUT != OUT_NONE) {
         block_reduce<kWaves, 1u, 1u>(&tmin, sh);
@@ -2516,10 +2511,17 @@ static kfn pick_mark(int in, int out) {
     return tab[i][o];
 }
 
-// Grid of the term pass: one block per kOwnSpan vertices, independent of the
-// scan grid (the term kernels loop over further windows if the grid is capped).
+// Windows of the term and dirty-set passes, one block each (the kernels loop over further windows
+// if the grid is capped). Their rows and cursors are chains of dependent loads, so that short windows
+// win, as more of them are in flight, until a block's start costs more. Measured per phase (us) with
+// windows of 4096 / 1024 / 256 vertices: random 2^16, degree 10: IN-SIMPLE|OUT-SIMPLE 50.8 / 31.3 /
+// 25.9, IN|OUT 93.6 / 51.1 / 40.0; grid of 249 k vertices, SIMPLE: 26.9 / 22.7 / 22.0; random, 1 M of
+// degree 10: 52.7 / 35.8 / 35.6 and 77.9 / 56.3 / 65.8; random 2^22, degree 16: 84.0 / 78.0 / 89.1 and
+// 138.6 / 138.8 / 185.9.
+static uint32_t term_window(uint32_t n) { return n <= (1u << 18) ? kBlock : 4 * kBlock; }
 static uint32_t terms_grid(uint32_t n) {
-    const uint64_t b = ((uint64_t)n + kOwnSpan - 1) / kOwnSpan;
+    const uint32_t w = term_window(n);
+    const uint64_t b = ((uint64_t)n + w - 1) / w;
     return (uint32_t)(b < 1 ? 1 : b > 65535 ? 65535 : b);
 }
 
@@ -3025,6 +3027,7 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     a.b.trace = nullptr;
     a.b.trace_cap = 0;
     a.crit = crit;
+    a.win = term_window(g->n);
     a.approx_k = apx ? *apx : 0u;
     a.mark = !learn && !trace_mode && !oracle && !apx && !delta_mode && stores(in, out);
     a.fresh_at = 0;
