@@ -112,7 +112,9 @@ typedef struct {
 int sssp_graph_create(uint32_t n, uint64_t m, const uint64_t *row_ptr, const uint32_t *col,
                       const uint32_t *weight, int device_ptrs, void *hip_stream, sssp_graph **out);
 
-/* Release every device buffer the graph owns. NULL is accepted. */
+/* Release every device buffer the graph owns. One block of 64 to 512 MiB per
+ * device, the graph's edges, is kept for the next graph that it fits; it is
+ * given back when an allocation of the library fails, and by a call with NULL. */
 int sssp_graph_destroy(sssp_graph *g);
 
 /* Change the HIP stream used by later calls on g. */
@@ -173,10 +175,10 @@ int sssp_delta_step_ex(sssp_graph *g, uint32_t source, const uint64_t *deltas, u
  * Runs on graphs[0]'s stream. In the default form each query of at most 2^19
  * vertices runs on a team of 1 to 32 workgroups (more for larger graphs, and
  * when there are few queries), all of them in one cooperative launch; a larger
- * graph, or a query alone, is solved on the whole device as by sssp_solve. The
- * call allocates about 16 bytes of device scratch per vertex that its
- * workgroups can hold (at most 16384 each), with a launch shape given about 29
- * bytes per vertex of each query, and frees it before returning. Errors: SSSP_ERR_INVALID for nq = 0, a NULL pointer, a bad source
+ * graph, or a query alone, is solved on the whole device as by sssp_solve.
+ * Device scratch: about 16 bytes per vertex that the workgroups hold (at most
+ * 16384 each, 150 MB in all), kept on graphs[0]; with a launch shape given about
+ * 29 bytes per vertex of each query, freed before returning. Errors: SSSP_ERR_INVALID for nq = 0, a NULL pointer, a bad source
  * or criterion; SSSP_ERR_UNSUPPORTED for the dynamic criteria; SSSP_ERR_OOM
  * when the scratch does not fit.
  */

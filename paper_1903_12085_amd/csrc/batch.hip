@@ -753,7 +753,7 @@ extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *so
         bool ran = true;
         if (!ids.empty()) {
             const int rc = resident_batch(graphs, sources, ids.data(), (uint32_t)ids.size(), in, out == OUT_STATIC_M,
-                                          dist_outs, phases_out, graphs[0]->stream, &ran);
+                                          dist_outs, phases_out, &ran);
             if (rc) return rc;
         }
         for (size_t j = 0; ran && j < rest.size(); ++j) {

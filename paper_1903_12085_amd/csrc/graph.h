@@ -10,6 +10,8 @@ struct sssp_graph {
     uint64_t m = 0;
     int device = 0;
     hipStream_t stream = nullptr;
+    void *base = nullptr;          // the allocation that holds rp, edges, vmin and emin
+    uint64_t base_bytes = 0;
     uint32_t *rp = nullptr;        // row_ptr as u32 (n+1)
     uint2 *edges = nullptr;        // (target, weight); rows sorted by weight once rows_sorted
     bool rows_sorted = false;      // set by graph_ensure_sorted (the dynamic criteria's cursors)
@@ -53,6 +55,8 @@ struct sssp_graph {
 
 DevGraph dev_view(const sssp_graph *g);
 int graph_ensure_csc(sssp_graph *g);
+void blocks_give_back();           // frees what is kept of destroyed graphs
+int resident_scratch(sssp_graph *g, uint64_t bytes);
 int graph_ensure_sorted(sssp_graph *g);
 void graph_default_cfg(sssp_graph *g);
 int solve_bufs_ensure(sssp_graph *g, bool cursors, bool stamps, bool queue, bool approx = false, bool store = false);
@@ -75,7 +79,7 @@ int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran);
 bool resident_batch_takes(const sssp_graph *g);
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
-                   bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, hipStream_t s, bool *ran);
+                   bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran);
 // A resident solve where the graph and its launch options allow one (phased.hip).
 int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
                  uint64_t *dist_out, uint32_t *phases_out, bool *ran);

@@ -4,7 +4,8 @@
 // computes the minimum in-edge weight with an atomic minimum per edge), and
 // the per-row weight sort and the reverse adjacency (CSC), both built lazily
 // for the dynamic criteria.
-#include <chrono>
+#include <algorithm>
+#include <mutex>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -32,22 +33,48 @@ extern "C" const char *sssp_last_error(void) { return g_err; }
 // ---------------------------------------------------------------------------
 // kernels
 
-// Checks row_ptr[0] == 0, monotone rows, row_ptr[n] == m and col < n.
-__global__ void k_validate(uint32_t n, uint64_t m, const uint64_t *__restrict__ rp,
-                           const uint32_t *__restrict__ col, unsigned int *__restrict__ bad) {
+// What creation learns about a graph, spread over kShards slots on lines of their own (same-address
+// atomics of many blocks serialise).
+struct CreateInfo {
+    struct alignas(128) Slot {
+        unsigned long long sum_w;   // sum of the weights
+        unsigned long long wmax;    // edges of weight 2^32 - 1
+        unsigned int max_deg;       // longest row
+    } s[kShards];
+    unsigned int bad;               // malformed CSR: 1 = rows, 2 = ends, 4 = targets
+};
+
+// One pass over the input: rows to 32 bits, edges to (target, weight) in input order, the weights'
+// sum and the edges of weight 2^32 - 1, and the checks row_ptr[0] == 0, monotone rows,
+// row_ptr[n] == m, col < n. Later kernels do nothing once a check has failed.
+__global__ __launch_bounds__(256) void k_load_csr(uint32_t n, uint64_t m, const uint64_t *__restrict__ rp64,
+                                                  const uint32_t *__restrict__ col, const uint32_t *__restrict__ w,
+                                                  uint32_t *__restrict__ rp, uint2 *__restrict__ edges, CreateInfo *info) {
+    __shared__ unsigned long long sh[8 * 4];
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (uint64_t v = t0; v < n; v += stride)
-        if (rp[v + 1] < rp[v]) atomicOr(bad, 1u);
-    if (t0 == 0 && (rp[0] != 0 || rp[n] != m)) atomicOr(bad, 2u);
-    for (uint64_t e = t0; e < m; e += stride)
-        if (col[e] >= n) atomicOr(bad, 4u);
-}
-
-__global__ void k_rp32(uint32_t n, const uint64_t *__restrict__ rp64, uint32_t *__restrict__ rp) {
-    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= n;
-         v += (uint64_t)gridDim.x * blockDim.x)
-        rp[v] = (uint32_t)rp64[v];
+    unsigned int bad = 0;
+    for (uint64_t v = t0; v <= n; v += stride) {
+        const uint64_t x = rp64[v];
+        if (v < n && rp64[v + 1] < x) bad |= 1u;
+        if ((v == 0 && x != 0) || (v == n && x != m)) bad |= 2u;
+        rp[v] = (uint32_t)x;
+    }
+    unsigned long long r[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // [0] weights, [1] edges of weight 2^32 - 1
+    for (uint64_t e = t0; e < m; e += stride) {
+        const uint2 ed = make_uint2(col[e], w[e]);
+        if (ed.x >= n) bad |= 4u;
+        r[0] += ed.y;
+        r[1] += ed.y == INF32 ? 1u : 0u;
+        edges[e] = ed;
+    }
+    if (bad) atomicOr(&info->bad, bad);
+    block_reduce<4, 3u, 0u>(r, sh);
+    if (threadIdx.x == 0) {
+        CreateInfo::Slot &s = info->s[blockIdx.x % kShards];
+        if (r[0]) atomicAdd(&s.sum_w, r[0]);
+        if (r[1]) atomicAdd(&s.wmax, r[1]);
+    }
 }
 
 // key = (target << 32) | weight for the reverse adjacency; payload = source.
@@ -79,8 +106,11 @@ __global__ void k_pack_edges(uint64_t m, const unsigned long long *__restrict__ 
 // binary search over the row starts held one per lane, and folds the weight
 // into that row's minimum in LDS.
 __global__ __launch_bounds__(256) void k_min_out(uint32_t n, const uint32_t *__restrict__ rp,
-                                                 const uint2 *__restrict__ edges, uint2 *__restrict__ vmin) {
+                                                 const uint2 *__restrict__ edges, uint2 *__restrict__ vmin,
+                                                 CreateInfo *info) {
+    if (info->bad) return;  // grid-uniform
     __shared__ uint32_t smin[256];
+    uint32_t dmax = 0;
     const uint32_t lane = threadIdx.x & 63;
     uint32_t *wmin = smin + (threadIdx.x & ~63u);
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -89,6 +119,8 @@ __global__ __launch_bounds__(256) void k_min_out(uint32_t n, const uint32_t *__r
         const uint32_t rs = v < n ? rp[v] : rp[n];  // this lane's row start (rows past n are empty)
         const uint32_t e0 = (uint32_t)__shfl((int)rs, 0, 64);
         const uint32_t e1 = rp[base + 64 < n ? base + 64 : n];
+        const uint32_t next = (uint32_t)__shfl_down((int)rs, 1, 64);
+        dmax = max(dmax, (lane == 63 ? e1 : next) - rs);  // rows past n start at e1
         wmin[lane] = INF32;
         __builtin_amdgcn_wave_barrier();
         for (uint32_t k = e0 + lane; __ballot(k < e1); k += 64) {  // wavefront-uniform
@@ -108,13 +140,9 @@ __global__ __launch_bounds__(256) void k_min_out(uint32_t n, const uint32_t *__r
         if (v < n) vmin[v] = make_uint2(INF32, wmin[lane]);
         __builtin_amdgcn_wave_barrier();
     }
-}
-
-// The input's edges as (target, weight), rows in input order.
-__global__ void k_pack_cw(uint64_t m, const uint32_t *__restrict__ col, const uint32_t *__restrict__ w,
-                          uint2 *__restrict__ out) {
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (uint64_t)gridDim.x * blockDim.x)
-        out[e] = make_uint2(col[e], w[e]);
+    for (int o = 32; o > 0; o >>= 1) dmax = max(dmax, (uint32_t)__shfl_xor((int)dmax, o, 64));
+    unsigned int *slot = &info->s[blockIdx.x % kShards].max_deg;
+    if (lane == 0 && dmax > *slot) atomicMax(slot, dmax);
 }
 
 // key = (row << 32) | weight and payload = target of every edge, for the row
@@ -134,56 +162,37 @@ __global__ void k_row_keys_e(uint32_t n, uint64_t m, const uint32_t *__restrict_
     }
 }
 
-// minIn[v] = min over in-edges (u, v) of c(u, v), by one atomic minimum per edge.
-__global__ void k_min_in(uint64_t m, const uint2 *__restrict__ edges, uint2 *__restrict__ vmin) {
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m;
-         e += (uint64_t)gridDim.x * blockDim.x) {
-        uint2 ed = edges[e];
-        uint32_t *slot = &vmin[ed.x].x;
-        if (ed.y < *slot) atomicMin(slot, ed.y);
+// Per edge (u, v): emin = minOut of v (relax folds the next OUT-STATIC threshold from the edge's own
+// position), and c(u, v) into minIn of v, by an atomic minimum where it is lower. Both come from one
+// random 8-byte load of v's minima, four edges' loads issued together: bound by the rate of random
+// lines, 1.2 ms for 2^26 edges over 2^22 vertices (with a pass for each minimum 2.4 ms).
+__global__ __launch_bounds__(256) void k_edge_minima(uint64_t m, const uint2 *__restrict__ edges, uint2 *vmin,
+                                                     uint32_t *__restrict__ emin, const CreateInfo *info) {
+    if (info->bad) return;  // grid-uniform
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t e0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e0 < m; e0 += 4 * stride) {
+        uint2 ed[4], mm[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (e0 + j * stride < m) ed[j] = edges[e0 + j * stride];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (e0 + j * stride < m) mm[j] = vmin[ed[j].x];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (e0 + j * stride < m) {
+                emin[e0 + j * stride] = mm[j].y;
+                if (ed[j].y < mm[j].x) atomicMin(&vmin[ed[j].x].x, ed[j].y);
+            }
     }
 }
 
-// emin[e] = minOut of edge e's target: relax folds the next OUT-STATIC threshold
+// After the rows were sorted: emin[e] = minOut of edge e's target: relax folds the next OUT-STATIC threshold
 // from the edge's own row position, with no load that waits for the atomic.
 __global__ void k_emin(uint64_t m, const uint2 *__restrict__ edges, const uint2 *__restrict__ vmin,
                        uint32_t *__restrict__ emin) {
     for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (uint64_t)gridDim.x * blockDim.x)
         emin[e] = vmin[edges[e].x].y;
-}
-
-// Exact sum of all edge weights (one block-level sum and one atomic per block);
-// out[1] counts the edges of weight 2^32 - 1, out[2] is the longest row.
-__global__ void k_sum_w(uint32_t n, uint64_t m, const uint32_t *__restrict__ rp, const uint2 *__restrict__ edges,
-                        unsigned long long *__restrict__ out) {
-    __shared__ unsigned long long sh[4], shx[4];
-    __shared__ uint32_t shd[4];
-    unsigned long long t = 0, x = 0;
-    uint32_t dmax = 0;
-    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (uint64_t)gridDim.x * blockDim.x)
-        dmax = max(dmax, rp[v + 1] - rp[v]);
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t w = edges[e].y;
-        t += w;
-        x += w == INF32 ? 1u : 0u;
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        t += __shfl_xor(t, o, 64);
-        x += __shfl_xor(x, o, 64);
-        dmax = max(dmax, (uint32_t)__shfl_xor((int)dmax, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        sh[threadIdx.x >> 6] = t;
-        shx[threadIdx.x >> 6] = x;
-        shd[threadIdx.x >> 6] = dmax;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicAdd(out, sh[0] + sh[1] + sh[2] + sh[3]);
-        const unsigned long long nx = shx[0] + shx[1] + shx[2] + shx[3];
-        if (nx) atomicAdd(out + 1, nx);
-        atomicMax(out + 2, (unsigned long long)max(max(shd[0], shd[1]), max(shd[2], shd[3])));
-    }
 }
 
 // in_ptr[v] = first index whose sorted key has target >= v.
@@ -236,82 +245,113 @@ static int radix_sort(unsigned long long *&k0, unsigned long long *&k1, uint32_t
 // ---------------------------------------------------------------------------
 // host API
 
+// One freed graph allocation per device is kept for the next graph: hipFree of a block of more than
+// 64 MiB takes 0.33 to 8 ms (smaller ones 12 us: the runtime keeps those itself), as much as the rest
+// of a creation or more. At most kKeepMax bytes; given back when an allocation fails, and by
+// sssp_graph_destroy(NULL). Every call on a graph has finished its device work when it returns, so a
+// block is idle here.
+constexpr uint64_t kKeepMin = 64ull << 20, kKeepMax = 512ull << 20;
+constexpr int kKeepDevices = 64;
+static std::mutex g_keep_mu;
+static struct { void *p; uint64_t bytes; } g_keep[kKeepDevices];
+
+static hipError_t block_alloc(int dev, uint64_t bytes, void **p, uint64_t *got) {
+    if (dev < kKeepDevices && bytes > kKeepMin) {
+        std::lock_guard<std::mutex> lock(g_keep_mu);
+        auto &k = g_keep[dev];
+        if (k.p && k.bytes >= bytes && k.bytes / 2 <= bytes) {
+            *p = k.p;
+            *got = k.bytes;
+            k.p = nullptr;
+            return hipSuccess;
+        }
+    }
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        blocks_give_back();
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    *got = bytes;
+    return e;
+}
+
+static void block_free(int dev, void *p, uint64_t bytes) {
+    if (p && dev < kKeepDevices && bytes > kKeepMin && bytes <= kKeepMax) {
+        std::lock_guard<std::mutex> lock(g_keep_mu);
+        std::swap(p, g_keep[dev].p);  // the block kept so far goes
+        g_keep[dev].bytes = bytes;
+    }
+    sssp_free(p);
+}
+
+void blocks_give_back() {
+    std::lock_guard<std::mutex> lock(g_keep_mu);
+    for (auto &k : g_keep) {
+        sssp_free(k.p);
+        k.p = nullptr;
+    }
+}
+
+static uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
+
+// Everything is queued on the stream and read back once: the arrays lie in one allocation, and
+// kernels that would follow a malformed row or target see the check's verdict on the device.
 static int create_impl(uint32_t n, uint64_t m, const uint64_t *row_ptr, const uint32_t *col,
                        const uint32_t *weight, int device_ptrs, hipStream_t s, sssp_graph *g) {
-    // 1. stage the CSR on the device
-    uint64_t *rp64 = nullptr;
-    uint32_t *dcol = nullptr, *dw = nullptr;
-    unsigned int *bad = nullptr;
-    int rc = SSSP_OK;
-#define TRY(call) do { hipError_t _e = (call); if (_e != hipSuccess) { \
-        rc = sssp_set_error(_e == hipErrorOutOfMemory ? SSSP_ERR_OOM : SSSP_ERR_DEVICE, "%s: %s", #call, hipGetErrorString(_e)); goto done; } } while (0)
-    TRY(hipMalloc(&g->rp, (n + 1) * sizeof(uint32_t)));
-    TRY(hipMalloc(&g->vmin, (uint64_t)n * sizeof(uint2)));
-    TRY(hipMalloc(&g->edges, (m ? m : 1) * sizeof(uint2)));
-    TRY(hipMalloc(&g->emin, (m ? m : 1) * sizeof(uint32_t)));
-    TRY(hipMalloc(&bad, sizeof(unsigned int)));
-    TRY(hipMemsetAsync(bad, 0, sizeof(unsigned int), s));
-    if (device_ptrs) {
-        rp64 = (uint64_t *)row_ptr;
-        dcol = (uint32_t *)col;
-        dw = (uint32_t *)weight;
-    } else {
-        TRY(hipMalloc(&rp64, (n + 1) * sizeof(uint64_t)));
-        TRY(hipMemcpyAsync(rp64, row_ptr, (n + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
+    const uint64_t o_edges = up256(sizeof(CreateInfo)), o_emin = up256(o_edges + m * sizeof(uint2)),
+                   o_vmin = up256(o_emin + m * sizeof(uint32_t)), o_rp = up256(o_vmin + (uint64_t)n * sizeof(uint2)),
+                   total = o_rp + (n + 1ull) * sizeof(uint32_t);
+    HIP_OK(block_alloc(g->device, total, &g->base, &g->base_bytes));
+    uint8_t *base = (uint8_t *)g->base;
+    CreateInfo *info = (CreateInfo *)base;
+    g->edges = (uint2 *)(base + o_edges);
+    g->emin = (uint32_t *)(base + o_emin);
+    g->vmin = (uint2 *)(base + o_vmin);
+    g->rp = (uint32_t *)(base + o_rp);
+    HIP_OK(hipMemsetAsync(info, 0, sizeof(CreateInfo), s));
+    CallBuffer stage;  // host input on the device
+    if (!device_ptrs) {
+        const uint64_t o_col = up256((n + 1ull) * sizeof(uint64_t)), o_w = up256(o_col + m * sizeof(uint32_t));
+        HIP_OK(hipMalloc(&stage.p, o_w + m * sizeof(uint32_t)));
+        uint8_t *st = (uint8_t *)stage.p;
+        HIP_OK(hipMemcpyAsync(st, row_ptr, (n + 1ull) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
         if (m) {
-            TRY(hipMalloc(&dcol, m * sizeof(uint32_t)));
-            TRY(hipMalloc(&dw, m * sizeof(uint32_t)));
-            TRY(hipMemcpyAsync(dcol, col, m * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-            TRY(hipMemcpyAsync(dw, weight, m * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+            HIP_OK(hipMemcpyAsync(st + o_col, col, m * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+            HIP_OK(hipMemcpyAsync(st + o_w, weight, m * sizeof(uint32_t), hipMemcpyHostToDevice, s));
         }
+        row_ptr = (const uint64_t *)st;
+        col = (const uint32_t *)(st + o_col);
+        weight = (const uint32_t *)(st + o_w);
     }
-    {
-        hipLaunchKernelGGL(k_validate, dim3(grid_for(m > n ? m : n)), dim3(256), 0, s, n, m, rp64, dcol, bad);
-        unsigned int hbad = 0;
-        TRY(hipMemcpyAsync(&hbad, bad, sizeof hbad, hipMemcpyDeviceToHost, s));
-        TRY(hipStreamSynchronize(s));
-        if (hbad) { rc = sssp_set_error(SSSP_ERR_INVALID, "malformed CSR (code %u)", hbad); goto done; }
-    }
-    {
-        hipEvent_t e0, e1;
-        TRY(hipEventCreate(&e0));
-        TRY(hipEventCreate(&e1));
-        TRY(hipEventRecord(e0, s));
-        hipLaunchKernelGGL(k_rp32, dim3(grid_for(n + 1)), dim3(256), 0, s, n, rp64, g->rp);
-        // 2. the edges in input order; rows are sorted by weight only when a solve first needs the
-        // cursors of the dynamic criteria (graph_ensure_sorted)
-        if (m) hipLaunchKernelGGL(k_pack_cw, dim3(grid_for(m)), dim3(256), 0, s, m, dcol, dw, g->edges);
-        // 3. static minima
-        hipLaunchKernelGGL(k_min_out, dim3(grid_for(n)), dim3(256), 0, s, n, g->rp, g->edges, g->vmin);
-        if (m) hipLaunchKernelGGL(k_min_in, dim3(grid_for(m)), dim3(256), 0, s, m, g->edges, g->vmin);
-        if (m) hipLaunchKernelGGL(k_emin, dim3(grid_for(m)), dim3(256), 0, s, m, g->edges, g->vmin, g->emin);
-        TRY(hipEventRecord(e1, s));
-        TRY(hipEventSynchronize(e1));
-        if (m) {  // weight sum for the selector's feature scale and the 2^32 - 1 flag (not timed)
-            unsigned long long *dsum = nullptr;
-            TRY(hipMalloc(&dsum, 4 * sizeof(unsigned long long)));
-            TRY(hipMemsetAsync(dsum, 0, 4 * sizeof(unsigned long long), s));  // whole 16-byte words: one fill
-            hipLaunchKernelGGL(k_sum_w, dim3(grid_for(m, 256, 1024)), dim3(256), 0, s, n, m, g->rp, g->edges, dsum);
-            unsigned long long hs[4] = {0, 0, 0, 0};
-            TRY(hipMemcpyAsync(hs, dsum, sizeof hs, hipMemcpyDeviceToHost, s));
-            TRY(hipStreamSynchronize(s));
-            sssp_free(dsum);
-            g->sum_w = hs[0];
-            g->wmax = hs[1] != 0;
-            g->max_deg = (uint32_t)hs[2];
+    struct Events {
+        hipEvent_t e[2] = {nullptr, nullptr};
+        ~Events() {
+            for (hipEvent_t x : e)
+                if (x) (void)hipEventDestroy(x);
         }
-        float ms = 0;
-        TRY(hipEventElapsedTime(&ms, e0, e1));
-        g->precompute_ns = (uint64_t)(ms * 1e6);
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-        TRY(hipGetLastError());
+    } ev;
+    for (hipEvent_t &x : ev.e) HIP_OK(hipEventCreate(&x));
+    HIP_OK(hipEventRecord(ev.e[0], s));
+    hipLaunchKernelGGL(k_load_csr, dim3(grid_for(m > n ? m : n + 1ull, 256, 4096)), dim3(256), 0, s, n, m, row_ptr, col,
+                       weight, g->rp, g->edges, info);
+    hipLaunchKernelGGL(k_min_out, dim3(grid_for(n)), dim3(256), 0, s, n, g->rp, g->edges, g->vmin, info);
+    if (m) hipLaunchKernelGGL(k_edge_minima, dim3(grid_for(m, 1024)), dim3(256), 0, s, m, g->edges, g->vmin, g->emin, info);
+    HIP_OK(hipEventRecord(ev.e[1], s));
+    HIP_OK(hipGetLastError());
+    CreateInfo h;
+    HIP_OK(hipMemcpyAsync(&h, info, sizeof h, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    if (h.bad) return sssp_set_error(SSSP_ERR_INVALID, "malformed CSR (code %u)", h.bad);
+    for (const CreateInfo::Slot &x : h.s) {
+        g->sum_w += x.sum_w;
+        g->wmax |= x.wmax != 0;
+        g->max_deg = std::max(g->max_deg, x.max_deg);
     }
-done:
-#undef TRY
-    if (!device_ptrs) { sssp_free(rp64); sssp_free(dcol); sssp_free(dw); }
-    sssp_free(bad);
-    return rc;
+    float ms = 0;
+    HIP_OK(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
+    g->precompute_ns = (uint64_t)(ms * 1e6);
+    return SSSP_OK;
 }
 
 extern "C" int sssp_graph_create(uint32_t n, uint64_t m, const uint64_t *row_ptr, const uint32_t *col,
@@ -346,8 +386,11 @@ extern "C" int sssp_graph_create(uint32_t n, uint64_t m, const uint64_t *row_ptr
 }
 
 extern "C" int sssp_graph_destroy(sssp_graph *g) {
-    if (!g) return SSSP_OK;
-    sssp_free(g->rp); sssp_free(g->edges); sssp_free(g->vmin); sssp_free(g->emin);
+    if (!g) {
+        blocks_give_back();
+        return SSSP_OK;
+    }
+    block_free(g->device, g->base, g->base_bytes);  // rows, edges and minima
     sssp_free(g->ip); sssp_free(g->in_edges);
     sssp_free(g->res);
     sssp_free(g->one_fm);  // the one-workgroup scratch's other buffers go with solve_bufs_free

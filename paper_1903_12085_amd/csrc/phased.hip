@@ -2403,7 +2403,12 @@ static uint32_t shard_capacity(uint32_t n, int G) {
 // call starts the group afresh.
 static int alloc_group(void **const *ptr, const uint64_t *bytes, int k) {
     for (int i = 0; i < k; ++i) {
-        const hipError_t e = hipMalloc(ptr[i], bytes[i] ? bytes[i] : 1);
+        hipError_t e = hipMalloc(ptr[i], bytes[i] ? bytes[i] : 1);
+        if (e == hipErrorOutOfMemory) {
+            blocks_give_back();
+            (void)hipGetLastError();
+            e = hipMalloc(ptr[i], bytes[i] ? bytes[i] : 1);
+        }
         if (e != hipSuccess) {
             for (int j = 0; j < k; ++j) {
                 sssp_free(*ptr[j]);
@@ -3163,6 +3168,23 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     return rc;
 }
 
+// The graph's scratch for resident solves and batches, kept between them.
+int resident_scratch(sssp_graph *g, uint64_t bytes) {
+    if (g->res_bytes >= bytes) return SSSP_OK;
+    sssp_free(g->res);
+    g->res = nullptr;
+    g->res_bytes = 0;
+    hipError_t e = hipMalloc(&g->res, bytes);
+    if (e == hipErrorOutOfMemory) {
+        blocks_give_back();
+        (void)hipGetLastError();
+        e = hipMalloc(&g->res, bytes);
+    }
+    HIP_OK(e);
+    g->res_bytes = bytes;
+    return SSSP_OK;
+}
+
 // A resident solve where the graph and the launch options allow one, with the graph's scratch
 // (kept between solves). *ran = false: not run, or not finished; the phase kernels then do it
 // (they also do timed solves: per-kernel timing is about them).
@@ -3171,15 +3193,10 @@ int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, bool out
     *ran = false;
     const ResShape r = resident_shape(g);
     if (!r.fits || g->prof) return SSSP_OK;
-    if (g->res_bytes < r.bytes) {
-        sssp_free(g->res);
-        g->res = nullptr;
-        g->res_bytes = 0;
-        HIP_OK(hipMalloc(&g->res, r.bytes));
-        g->res_bytes = r.bytes;
-    }
+    int rc = resident_scratch(g, r.bytes);
+    if (rc) return rc;
     uint32_t phases = 0;
-    const int rc = resident_solve(g, r, s, source, in, out_static, delta, dist_out, g->res, &phases, ran);
+    rc = resident_solve(g, r, s, source, in, out_static, delta, dist_out, g->res, &phases, ran);
     if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
     return rc;
 }

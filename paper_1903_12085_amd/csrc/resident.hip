@@ -948,10 +948,11 @@ static uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
 bool resident_batch_takes(const sssp_graph *g) { return g->n <= (uint64_t)kGang * kWgVertices; }
 
 // Solves the queries ids[0 .. nq) (each of a graph that resident_batch_takes) in one cooperative
-// launch on stream s. *ran = false: as in resident_solve.
+// launch on graphs[0]'s stream and scratch. *ran = false: as in resident_solve.
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
-                   bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, hipStream_t s, bool *ran) {
+                   bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran) {
     *ran = false;
+    hipStream_t s = graphs[0]->stream;
     const bafn k = pick_res_batch(in, out_static);
     int dev = 0, cus = 0, per_cu = 0;
     HIP_OK(hipGetDevice(&dev));
@@ -1005,9 +1006,10 @@ int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uin
                    o_phases = up256(o_heads + 4 * (kGangLog + 2)), o_bar = up256(o_phases + 4ull * nq),
                    o_rec = up256(o_bar + gangs * 2 * kGang * kTeamBar * 8), o_box = up256(o_rec + blocks * kShareCap * 16),
                    o_mark = up256(o_box + blocks * wgv * 16), total = o_mark + blocks * 2 * slots;
-    CallBuffer buf;
-    HIP_OK(hipMalloc(&buf.p, total));
-    uint8_t *base = (uint8_t *)buf.p;
+    // kept on graphs[0]: allocating and freeing it took 0.4 to 8 ms a call
+    const int rc = resident_scratch(graphs[0], total);
+    if (rc) return rc;
+    uint8_t *base = (uint8_t *)graphs[0]->res;
     std::vector<uint8_t> up(o_heads);
     ResQuery *hq = (ResQuery *)up.data();
     for (uint32_t i = 0; i < nq; ++i) {
