@@ -303,7 +303,8 @@ typedef struct {
                                scan_blocks * 4), else the dense scan runs. Ignored by every other
                                criterion and solver. Values above 2: SSSP_ERR_INVALID. */
     uint32_t single;        /* how sssp_solve runs a criterion made of DIJK, IN_STATIC and OUT_STATIC
-                               (sssp_delta_step: 0 and 1 resident, 2 the phase kernels).
+                               (sssp_delta_step, and sssp_solve with IN_SIMPLE or OUT_SIMPLE and
+                               no stronger member: 0 and 1 resident, 2 the phase kernels).
                                0 (default): resident, the whole solve in one cooperative launch whose
                                workgroups meet at a barrier once per phase (graphs of at most 2^24
                                vertices; larger ones, and solves with per-kernel timing on, use the

@@ -75,11 +75,11 @@ struct ResShape {
     uint64_t bytes;       // device scratch
 };
 ResShape resident_shape(const sssp_graph *g);
-int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
+int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran);
 bool resident_batch_takes(const sssp_graph *g);
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
                    bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran);
 // A resident solve where the graph and its launch options allow one (phased.hip).
-int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
+int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                  uint64_t *dist_out, uint32_t *phases_out, bool *ran);

@@ -3188,15 +3188,21 @@ int resident_scratch(sssp_graph *g, uint64_t bytes) {
 // A resident solve where the graph and the launch options allow one, with the graph's scratch
 // (kept between solves). *ran = false: not run, or not finished; the phase kernels then do it
 // (they also do timed solves: per-kernel timing is about them).
-int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
+int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                  uint64_t *dist_out, uint32_t *phases_out, bool *ran) {
     *ran = false;
     const ResShape r = resident_shape(g);
     if (!r.fits || g->prof) return SSSP_OK;
-    int rc = resident_scratch(g, r.bytes);
+    int rc = SSSP_OK;
+    if (!static_modes(in, out)) {  // heads, cursors and sorted rows, as the phase kernels need them
+        if (in == IN_SIMPLE_M) rc = graph_ensure_csc(g);
+        if (rc == SSSP_OK) rc = graph_ensure_sorted(g);
+        if (rc == SSSP_OK) rc = solve_bufs_ensure(g, true, false, false);
+    }
+    if (rc == SSSP_OK) rc = resident_scratch(g, r.bytes);
     if (rc) return rc;
     uint32_t phases = 0;
-    rc = resident_solve(g, r, s, source, in, out_static, delta, dist_out, g->res, &phases, ran);
+    rc = resident_solve(g, r, s, source, in, out, delta, dist_out, g->res, &phases, ran);
     if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
     return rc;
 }
@@ -3206,14 +3212,14 @@ extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, ui
     if (g && g->cfg.single != kPhaseKernels && criterion != 0 && !(criterion & ~SSSP_CRIT_ALL)) {
         int in = IN_NONE, out = OUT_NONE;
         crit_modes(criterion, &in, &out);
-        if (static_modes(in, out)) {
+        if (in <= IN_SIMPLE_M && out <= OUT_SIMPLE_M) {
             if (!dist_out) return sssp_set_error(SSSP_ERR_INVALID, "dist_out is NULL");
             if (source >= g->n) return sssp_set_error(SSSP_ERR_INVALID, "source %u >= n = %u", source, g->n);
             HIP_OK(hipSetDevice(g->device));
             // the whole solve in one workgroup (the batched kernel)
-            if (g->cfg.single) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
+            if (g->cfg.single && static_modes(in, out)) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
             bool ran = false;
-            const int rc = resident_try(g, g->stream, source, in, out == OUT_STATIC_M, 0, dist_out, phases_out, &ran);
+            const int rc = resident_try(g, g->stream, source, in, out, 0, dist_out, phases_out, &ran);
             if (rc || ran) return rc;
         }
     }
@@ -3235,7 +3241,7 @@ extern "C" int sssp_delta_step(sssp_graph *g, uint32_t source, uint64_t delta, u
     if (g && dist_out && source < g->n && g->cfg.single != kPhaseKernels) {
         HIP_OK(hipSetDevice(g->device));
         bool ran = false;
-        const int rc = resident_try(g, g->stream, source, IN_NONE, false, delta, dist_out, phases_out, &ran);
+        const int rc = resident_try(g, g->stream, source, IN_NONE, OUT_NONE, delta, dist_out, phases_out, &ran);
         if (rc || ran) return rc;
     }
     sssp_stats st;
@@ -3472,7 +3478,7 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
     if (r.fits && r.bytes <= kNoAllocBytes) {
         bool ran = false;
         uint32_t phases = 0;
-        rc = resident_solve(g, r, g->stream, source, in, out == OUT_STATIC_M, 0, dist_out, base, &phases, &ran);
+        rc = resident_solve(g, r, g->stream, source, in, out, 0, dist_out, base, &phases, &ran);
         if (rc) return rc;
         if (ran) {
             if (phases_out) *phases_out = phases;

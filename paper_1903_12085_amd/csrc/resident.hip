@@ -1,6 +1,7 @@
 // Resident solver: the whole solve of one query in one cooperative launch, for
-// sssp_solve and sssp_solve_noalloc with static criteria, and for sssp_delta_step;
-// and batches of queries, each by a team of workgroups (at the end of this file).
+// sssp_solve and sssp_solve_noalloc with static criteria, for sssp_solve with SIMPLE
+// ones, and for sssp_delta_step; and batches of queries, each by a team of workgroups
+// (at the end of this file).
 //
 // W workgroups (a power of two) stay on the device for the whole solve. The
 // vertices are cut into groups of K = 8 (16) consecutive ones; every group has an
@@ -33,6 +34,20 @@
 // a box undercuts its distance), the heavy round those the bucket removed. The
 // barrier carries whether anything was lowered inside the window, and after a
 // heavy round the smallest queued distance.
+//
+// SIMPLE criteria (eq. crit:insimple, crit:outsimple): a vertex's term is the lightest edge of a
+// sorted row whose other end has not settled; the vertex keeps that edge, its head. Certifying
+// must not start before every head is current, and heads move when vertices settle, so a phase
+// has a second barrier: refresh the heads, combine minD and T, certify, relax, meet. With it one
+// box per vertex does; its top bit says settled. A relax marks its target also where the edge is
+// the target's IN head. OUT heads would need the in-edges of all that settles, so they are
+// checked lazily: a sum d + term seen before is a lower bound, and only a sum below the next T
+// matters. Sums up to a guess, four times as far beyond the last T as that lay beyond its minD,
+// are checked before the barrier; when T turns out larger, a further pass and barrier follow
+// (1.5 passes a phase on a random graph with the guess one time as far, 1.1 with four times).
+// R-MAT 20: 31.6 us a phase, 46.5 with the phase kernels; random, 1 M vertices of degree 16: 20.9
+// and 38.2; 5000 of degree 9: 11.8 and 26.7. Half of a phase is the wait for the wavefront with
+// the longest chain of loads in refresh.
 //
 // Skewed graphs (a row over kShareDeg edges): one workgroup's segments would
 // hold up all, so its segments form one list, and rows past a quota, or longer
@@ -101,6 +116,12 @@ struct ResArgs {
     uint32_t share;      // rows beyond the quota become records relaxed by all workgroups
     uint32_t lgK;        // vertices per group
     unsigned long long delta;  // Delta-stepping: bucket width
+    // SIMPLE criteria: the reverse adjacency and, per vertex, the lightest edge of each row whose other
+    // end had not settled when the owner last looked, with its place in the row
+    const uint32_t *ip;
+    const uint2 *in_edges;
+    uint2 *in_head, *out_head;
+    uint32_t *in_cur, *out_cur;
 };
 
 __device__ __forceinline__ unsigned long long ld64(const unsigned long long *p) {
@@ -188,13 +209,43 @@ __device__ __forceinline__ void wave_fence() {  // LDS values pass between lanes
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// SIMPLE criteria, instead of k_res_init: of the two words per vertex in `box` the first is the box,
+// the second the weight of its IN head (all ones without one).
+__global__ void k_res_init_simple(ResArgs a, ResCtl *ctl, int in_simple) {
+    const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint2 none = make_uint2(INF32, INF32);
+    for (uint64_t v = t0; v < a.n; v += stride) {
+        const unsigned long long x = v == a.src ? 0ull : INF64;
+        a.dist[v] = x;
+        const uint32_t o = a.rp[v];
+        a.out_cur[v] = o;
+        a.out_head[v] = o < a.rp[v + 1] ? a.edges[o] : none;
+        uint2 h = none;
+        if (in_simple) {
+            const uint32_t i = a.ip[v];
+            if (i < a.ip[v + 1]) h = a.in_edges[i];
+            a.in_cur[v] = i;
+            a.in_head[v] = h;
+        }
+        a.box[2 * v] = x;
+        a.box[2 * v + 1] = h.x != INF32 ? h.y : INF64;
+    }
+    const uint64_t src_mark = mark_of(a, a.src >> a.lgK);
+    uint32_t *mw = reinterpret_cast<uint32_t *>(a.mark);
+    for (uint64_t i = t0; i < (uint64_t)a.W * a.mstride / 2; i += stride)
+        mw[i] = i == src_mark / 4 ? phase_tag(0) << (8 * (src_mark & 3)) : 0u;
+    uint32_t *c = reinterpret_cast<uint32_t *>(ctl);
+    for (uint64_t i = t0; i < sizeof(ResCtl) / 4; i += stride) c[i] = 0;
+}
+
 // One solve by a team of a.W workgroups, this one the wg-th. Boxes, marks and distances are set up
 // and visible to the team; nb counts the team's barriers. Returns the number of phases (rounds), or
 // INF32 when a workgroup did not arrive in time (a.error is set).
-template <int BS, int K, int IN, bool OUT, bool DELTA>
+template <int BS, int K, int IN, int OUT, bool DELTA>
 __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, uint32_t &nb) {
     extern __shared__ unsigned long long dyn[];
     constexpr uint32_t kWv = BS / 64, kR = 64 / K;
+    constexpr bool SIMPLE = IN == IN_SIMPLE_M || OUT == OUT_SIMPLE_M;
     __shared__ unsigned long long s_red[2 * kWv];
     __shared__ unsigned long long s_all[2 * (kResMaxW / 64)];
     __shared__ uint32_t s_wn[kWv], s_wl[kWv];  // per list: segments reserved, first reservation that failed
@@ -240,7 +291,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
     pend += ws0;
     auto first_vertex = [&](uint32_t s) { return ((((s * kWv + wave) << a.lgW) | wg)) * K; };
     unsigned long long *myshare = a.rec + 2ull * kShareCap * wg;
-    unsigned long long minD = 0, T = OUT ? min_out64(a.vmin[a.src].y, a.wmax, a.rp, a.src) : 0ull;
+    unsigned long long minD = 0, T = OUT && !SIMPLE ? min_out64(a.vmin[a.src].y, a.wmax, a.rp, a.src) : 0ull;
     __syncthreads();
 
     // Cuts the row [r0, r0 + deg) of a settled vertex at distance d into segments of this
@@ -271,27 +322,258 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
     // light round of a bucket, 1 = later light round, 2 = heavy round
     int kind = 0;
     unsigned long long hi = a.delta;
+    // SIMPLE criteria: groups whose minimum of d + OUT term lies below `guess` are refreshed unasked
+    unsigned long long guess = 0;
+    auto in_term = [&](uint2 mm, uint2 h) { return IN != IN_SIMPLE_M ? min_in_test(mm.x) : h.x != INF32 ? h.y : INF64; };
+    auto out_term = [&](uint2 mm, uint2 h, uint32_t v) {
+        return OUT != OUT_SIMPLE_M ? min_out64(mm.y, a.wmax, a.rp, v) : h.x != INF32 ? h.y : INF64;
+    };
     for (uint32_t k = 0; minD != INF64; ++k) {
         const uint32_t par = k & 1;
+        const uint8_t pt = (uint8_t)phase_tag(k);
+        if constexpr (SIMPLE) {
+            // The barrier of step 4 between refresh and certify; false when a workgroup did not arrive in
+            // time. (Step 4 itself stays spelled out: as a call of this it takes 18 more registers and 1 to
+            // 3 % of the time of the static criteria.)
+            auto meet = [&](unsigned long long tag, unsigned long long *bar_a, unsigned long long fm, unsigned long long ft,
+                            unsigned long long &pm, unsigned long long &pt2) {
+                fm = wave_min_rel(fm, minD);
+                if (OUT) ft = wave_min_rel(ft, minD);
+                if (lane == 0) {
+                    s_red[wave] = fm;
+                    if (OUT) s_red[kWv + wave] = ft;
+                }
+                __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have completed
+                __syncthreads();
+                if (wave == 0) {  // lanes below kWv: the minima, the next kWv: the thresholds
+                    unsigned long long x = lane < (OUT ? 2 * kWv : kWv) ? s_red[lane] : INF64;
+                    x = umin64(x, dpp64<kDppQuadSwap1>(x));
+                    x = umin64(x, dpp64<kDppQuadSwap2>(x));
+                    if (kWv >= 8) x = umin64(x, dpp64<kDppHalfMirror>(x));
+                    if (kWv >= 16) x = umin64(x, dpp64<kDppMirror>(x));
+                    if (lane == 0 || (OUT && lane == kWv))
+                        st_agent(&bar_a[wg * kSlotStride + (lane ? 1 : 0)], tag | umin64(x, kVal));
+                }
+                pm = pt2 = kVal;
+                if (tid < W) {
+                    const unsigned long long *w = &bar_a[tid * kSlotStride];
+                    uint32_t spins = 0;
+                    for (;;) {
+                        pm = ld64(w);
+                        if (OUT) pt2 = ld64(w + 1);
+                        if ((pm & kTag) == tag && (!OUT || (pt2 & kTag) == tag)) break;
+                        if (++spins >= kResSpin) {
+                            atomicOr(&s_flags, 1u);
+                            break;
+                        }
+                    }
+                    pm &= kVal;
+                    if (OUT) pt2 &= kVal;
+                }
+                if (wave * 64 < W) {
+                    pm = wave_min_rel(pm == kVal ? INF64 : pm, minD);
+                    if (OUT) pt2 = wave_min_rel(pt2 == kVal ? INF64 : pt2, minD);
+                    if (lane == 0) {
+                        s_all[wave] = pm;
+                        s_all[kResMaxW / 64 + wave] = pt2;
+                    }
+                }
+                __syncthreads();
+                if (s_flags & 1u) {  // block-uniform
+                    if (tid == 0) atomicOr(a.error, 1u);
+                    return false;
+                }
+                pm = s_all[0];
+                pt2 = s_all[kResMaxW / 64];
+                for (uint32_t i = 1; i * 64 < W; ++i) {
+                    pm = umin64(pm, s_all[i]);
+                    pt2 = umin64(pt2, s_all[kResMaxW / 64 + i]);
+                }
+                pm = readlane64(pm, 0);
+                if (OUT) pt2 = readlane64(pt2, 0);
+                return true;
+            };
+            uint32_t na = 0;
+            auto list = [&](uint32_t j, bool act) {
+                const unsigned long long mask = __ballot(act);
+                if (act) lst[na + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)(j * 64 + lane);
+                na += (uint32_t)__popcll(mask);
+            };
+            {
+                uint8_t m[kMaxJ];
+#pragma unroll
+                for (uint32_t j = 0; j < kMaxJ; ++j) {
+                    m[j] = 0;
+                    if (j < nj) m[j] = __hip_atomic_load(mk + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (uint32_t j = 0; j < kMaxJ; ++j) {
+                    if (j >= nj) break;  // block-uniform
+                    const unsigned long long o = OUT == OUT_SIMPLE_M ? go[j * 64 + lane] : INF64;
+                    list(j, m[j] == pt || (o != INF64 && o <= guess));
+                }
+            }
+            // Brings the listed groups' minima up to date. An OUT head is looked at only where the sum it
+            // was last seen with is at most `limit`: it only grows, so larger ones stay larger.
+            auto refresh = [&](unsigned long long limit) {
+                struct Vert {
+                    uint32_t s, v, cur, end;
+                    unsigned long long d;
+                    uint2 mm, hi, ho;
+                };
+                auto load = [&](uint32_t i0) {
+                    Vert c{INF32, 0u, 0u, 0u, INF64, make_uint2(INF32, INF32), make_uint2(INF32, INF32), make_uint2(INF32, INF32)};
+                    const uint32_t i = i0 + lane / K;
+                    if (i < na) {
+                        c.s = lst[i];
+                        c.v = first_vertex(c.s) + li;
+                        if (c.v < n) {
+                            c.d = ld64(&a.box[2ull * c.v]);
+                            if (IN == IN_SIMPLE_M) {
+                                c.hi = a.in_head[c.v];
+                                c.cur = a.in_cur[c.v];
+                                c.end = a.ip[c.v + 1];
+                            }
+                            if (OUT == OUT_SIMPLE_M) c.ho = a.out_head[c.v];
+                            if (IN == IN_STATIC_M || OUT == OUT_STATIC_M) c.mm = a.vmin[c.v];
+                        }
+                    }
+                    return c;
+                };
+                struct Next {
+                    uint2 e[2];
+                };
+                auto next_edges = [&](const uint2 *row, uint32_t cur, uint32_t end) {
+                    Next x;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        x.e[q] = make_uint2(INF32, INF32);
+                        if (cur + q < end) x.e[q] = row[cur + q];
+                    }
+                    return x;
+                };
+                // h: the first edge at or after row[cur] whose other end has not settled; x holds the next two.
+                // Two at a time, read before it is known that the head settled: of the vertices looked at
+                // few move and most of these by one (four at a time 3 to 4 % slower, none ahead 2 to 5 %)
+                auto advance = [&](uint2 &h, uint32_t &cur, Next x, const uint2 *row, uint32_t end) {
+                    for (;;) {
+                        unsigned long long d[2];
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) d[q] = x.e[q].x != INF32 ? ld64(&a.box[2ull * x.e[q].x]) : INF64;
+                        h = make_uint2(INF32, INF32);
+                        uint32_t step = 2;
+#pragma unroll
+                        for (int q = 1; q >= 0; --q)
+                            if (!dist_settled(d[q])) {  // an edge, or the end of the row
+                                h = x.e[q];
+                                step = q;
+                            }
+                        cur += step;
+                        if (step < 2) return;
+                        x = next_edges(row, cur, end);
+                    }
+                };
+                wave_fence();
+                Vert nxt = load(0);
+                for (uint32_t i0 = 0; i0 < na; i0 += kR) {
+                    Vert c = nxt;
+                    if (i0 + kR < na) nxt = load(i0 + kR);
+                    const bool q = !(c.d >> 63);  // queued: neither infinite nor settled
+                    const bool qi = IN == IN_SIMPLE_M && q && c.hi.x != INF32;
+                    const bool qo = OUT == OUT_SIMPLE_M && q && c.ho.x != INF32 && sadd64(c.d, c.ho.y) <= limit;
+                    unsigned long long xi = INF64, xo = INF64;
+                    uint32_t ocur = 0, oend = 0;
+                    if (qo) {
+                        xo = ld64(&a.box[2ull * c.ho.x]);
+                        ocur = a.out_cur[c.v] + 1;
+                        oend = a.rp[c.v + 1];
+                    }
+                    if (qi) {
+                        xi = ld64(&a.box[2ull * c.hi.x]);
+                        const Next x = next_edges(a.in_edges, ++c.cur, c.end);
+                        if (dist_settled(xi)) {
+                            advance(c.hi, c.cur, x, a.in_edges, c.end);
+                            a.in_cur[c.v] = c.cur;
+                            a.in_head[c.v] = c.hi;
+                            st_agent(&a.box[2ull * c.v + 1], c.hi.x != INF32 ? (unsigned long long)c.hi.y : INF64);
+                        }
+                    }
+                    if (dist_settled(xo)) {
+                        advance(c.ho, ocur, next_edges(a.edges, ocur, oend), a.edges, oend);
+                        a.out_cur[c.v] = ocur;
+                        a.out_head[c.v] = c.ho;
+                    }
+                    if (q) a.dist[c.v] = c.d;
+                    const unsigned long long mi = in_term(c.mm, c.hi), mo = out_term(c.mm, c.ho, c.v);
+                    // keys below the last minD pass any test: cut off there, where the minima are based
+                    unsigned long long key = c.d > mi ? c.d - mi : 0ull;
+                    if (key < minD) key = minD;
+                    const unsigned long long rk = IN != IN_NONE ? row_min_rel<K>(q ? key : INF64, minD) : INF64;
+                    const unsigned long long rd = row_min_rel<K>(q ? c.d : INF64, minD);
+                    const unsigned long long ro = OUT ? row_min_rel<K>(q ? sadd64(c.d, mo) : INF64, minD) : INF64;
+                    if (c.s != INF32 && li == 0) {
+                        if (IN != IN_NONE) gk[c.s] = rk;
+                        gd[c.s] = rd;
+                        if (OUT) go[c.s] = ro;
+                    }
+                }
+                wave_fence();
+            };
+            unsigned long long pm, pt2;
+            for (;;) {
+                refresh(guess);
+                unsigned long long fm = INF64, ft = INF64;
+#pragma unroll
+                for (uint32_t j = 0; j < kMaxJ; ++j)
+                    if (j < nj) {
+                        fm = umin64(fm, gd[j * 64 + lane]);
+                        if (OUT) ft = umin64(ft, go[j * 64 + lane]);
+                    }
+                if (!meet(bar_tag(nb), a.bar + (nb & 1) * bstride, fm, ft, pm, pt2)) return INF32;
+                ++nb;
+                // sums up to the guess are exact, larger ones lower bounds
+                if (OUT != OUT_SIMPLE_M || pt2 == INF64 || pt2 <= guess) break;
+                const unsigned long long seen = guess;
+                guess = sadd64(pt2, 4 * (pt2 - pm));
+                na = 0;
+#pragma unroll
+                for (uint32_t j = 0; j < kMaxJ; ++j)
+                    if (j < nj) {
+                        const unsigned long long o = go[j * 64 + lane];
+                        list(j, o > seen && o <= guess && o != INF64);
+                    }
+            }
+            if (pm == INF64) return k;  // nothing is queued
+            if (k > n) {  // every phase settles the queue minimum
+                if (tid == 0) atomicOr(a.error, 2u);
+                return INF32;
+            }
+            minD = pm;
+            T = pt2;
+            guess = sadd64(T, 4 * (T - minD));
+        }
         const unsigned long long tag = bar_tag(nb);
         unsigned long long *bar_a = a.bar + (nb & 1) * bstride, *bar_b = bar_a + 2 * bstride;
+        // counts of shared records: with SIMPLE criteria a barrier lies between two phases' words, and
+        // the number of barriers per phase varies
+        const unsigned long long tag_b = SIMPLE ? (unsigned long long)(k % 15u + 1u) << 60 : tag;
+        if (SIMPLE) bar_b = a.bar + 2 * bstride;
         ++nb;
         // 1. the wavefront's active groups
-        const uint8_t pt = (uint8_t)phase_tag(k);
         uint32_t na = 0;  // wavefront-uniform
         {
             uint8_t m[kMaxJ];
 #pragma unroll
             for (uint32_t j = 0; j < kMaxJ; ++j) {
                 m[j] = 0;
-                if (j < nj) m[j] = __hip_atomic_load(mk + par * mall + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!SIMPLE && j < nj) m[j] = __hip_atomic_load(mk + par * mall + j * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
 #pragma unroll
             for (uint32_t j = 0; j < kMaxJ; ++j) {
                 if (j >= nj) break;  // block-uniform
                 const uint32_t s = j * 64 + lane;
                 const unsigned long long d = gd[s];
-                const bool act = m[j] == pt || (IN != IN_NONE && gk[s] <= minD) || (OUT && d != INF64 && d <= T) ||
+                const bool act = (!SIMPLE && m[j] == pt) || (IN != IN_NONE && gk[s] <= minD) || (OUT && d != INF64 && d <= T) ||
                                  (DELTA && (kind == 0 ? d < hi : kind == 2 && rset[s] != 0));
                 const unsigned long long mask = __ballot(act);
                 if (act) lst[na + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)s;
@@ -303,18 +585,20 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
         struct Cand {
             uint32_t s, v, r0, r1;
             unsigned long long d, x;
-            uint2 mm;
+            uint2 mm, hi, ho;  // static minima, heads
         };
         auto load = [&](uint32_t i0) {
-            Cand c{INF32, 0u, 0u, 0u, INF64, INF64, make_uint2(INF32, INF32)};
+            Cand c{INF32, 0u, 0u, 0u, INF64, INF64, make_uint2(INF32, INF32), make_uint2(INF32, INF32), make_uint2(INF32, INF32)};
             const uint32_t i = i0 + lane / K;
             if (i < na) {
                 c.s = lst[i];
                 c.v = first_vertex(c.s) + li;
                 if (c.v < n) {
                     c.d = a.dist[c.v];
-                    c.x = ld64(&a.box[2ull * c.v + par]);
-                    c.mm = a.vmin[c.v];
+                    if (!SIMPLE) c.x = ld64(&a.box[2ull * c.v + par]);
+                    if (IN != IN_SIMPLE_M || OUT == OUT_STATIC_M) c.mm = a.vmin[c.v];
+                    if (IN == IN_SIMPLE_M) c.hi = a.in_head[c.v];
+                    if (OUT == OUT_SIMPLE_M) c.ho = a.out_head[c.v];
                     c.r0 = a.rp[c.v];
                     c.r1 = a.rp[c.v + 1];
                 }
@@ -333,13 +617,14 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             }
             const bool removed = DELTA && c.s != INF32 && ((uint32_t)rset[c.s] >> li & 1u);
             const bool q = c.d != INF64 && !((uint32_t)sset[c.s] >> li & 1u);  // d is INF64 without a group
-            const unsigned long long mi = min_in_test(c.mm.x);
+            const unsigned long long mi = in_term(c.mm, c.hi);
             const unsigned long long key = IN == IN_DIJK ? c.d : c.d > mi ? c.d - mi : 0ull;  // d - minIn
             bool ok = false;
             if (IN != IN_NONE) ok = key <= minD;  // eq. crit:instatic
             if (OUT) ok = ok || c.d <= T;         // eq. crit:outstatic
             if (DELTA) ok = kind == 2 ? removed : c.d < hi && (kind == 0 || lowered);
             ok = ok && q;
+            if (SIMPLE && ok) st_agent(&a.box[2ull * c.v], c.d | kSettledBit);
             const uint32_t deg = c.r1 - c.r0;
             bool wait = false;
             const unsigned long long okm = __ballot(ok);
@@ -374,7 +659,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             const unsigned long long rk = IN != IN_NONE ? row_min_rel<K>(keep ? key : INF64, minD) : INF64;
             const unsigned long long rd = row_min_rel<K>(keep ? c.d : INF64, minD);
             const unsigned long long ro =
-                OUT ? row_min_rel<K>(keep ? sadd64(c.d, min_out64(c.mm.y, a.wmax, a.rp, c.v)) : INF64, minD) : INF64;
+                OUT ? row_min_rel<K>(keep ? sadd64(c.d, out_term(c.mm, c.ho, c.v)) : INF64, minD) : INF64;
             const unsigned long long wm = __ballot(wait);
             waiting = waiting || wm != 0;
             if (c.s != INF32 && li == 0) {
@@ -393,7 +678,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             if (waiting && lane == 0) s_pend = 1;
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's records are written
             __syncthreads();
-            if (tid == 0) st_agent(&bar_b[wg * kSlotStride], tag | umin32(s_nsh, s_shlim));
+            if (tid == 0) st_agent(&bar_b[wg * kSlotStride], tag_b | umin32(s_nsh, s_shlim));
         }
         wave_fence();
         uint32_t nseg = umin32(s_wn[lw], s_wl[lw]);
@@ -405,15 +690,30 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
         const uint8_t nt = (uint8_t)phase_tag(k + 1);
         auto apply = [&](uint2 ed, uint32_t em, unsigned long long cur, unsigned long long d) {
             const unsigned long long cand = d + ed.y;
+            if constexpr (SIMPLE) {  // em: the target's IN term, which the settling of this edge's source may raise
+                if (dist_settled(cur)) return;
+                if (cand < cur)
+                    (void)__hip_atomic_fetch_min(&a.box[2ull * ed.x], cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (cand < cur || (IN == IN_SIMPLE_M && ed.y == em)) st_agent(a.mark + mark_of(a, ed.x / K), nt);
+                return;
+            }
             if (cand >= cur) return;
             (void)__hip_atomic_fetch_min(&a.box[2ull * ed.x + (par ^ 1)], cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             st_agent(a.mark + (par ^ 1) * mall + mark_of(a, ed.x / K), nt);
             if (!DELTA || kind == 2 || cand < hi) fm = umin64(fm, cand);
             if (OUT) ft = umin64(ft, sadd64(cand, min_out64(em, a.wmax, a.rp, ed.x)));
         };
+        constexpr unsigned long long none = SIMPLE ? kSettledBit : 0ull;  // the target word of a lane without an edge
         // Delta-stepping: light rounds take edges below the width, the heavy round the others
         auto takes = [&](uint32_t w) { return !DELTA || (w < a.delta) == (kind != 2); };
-        auto target = [&](uint32_t v) { return umin64(ld64(&a.box[2ull * v]), ld64(&a.box[2ull * v + 1])); };
+        auto target = [&](uint32_t v) {
+            if (SIMPLE) return ld64(&a.box[2ull * v]);
+            return umin64(ld64(&a.box[2ull * v]), ld64(&a.box[2ull * v + 1]));
+        };
+        auto extra = [&](uint64_t e, uint32_t v) {  // of an edge: what apply takes as em
+            if (IN == IN_SIMPLE_M) return (uint32_t)ld64(&a.box[2ull * v + 1]);
+            return OUT && !SIMPLE ? a.emin[e] : INF32;
+        };
         // relaxes edges [e, e + len) at distance d by the wavefront
         auto relax_range = [&](uint32_t e, uint32_t len, unsigned long long d) {
             for (uint64_t j0 = lane; j0 < len; j0 += 256) {
@@ -426,26 +726,32 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
                     hm[j] = INF32;
                     if (j0 + j * 64 < len) {
                         he[j] = a.edges[e + j0 + j * 64];
-                        if (OUT) hm[j] = a.emin[e + j0 + j * 64];
+                        if (!SIMPLE) hm[j] = extra(e + j0 + j * 64, 0u);
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) hc[j] = j0 + j * 64 < len && takes(he[j].y) ? target(he[j].x) : 0ull;
+                for (int j = 0; j < 4; ++j) {
+                    hc[j] = none;
+                    if (j0 + j * 64 < len && takes(he[j].y)) {
+                        hc[j] = target(he[j].x);
+                        if (SIMPLE) hm[j] = extra(0, he[j].x);
+                    }
+                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) apply(he[j], hm[j], hc[j], d);
             }
         };
         uint2 ed = make_uint2(0u, 0u);
         uint32_t em = INF32;
-        unsigned long long cur = 0, sd = 0;
+        unsigned long long cur = none, sd = 0;
         auto fetch = [&](uint32_t i) {  // lane l of a row of 16: edge l of segment i
-            cur = 0;
+            cur = none;
             if (i < nseg) {
                 const Seg sg = seg[i];
                 const uint32_t l = lane & (kSegEdges - 1);
                 if (l < sg.len) {
                     ed = a.edges[sg.e + l];
-                    if (OUT) em = a.emin[sg.e + l];
+                    em = extra(sg.e + l, ed.x);
                     sd = sg.d;
                     if (takes(ed.y)) cur = target(ed.x);
                 }
@@ -464,7 +770,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
         // the workgroup's minima over what it keeps
 #pragma unroll
         for (uint32_t j = 0; j < kMaxJ; ++j)
-            if (j < nj && (!DELTA || kind == 2)) {
+            if (!SIMPLE && j < nj && (!DELTA || kind == 2)) {
                 fm = umin64(fm, gd[j * 64 + lane]);
                 if (OUT) ft = umin64(ft, go[j * 64 + lane]);
             }
@@ -517,9 +823,9 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             if (tid < W) {
                 uint32_t spins = 0;
                 unsigned long long v;
-                while (((v = ld64(&bar_b[tid * kSlotStride])) & kTag) != tag && ++spins < kResSpin) {}
+                while (((v = ld64(&bar_b[tid * kSlotStride])) & kTag) != tag_b && ++spins < kResSpin) {}
                 s_sh[tid] = (uint32_t)v;
-                if ((v & kTag) != tag) atomicOr(&s_flags, 1u);
+                if ((v & kTag) != tag_b) atomicOr(&s_flags, 1u);
                 else if (v & kVal) atomicOr(&s_flags, 2u);
             }
             __syncthreads();
@@ -631,6 +937,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             pt2 = umin64(pt2, s_all[kResMaxW / 64 + i]);
         }
         pm = readlane64(pm, 0);
+        if (SIMPLE) continue;  // the next phase's refresh finds minD and T
         if (!DELTA) {
             minD = pm;
             if (OUT) T = readlane64(pt2, 0);
@@ -651,7 +958,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
     return 0;  // not reached: the first phase settles the source
 }
 
-template <int BS, int K, int IN, bool OUT, bool DELTA = false>
+template <int BS, int K, int IN, int OUT, bool DELTA = false>
 __global__ __launch_bounds__(BS) void k_resident(ResArgs a, ResCtl *ctl, uint32_t one_xcd) {
     __shared__ uint32_t s_wg;
     // the workgroup's rank in the team
@@ -687,7 +994,19 @@ static rfn pick_res_bs(int in, bool out) {
     return k_resident<BS, K, IN_NONE, true>;
 }
 
-static rfn pick_res(int bs, int lgK, int in, bool out, bool delta) {
+template <int BS, int K>
+static rfn pick_res_simple(int in, int out) {
+    if (in == IN_NONE) return k_resident<BS, K, IN_NONE, OUT_SIMPLE_M>;
+    if (in == IN_STATIC_M) return k_resident<BS, K, IN_STATIC_M, OUT_SIMPLE_M>;
+    if (out == OUT_NONE) return k_resident<BS, K, IN_SIMPLE_M, OUT_NONE>;
+    return out == OUT_STATIC_M ? k_resident<BS, K, IN_SIMPLE_M, OUT_STATIC_M> : k_resident<BS, K, IN_SIMPLE_M, OUT_SIMPLE_M>;
+}
+
+static rfn pick_res(int bs, int lgK, int in, int out, bool delta) {
+    if (in == IN_SIMPLE_M || out == OUT_SIMPLE_M) {
+        if (bs == 512) return lgK == 3 ? pick_res_simple<512, 8>(in, out) : pick_res_simple<512, 16>(in, out);
+        return lgK == 3 ? pick_res_simple<1024, 8>(in, out) : pick_res_simple<1024, 16>(in, out);
+    }
     if (delta) {
         if (bs == 512) return lgK == 3 ? k_resident<512, 8, IN_NONE, false, true> : k_resident<512, 16, IN_NONE, false, true>;
         return lgK == 3 ? k_resident<1024, 8, IN_NONE, false, true> : k_resident<1024, 16, IN_NONE, false, true>;
@@ -730,7 +1049,7 @@ ResShape resident_shape(const sssp_graph *g) {
 // Runs a resident solve (delta > 0: Delta-stepping) with `scratch` (r.bytes, 256-byte aligned).
 // *ran = false: the device cannot hold the workgroups at once, or one waited too long for another
 // (the device is shared with other work); the distances are unfinished.
-int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, bool out_static, uint64_t delta,
+int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran) {
     ResArgs a;
     a.rp = g->rp;
@@ -756,9 +1075,18 @@ int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32
     a.wslots = r.slots >> a.lgWv;
     a.mstride = r.slots;
     a.delta = delta;
-    const uint64_t ib = ((uint64_t)g->n + 255) / 256;
-    hipLaunchKernelGGL(k_res_init, dim3((uint32_t)(ib > 2048 ? 2048 : ib < 64 ? 64 : ib)), dim3(256), 0, s, a, ctl);
-    rfn k = pick_res(r.bs, r.lgK, in, out_static, delta != 0);
+    a.ip = g->ip;
+    a.in_edges = g->in_edges;
+    a.in_head = g->b.in_head;
+    a.out_head = g->b.out_head;
+    a.in_cur = g->b.in_cur;
+    a.out_cur = g->b.out_cur;
+    const uint64_t nb = ((uint64_t)g->n + 255) / 256;
+    const dim3 ib((uint32_t)(nb > 2048 ? 2048 : nb < 64 ? 64 : nb));
+    if (in == IN_SIMPLE_M || out == OUT_SIMPLE_M)
+        hipLaunchKernelGGL(k_res_init_simple, ib, dim3(256), 0, s, a, ctl, (int)(in == IN_SIMPLE_M));
+    else hipLaunchKernelGGL(k_res_init, ib, dim3(256), 0, s, a, ctl);
+    rfn k = pick_res(r.bs, r.lgK, in, out, delta != 0);
     const size_t lds = res_lds(r.slots, r.bs);
     if (lds > 65536) HIP_OK(hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     uint32_t one_xcd = r.one_xcd;
