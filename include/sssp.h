@@ -470,6 +470,8 @@ int sssp_solve_schedule(sssp_graph *g, uint32_t source, uint32_t crit_first, uin
  *   features_out HOST, may be NULL: row j (12 floats) = checkpoint j's features,
  *                for j < min(checkpoints, trace_cap); needs trace_cap > 0.
  * Other arguments as sssp_solve_ex; trace records carry each phase's criterion.
+ * Without phase_of, trace and features_out the static phases run resident (see `single` in
+ * sssp_launch_cfg); improving, which depends on the order of relaxations, may then differ.
  */
 int sssp_solve_learned_checkpoint(sssp_graph *g, uint32_t source, const sssp_selector *sel, uint64_t *dist_out,
                                   sssp_stats *stats, uint32_t *phase_of, sssp_phase_rec *trace, uint32_t trace_cap,

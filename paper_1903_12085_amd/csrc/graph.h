@@ -77,6 +77,16 @@ struct ResShape {
 ResShape resident_shape(const sssp_graph *g);
 int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran);
+// What the static stage of a learned checkpoint solve leaves: counts, and minD and the OUT-STATIC
+// threshold of the phase after it (INF64: the solve is finished).
+struct ResLearned {
+    unsigned long long min_d, t, reached, settled, sum_f, m_reach, improving, relax_edges;
+    uint32_t phases, choice;
+};
+uint64_t resident_learn_bytes(const sssp_graph *g, const ResShape &r);
+int resident_learn(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, const float *mlp_w, double wm,
+                   uint64_t *dist_out, void *scratch, ResLearned *out, bool *ran);
+int resident_learn_state(const sssp_graph *g, const ResShape &r, hipStream_t s, uint64_t *dist_out, void *scratch);
 bool resident_batch_takes(const sssp_graph *g);
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
                    bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran);

@@ -155,6 +155,23 @@ __global__ void k_init_ctl(Ctl *ctl, const uint2 *__restrict__ vmin, const uint3
     }
 }
 
+// After k_init_ctl: the control block after the static stage of a learned checkpoint solve.
+__global__ void k_resume_ctl(Ctl *ctl, ResLearned r) {
+    CtlHead &h = ctl->h;
+    h.settled = r.settled;
+    h.sum_f = r.sum_f;
+    h.m_reach = r.m_reach;
+    h.phases = r.phases;
+    h.pnum[0] = h.pnum[1] = r.phases;
+    h.done = r.min_d == INF64;
+    ctl->reached.v[0] = r.reached;
+    ctl->relax_edges.v[0] = r.relax_edges;
+    ctl->improving.v[0] = r.improving;
+    ctl->minD[0].v[0] = ctl->tst[0].v[0] = INF64;
+    ctl->minD[r.phases % 3].v[0] = r.min_d;
+    ctl->tst[r.phases % 3].v[0] = r.t;
+}
+
 // Learned mode: the degree sum of the queued set starts with the source, and
 // the first phase's (or bucket's) choice comes from the features of {s}.
 // One wavefront.
@@ -3052,13 +3069,29 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
         a.b.trace_cf = (uint32_t *)cf_buf.p;
     }
     const int ib = (int)(((uint64_t)g->n + 255) / 256 > 8192 ? 8192 : ((uint64_t)g->n + 255) / 256);
-    hipLaunchKernelGGL(k_init_state, dim3(ib), dim3(256), 0, s, g->n, source, a.b.dist, a.b.st, a.b.phase_of,
-                       dyn ? a.b.out_cur : nullptr, g->rp, (in_all >= IN_SIMPLE_M) ? a.b.in_cur : nullptr,
-                       g->ip, delta_mode ? a.b.stamp : nullptr, a.b.out_head, g->edges, a.b.in_head, g->in_edges);
+    // learned checkpoint solves: the static stage resident, unless the caller wants what only the
+    // phase kernels record
+    bool staged = false;
+    ResLearned stage{};
+    const ResShape rs = resident_shape(g);
+    if (ckpt && rs.fits && !trace_cap && !phase_of && g->cfg.single != kPhaseKernels) {
+        rc = resident_scratch(g, resident_learn_bytes(g, rs));
+        if (rc == SSSP_OK) rc = resident_learn(g, rs, s, source, a.mlp_w, a.wm, dist_out, g->res, &stage, &staged);
+        if (rc) return rc;
+    }
+    if (!staged)
+        hipLaunchKernelGGL(k_init_state, dim3(ib), dim3(256), 0, s, g->n, source, a.b.dist, a.b.st, a.b.phase_of,
+                           dyn ? a.b.out_cur : nullptr, g->rp, (in_all >= IN_SIMPLE_M) ? a.b.in_cur : nullptr,
+                           g->ip, delta_mode ? a.b.stamp : nullptr, a.b.out_head, g->edges, a.b.in_head, g->in_edges);
     // keyed queue arrays: the first split lies a sixteenth of the mean weight above T (or minD)
     const unsigned long long qdelta0 = g->m ? (g->sum_w / g->m) / 16 + 1 : 1;
     hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(64), 0, s, a.b.ctl, g->vmin, g->rp, g->wmax, source, n_deltas,
                        qdelta0);
+    if (staged) {
+        hipLaunchKernelGGL(k_resume_ctl, dim3(1), dim3(1), 0, s, a.b.ctl, stage);
+        if (stage.min_d != INF64) rc = resident_learn_state(g, rs, s, dist_out, g->res);
+        if (rc) return rc;
+    }
     if (learn) hipLaunchKernelGGL(k_init_choice, dim3(1), dim3(64), 0, s, a, source, (int)delta_mode);
     if (apx) hipLaunchKernelGGL(k_fill_u32, dim3(ib), dim3(256), 0, s, g->n, a.b.apx_lin, a.b.apx_lout, 0u);
     const PhaseKernels K = oracle ? pick_oracle(g->cfg.chunk)
@@ -3121,7 +3154,11 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
         CtlHead h{};
         uint64_t k_next = 0;
         unsigned int choice = 0;
-        if (sw->mode == 1) {
+        if (staged) {
+            h.done = stage.min_d == INF64;
+            k_next = stage.phases;
+            choice = stage.choice;
+        } else if (sw->mode == 1) {
             const bool graphs = g->cfg.use_graph;
             g->cfg.use_graph = false;
             rc = sw->at ? run_loop(g, a, K, max_phases, 0, sw->at, &h) : SSSP_OK;
