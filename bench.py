@@ -157,8 +157,9 @@ def solve_frac(st, ms, n):
 
 
 def measure_plain(B, torch, dg, src, crit, steps, warmup, record):
-    """Timed plain solves (steps after warmup) and the dominant kernel's roofline from a separate
-    HIP-event pass over the same solve."""
+    """Timed plain solves (steps after warmup; resident unless the launch shape says otherwise) and, from
+    a separate HIP-event pass over the same solve by the phase kernels, the roofline of their dominant
+    kernel."""
     dist = B.new_dist(dg.n)
     for _ in range(warmup):
         B.solve(dg, src, crit, dist)
@@ -188,7 +189,8 @@ def measure_plain(B, torch, dg, src, crit, steps, warmup, record):
                 "kernel": kname,
                 "alg_bytes_per_launch": round(per_launch), "avg_launch_us": round(avg_us, 2),
                 "launches": prof["phases"], "identify_ms": round(prof["identify_ms"], 3),
-                "relax_ms": round(prof["relax_ms"], 3)}
+                "relax_ms": round(prof["relax_ms"], 3),
+                "timed_solver": {0: "resident", 1: "one workgroup"}.get(dg.launch()["single"], "phase kernels")}
     return ms, phases, st, roofline, prof, dist
 
 
@@ -298,7 +300,7 @@ def bench_switched(B, torch, dg, src, m_reach, plain_ms, ref):
 def bench_c1(B, torch, G):
     """The small random graph (n = 16384, out-degree 8, weights [1, 1000], source 0) with
     IN_STATIC|OUT_STATIC: latency-bound (about a hundred short phases), so reported per phase, for
-    the grid-wide kernels and the one-workgroup launch option; median of 11 solves."""
+    the resident solver and the one-workgroup launch option; median of 11 solves."""
     g = G.config_small(seed=1)
     dg = B.DeviceGraph.from_graph(g)
     dist = B.new_dist(g.n)
