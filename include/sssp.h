@@ -112,7 +112,7 @@ typedef struct {
 int sssp_graph_create(uint32_t n, uint64_t m, const uint64_t *row_ptr, const uint32_t *col,
                       const uint32_t *weight, int device_ptrs, void *hip_stream, sssp_graph **out);
 
-/* Release every device buffer the graph owns. One block of 64 to 512 MiB per
+/* Release every device buffer the graph owns. One block of 64 MiB to 2 GiB per
  * device, the graph's edges, is kept for the next graph that it fits; it is
  * given back when an allocation of the library fails, and by a call with NULL. */
 int sssp_graph_destroy(sssp_graph *g);

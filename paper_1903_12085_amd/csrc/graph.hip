@@ -249,8 +249,9 @@ static int radix_sort(unsigned long long *&k0, unsigned long long *&k1, uint32_t
 // 64 MiB takes 0.33 to 8 ms (smaller ones 12 us: the runtime keeps those itself), as much as the rest
 // of a creation or more. At most kKeepMax bytes; given back when an allocation fails, and by
 // sssp_graph_destroy(NULL). Every call on a graph has finished its device work when it returns, so a
-// block is idle here.
-constexpr uint64_t kKeepMin = 64ull << 20, kKeepMax = 512ull << 20;
+// block is idle here. 2 GiB hold a graph of 2^27 edges, and are 0.7 % of the memory; with 512 MiB the
+// creation and release of one of 2^26 edges took 4 or 33 ms, by the process, now 1.8.
+constexpr uint64_t kKeepMin = 64ull << 20, kKeepMax = 2ull << 30;
 constexpr int kKeepDevices = 64;
 static std::mutex g_keep_mu;
 static struct { void *p; uint64_t bytes; } g_keep[kKeepDevices];
