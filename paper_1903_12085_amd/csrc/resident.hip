@@ -71,11 +71,10 @@
 #include "common.h"
 #include "graph.h"
 #include "selector.h"
+#include "words.h"
 
 constexpr uint32_t kSegEdges = 16;     // edges per segment = lanes per row in relax
-constexpr uint32_t kResMaxW = 256;
 constexpr uint32_t kMaxJ = 4;          // slots per thread
-constexpr uint32_t kSlotStride = 8;    // u64 between two workgroups' barrier words (64 bytes)
 constexpr uint32_t kWaveSegs = 64;     // segments a wavefront holds in LDS; further settled vertices stay pending
 constexpr uint32_t kHubEdges = 1024;   // longer rows are cut by the whole wavefront
 constexpr uint32_t kShareEdges = 256;  // edges of a shared record (more for a hub past kShareCap / 2 records)
@@ -83,9 +82,6 @@ constexpr uint32_t kShareCap = 1024;   // shared records per workgroup and phase
 constexpr uint32_t kShareDeg = 128;    // graphs with a longer row share records (see `share` in ResArgs)
 constexpr uint32_t kQuota = 64;        // segments a list takes in a phase before further rows are shared
 constexpr uint32_t kResSpin = 1u << 21;
-// Barrier word: tag (4 bits) and value (all ones: infinity; distances and thresholds stay below
-// 2^58 + 2^32).
-constexpr unsigned long long kVal = (1ull << 60) - 1, kTag = ~kVal;
 
 // Learned checkpoint solves.
 struct ResLearn {
@@ -95,7 +91,7 @@ struct ResLearn {
 };
 
 struct ResCtl {
-    unsigned long long bar[4 * kResMaxW * kSlotStride];  // see ResArgs::bar
+    unsigned long long bar[team_words(kResMaxW)];     // see words.h
     unsigned int rank[16 * 32];                       // arrivals per XCD
     unsigned int error;
     unsigned int phases;
@@ -112,9 +108,7 @@ struct ResArgs {
     unsigned long long *box;   // per vertex, by phase parity: the lowest candidate relaxes delivered
     uint8_t *mark;       // by phase parity, W rows of mstride bytes: the phase tag each slot was last marked for
     unsigned long long *rec;    // W rows of kShareCap records (first edge and count, distance)
-    // barrier words, by barrier parity, a slot per workgroup: tagged minD and tagged threshold;
-    // then likewise the tagged counts of shared records
-    unsigned long long *bar;
+    unsigned long long *bar;    // the team's words (words.h)
     unsigned int *error;
     uint32_t n, src, wmax;
     uint32_t W, lgW;     // workgroups
@@ -186,7 +180,6 @@ __device__ __forceinline__ unsigned long long wave_min_rel(unsigned long long x,
 // a / b rounded up, for any a (a row may hold nearly 2^32 edges)
 __device__ __forceinline__ uint32_t ceil_div(uint32_t a, uint32_t b) { return a / b + (a % b != 0); }
 __device__ __forceinline__ uint32_t phase_tag(uint32_t k) { return k % 255u + 1u; }
-__device__ __forceinline__ unsigned long long bar_tag(uint32_t b) { return (unsigned long long)((b >> 1) % 15u + 1u) << 60; }
 
 // Group g belongs to workgroup g mod W, there to wavefront (g / W) mod (wavefronts), as that
 // wavefront's slot: neighbouring groups are spread over workgroups first, then over wavefronts.
@@ -310,7 +303,6 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t li = lane & (K - 1);        // the lane's vertex in its row's group
     const uint32_t W = a.W, NS = a.mstride, n = a.n, nj = a.wslots / 64, ws0 = wave * a.wslots;
-    const uint32_t bstride = W * kSlotStride;
     // segments: each wavefront cuts and relaxes its own; with `share`, all go to one list whose
     // segments the workgroup's rows take in turn
     const uint32_t lw = a.share ? 0u : wave, rows = a.share ? BS / kSegEdges : 64 / kSegEdges;
@@ -639,7 +631,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
                         fm = umin64(fm, gd[j * 64 + lane]);
                         if (OUT) ft = umin64(ft, go[j * 64 + lane]);
                     }
-                if (!meet(bar_tag(nb), a.bar + (nb & 1) * bstride, fm, ft, pm, pt2)) return INF32;
+                if (!meet(bar_tag(nb), a.bar + bar_words(nb, W), fm, ft, pm, pt2)) return INF32;
                 ++nb;
                 // sums up to the guess are exact, larger ones lower bounds
                 if (OUT != OUT_SIMPLE_M || pt2 == INF64 || pt2 <= guess) break;
@@ -663,11 +655,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             guess = sadd64(T, 4 * (T - minD));
         }
         const unsigned long long tag = bar_tag(nb);
-        unsigned long long *bar_a = a.bar + (nb & 1) * bstride, *bar_b = bar_a + 2 * bstride;
-        // counts of shared records: with SIMPLE criteria a barrier lies between two phases' words, and
-        // the number of barriers per phase varies
-        const unsigned long long tag_b = SIMPLE ? (unsigned long long)(k % 15u + 1u) << 60 : tag;
-        if (SIMPLE) bar_b = a.bar + 2 * bstride;
+        unsigned long long *bar_a = a.bar + bar_words(nb, W), *bar_b = a.bar + count_words(W);
         ++nb;
         // 1. the wavefront's active groups
         uint32_t na = 0;  // wavefront-uniform
@@ -815,7 +803,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             if (waiting && lane == 0) s_pend = 1;
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's records are written
             __syncthreads();
-            if (tid == 0) st_agent(&bar_b[wg * kSlotStride], tag_b | umin32(s_nsh, s_shlim));
+            if (tid == 0) st_agent(&bar_b[wg * kSlotStride], count_word(nb, umin32(s_nsh, s_shlim)));
         }
         wave_fence();
         uint32_t nseg = umin32(s_wn[lw], s_wl[lw]);
@@ -962,10 +950,10 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             if (tid < W) {
                 uint32_t spins = 0;
                 unsigned long long v;
-                while (((v = ld64(&bar_b[tid * kSlotStride])) & kTag) != tag_b && ++spins < kResSpin) {}
+                while (!count_is_for(v = ld64(&bar_b[tid * kSlotStride]), nb) && ++spins < kResSpin) {}
                 s_sh[tid] = (uint32_t)v;
-                if ((v & kTag) != tag_b) atomicOr(&s_flags, 1u);
-                else if (v & kVal) atomicOr(&s_flags, 2u);
+                if (!count_is_for(v, nb)) atomicOr(&s_flags, 1u);
+                else if ((uint32_t)v) atomicOr(&s_flags, 2u);
             }
             __syncthreads();
             uint32_t pending = s_pend;
@@ -1418,7 +1406,7 @@ constexpr uint32_t kGangLog = 5, kGang = 1u << kGangLog;
 constexpr int kBatchBs = 512;                    // threads: two workgroups per CU
 constexpr uint32_t kBatchNj = 4;                 // slots per thread of a batch workgroup at most
 constexpr uint32_t kWgVertices = 8u * kBatchBs * kBatchNj;  // vertices per workgroup at most
-constexpr uint32_t kTeamBar = 4 * kGang * kSlotStride + kSlotStride;  // u64 of a team: barrier words, query word
+constexpr uint32_t kTeamBar = team_words(kGang) + kSlotStride;  // u64 of a team: its words, query word
 
 struct ResQuery {
     const uint32_t *rp;
@@ -1463,7 +1451,7 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
         const uint32_t W = 1u << cls, wg = member & (W - 1), m0 = member - wg;
         const uint64_t g0 = (uint64_t)gang * kGang + m0;  // the team's first workgroup
         unsigned long long *bar = b.bar + ((uint64_t)gang * 2 * kGang + (kGang >> cls) + (member >> cls)) * kTeamBar;
-        unsigned long long *qword = bar + 4 * kGang * kSlotStride;
+        unsigned long long *qword = bar + team_words(kGang);
         uint32_t nb = 0;
         for (uint32_t turn = 1;; ++turn) {
             // the team's first workgroup takes the next query and tells the others
@@ -1535,7 +1523,7 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (W > 1) {  // the team's set-up is done
-                unsigned long long *words = bar + (nb & 1) * W * kSlotStride;
+                unsigned long long *words = bar + bar_words(nb, W);
                 const unsigned long long tag = bar_tag(nb);
                 ++nb;
                 if (tid == 0) st_agent(&words[wg * kSlotStride], tag | kVal);
