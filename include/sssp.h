@@ -175,10 +175,14 @@ int sssp_delta_step_ex(sssp_graph *g, uint32_t source, const uint64_t *deltas, u
  * Runs on graphs[0]'s stream. In the default form each query of at most 2^19
  * vertices runs on a team of 1 to 32 workgroups (more for larger graphs, and
  * when there are few queries), all of them in one cooperative launch; a larger
- * graph, or a query alone, is solved on the whole device as by sssp_solve.
+ * graph, or a query alone, is solved on the whole device as by sssp_solve, one
+ * after the other. Many large graphs, large graphs of many phases (grids) from
+ * three on, and graphs of more than 2^24 vertices run with the whole batch as
+ * with a launch shape given (see sssp_batch_cfg).
  * Device scratch: about 16 bytes per vertex that the workgroups hold (at most
- * 16384 each, 150 MB in all), kept on graphs[0]; with a launch shape given about
- * 29 bytes per vertex of each query, freed before returning. Errors: SSSP_ERR_INVALID for nq = 0, a NULL pointer, a bad source
+ * 16384 each, 150 MB in all) or of the largest graph, kept on graphs[0]; with a
+ * launch shape given about 29 bytes per vertex of each query, freed before
+ * returning. Errors: SSSP_ERR_INVALID for nq = 0, a NULL pointer, a bad source
  * or criterion; SSSP_ERR_UNSUPPORTED for the dynamic criteria; SSSP_ERR_OOM
  * when the scratch does not fit.
  */

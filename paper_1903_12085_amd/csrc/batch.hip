@@ -20,6 +20,7 @@
 // Criteria: DIJK, IN-STATIC, OUT-STATIC and their disjunctions (the static
 // criteria need no per-phase term pass).
 #include <algorithm>
+#include <math.h>
 #include <string.h>
 #include <vector>
 
@@ -721,49 +722,9 @@ extern "C" int sssp_batch_get_config(sssp_batch_cfg *cfg) {
     return SSSP_OK;
 }
 
-extern "C" int sssp_solve_batch(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq,
-                                uint32_t criterion, uint64_t *const *dist_outs, uint32_t *phases_out) {
-    return sssp_solve_batch_ex(graphs, sources, nq, criterion, dist_outs, phases_out, nullptr);
-}
-
-extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq,
-                                   uint32_t criterion, uint64_t *const *dist_outs, uint32_t *phases_out,
-                                   const sssp_batch_cfg *cfg_in) {
-    const sssp_batch_cfg cfg = cfg_in ? *cfg_in : g_batch_cfg;
-    if (cfg.block != 0 && cfg.block != 256 && cfg.block != 512 && cfg.block != 1024)
-        return sssp_set_error(SSSP_ERR_INVALID, "block size must be 256, 512 or 1024");
-    if (nq == 0 || !graphs || !sources || !dist_outs)
-        return sssp_set_error(SSSP_ERR_INVALID, "empty batch or NULL array");
-    if (criterion == 0 || (criterion & ~SSSP_CRIT_ALL))
-        return sssp_set_error(SSSP_ERR_INVALID, "criterion 0x%x is empty or has unknown bits", criterion);
-    int in = IN_NONE, out = OUT_NONE;
-    crit_modes(criterion, &in, &out);
-    if (in > IN_STATIC_M || out > OUT_STATIC_M)
-        return sssp_set_error(SSSP_ERR_UNSUPPORTED, "the batched solver evaluates DIJK, IN-STATIC and OUT-STATIC");
-    if ((!cfg.block || cfg.block == 512) && !cfg.split && !cfg.blocks && !cfg.team_edges && !cfg.team_size) {
-        // the default form: resident teams (resident.hip), a graph too large for one, or a query
-        // alone, on the whole device; what neither takes is left to the launch below
-        for (uint32_t i = 0; i < nq; ++i) {
-            if (!graphs[i] || !dist_outs[i]) return sssp_set_error(SSSP_ERR_INVALID, "query %u: NULL graph or output", i);
-            if (sources[i] >= graphs[i]->n) return sssp_set_error(SSSP_ERR_INVALID, "query %u: source %u >= n", i, sources[i]);
-        }
-        HIP_OK(hipSetDevice(graphs[0]->device));
-        std::vector<uint32_t> ids, rest;
-        for (uint32_t i = 0; i < nq; ++i) (nq > 1 && resident_batch_takes(graphs[i]) ? ids : rest).push_back(i);
-        bool ran = true;
-        if (!ids.empty()) {
-            const int rc = resident_batch(graphs, sources, ids.data(), (uint32_t)ids.size(), in, out == OUT_STATIC_M,
-                                          dist_outs, phases_out, &ran);
-            if (rc) return rc;
-        }
-        for (size_t j = 0; ran && j < rest.size(); ++j) {
-            const uint32_t i = rest[j];
-            const int rc = resident_try(graphs[i], graphs[0]->stream, sources[i], in, out == OUT_STATIC_M, 0, dist_outs[i],
-                                        phases_out ? phases_out + i : nullptr, &ran);
-            if (rc) return rc;
-        }
-        if (ran) return SSSP_OK;
-    }
+// The queries by one launch of persistent workgroups and teams, in the given shape, on g0's stream.
+static int batch_launch(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq, int in, bool out_static,
+                        uint64_t *const *dist_outs, uint32_t *phases_out, const sssp_batch_cfg &cfg, const sssp_graph *g0) {
     std::vector<BatchQuery> hq(nq);
     std::vector<uint64_t> st_off(nq), fl_off(nq), fm_off(nq);
     uint64_t st_total = 0, fl_total = 0, fm_total = 0;
@@ -798,8 +759,8 @@ extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *so
         return sssp_set_error(SSSP_ERR_INVALID, "team size must be 2 .. 64 (0: automatic)");
     std::vector<uint32_t> large, small;
     for (uint32_t i : order) (cfg.team_edges != UINT32_MAX && graphs[i]->m >= team_edges ? large : small).push_back(i);
-    hipStream_t s = graphs[0]->stream;
-    HIP_OK(hipSetDevice(graphs[0]->device));
+    hipStream_t s = g0->stream;
+    HIP_OK(hipSetDevice(g0->device));
     uint8_t *st = nullptr;
     uint32_t *fl = nullptr;
     uint2 *fm = nullptr;
@@ -834,7 +795,7 @@ extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *so
         if (!large.empty()) {
             // one cooperative launch: teams of W workgroups for the large queries, the other
             // resident workgroups for the rest, all at once
-            tfn tk = pick_team(bs, in, out == OUT_STATIC_M);
+            tfn tk = pick_team(bs, in, out_static);
             int per_cu = 0;
             TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)tk, bs, 0));
             const uint64_t resident = (uint64_t)(per_cu > 0 ? per_cu : 0) * cus;
@@ -870,7 +831,7 @@ extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *so
             TRY(hipMemcpyAsync(dorder, small.data(), nsmall * sizeof(uint32_t), hipMemcpyHostToDevice, s));
             uint32_t grid = cfg.blocks ? cfg.blocks : (uint32_t)cus * (bs >= 1024 ? 2 : 4);
             if (grid > nsmall) grid = nsmall;
-            bfn k = pick_batch(bs, in, out == OUT_STATIC_M);
+            bfn k = pick_batch(bs, in, out_static);
             hipLaunchKernelGGL(k, dim3(grid), dim3(bs), 0, s, dq, dorder, nsmall, dctl, dph, split);
             TRY(hipGetLastError());
         }
@@ -886,4 +847,115 @@ done:
     sssp_free(st); sssp_free(fl); sssp_free(fm); sssp_free(dq); sssp_free(dorder); sssp_free(dph); sssp_free(dctl);
     sssp_free(dlarge); sssp_free(dteams);
     return rc;
+}
+
+// The default form: queries of graphs that a resident team takes run on teams, larger ones and a query
+// alone on the whole device, one after the other. *left: the queries that were not solved.
+//
+// Larger graphs, up to two: each takes the device in turn, which is faster than both at once by the
+// launch above, whatever the graph (two grids of 1 M vertices 104 ms and 222, two paths of 525 k 3.2 s
+// and 3.7, two random graphs of 4 M vertices 14 and 397). Of more, only those with few phases: a grid
+// of 1 M vertices costs 59 ms each, where the launch takes 256 ms for three, 305 for eight and 260 for
+// sixty-four. The number of phases tells them apart: random and R-MAT graphs of 2^19 to 2^23 vertices
+// took at most 0.6 sqrt(n), grids and meshes of up to eight neighbours at least 8 sqrt(n), so that a
+// solve is given up beyond sqrt(n), after 2 % of the launch's time, and the rest of the batch left to
+// the launch. Nor do many graphs of few phases gain, since a phase does not fill the device (530 k
+// vertices, degree 2: 16 queries 38 ms and 54, 32 queries 75 and 36; 1 M vertices, degree 2: 16 queries
+// 52 and 82, 32 queries 105 and 71; R-MAT 21 with 4 edges a vertex: 32 queries 83 and 138, 128 queries
+// 331 and 243), unless they have 2^25 edges (random, 2 M vertices of degree 16: 64 queries 301 and 798;
+// R-MAT 22: 64 queries 348 and 930).
+static int batch_default(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq, int in, bool out_static,
+                         uint64_t *const *dist_outs, uint32_t *phases_out, std::vector<uint32_t> *left) {
+    std::vector<uint32_t> small, large;
+    for (uint32_t i = 0; i < nq; ++i) (nq > 1 && resident_batch_takes(graphs[i]) ? small : large).push_back(i);
+    // shares of what the device takes in turn: 16 graphs under 2^20 vertices, 20 of more
+    constexpr uint64_t kTurns = 80;
+    uint64_t turns = 0, scratch = 0;
+    bool fits = true;
+    for (uint32_t i : large) {
+        const ResShape r = resident_shape(graphs[i]);
+        fits = fits && r.fits;
+        scratch = std::max(scratch, r.bytes);
+        turns += graphs[i]->m >= (1u << 25) ? 0 : graphs[i]->n < (1u << 20) ? 5 : 4;
+    }
+    if (!fits || (large.size() > 2 && turns > kTurns)) {
+        for (uint32_t i = 0; i < nq; ++i) left->push_back(i);
+        return SSSP_OK;
+    }
+    // the likely longest first: the fewer edges a vertex has, the more phases
+    std::stable_sort(large.begin(), large.end(), [&](uint32_t x, uint32_t y) {
+        return graphs[x]->m * (double)graphs[y]->n < graphs[y]->m * (double)graphs[x]->n;
+    });
+    if (!large.empty()) {
+        const int rc = resident_scratch(graphs[0], scratch);
+        if (rc) return rc;
+    }
+    for (size_t j = 0; j < large.size(); ++j) {
+        const uint32_t i = large[j];
+        const uint32_t cap = large.size() > 2 ? (uint32_t)sqrt((double)graphs[i]->n) : 0;
+        uint32_t phases = 0;
+        bool ran = false;
+        const int rc = resident_solve(graphs[i], resident_shape(graphs[i]), graphs[0]->stream, sources[i], in, out_static, 0,
+                                      dist_outs[i], graphs[0]->res, &phases, &ran, cap);
+        if (rc) return rc;
+        if (!ran) {
+            left->assign(large.begin() + j, large.end());
+            left->insert(left->end(), small.begin(), small.end());
+            return SSSP_OK;
+        }
+        if (phases_out) phases_out[i] = phases;
+    }
+    if (small.empty()) return SSSP_OK;
+    bool ran = false;
+    const int rc = resident_batch(graphs, sources, small.data(), (uint32_t)small.size(), in, out_static, dist_outs,
+                                  phases_out, &ran);
+    if (rc == SSSP_OK && !ran) *left = small;
+    return rc;
+}
+
+extern "C" int sssp_solve_batch(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq,
+                                uint32_t criterion, uint64_t *const *dist_outs, uint32_t *phases_out) {
+    return sssp_solve_batch_ex(graphs, sources, nq, criterion, dist_outs, phases_out, nullptr);
+}
+
+extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq,
+                                   uint32_t criterion, uint64_t *const *dist_outs, uint32_t *phases_out,
+                                   const sssp_batch_cfg *cfg_in) {
+    const sssp_batch_cfg cfg = cfg_in ? *cfg_in : g_batch_cfg;
+    if (cfg.block != 0 && cfg.block != 256 && cfg.block != 512 && cfg.block != 1024)
+        return sssp_set_error(SSSP_ERR_INVALID, "block size must be 256, 512 or 1024");
+    if (nq == 0 || !graphs || !sources || !dist_outs)
+        return sssp_set_error(SSSP_ERR_INVALID, "empty batch or NULL array");
+    if (criterion == 0 || (criterion & ~SSSP_CRIT_ALL))
+        return sssp_set_error(SSSP_ERR_INVALID, "criterion 0x%x is empty or has unknown bits", criterion);
+    int in = IN_NONE, out = OUT_NONE;
+    crit_modes(criterion, &in, &out);
+    if (in > IN_STATIC_M || out > OUT_STATIC_M)
+        return sssp_set_error(SSSP_ERR_UNSUPPORTED, "the batched solver evaluates DIJK, IN-STATIC and OUT-STATIC");
+    if ((!cfg.block || cfg.block == 512) && !cfg.split && !cfg.blocks && !cfg.team_edges && !cfg.team_size) {
+        // the default form; what it leaves is for the launch below
+        for (uint32_t i = 0; i < nq; ++i) {
+            if (!graphs[i] || !dist_outs[i]) return sssp_set_error(SSSP_ERR_INVALID, "query %u: NULL graph or output", i);
+            if (sources[i] >= graphs[i]->n) return sssp_set_error(SSSP_ERR_INVALID, "query %u: source %u >= n", i, sources[i]);
+        }
+        HIP_OK(hipSetDevice(graphs[0]->device));
+        std::vector<uint32_t> left;
+        const int rc = batch_default(graphs, sources, nq, in, out == OUT_STATIC_M, dist_outs, phases_out, &left);
+        if (rc || left.empty()) return rc;
+        if (left.size() < nq) {
+            std::vector<sssp_graph *> lg;
+            std::vector<uint32_t> ls, lp(left.size());
+            std::vector<uint64_t *> ld;
+            for (uint32_t i : left) {
+                lg.push_back(graphs[i]);
+                ls.push_back(sources[i]);
+                ld.push_back(dist_outs[i]);
+            }
+            const int rl = batch_launch(lg.data(), ls.data(), (uint32_t)left.size(), in, out == OUT_STATIC_M, ld.data(),
+                                        lp.data(), cfg, graphs[0]);
+            for (size_t j = 0; rl == SSSP_OK && phases_out && j < left.size(); ++j) phases_out[left[j]] = lp[j];
+            return rl;
+        }
+    }
+    return batch_launch(graphs, sources, nq, in, out == OUT_STATIC_M, dist_outs, phases_out, cfg, graphs[0]);
 }

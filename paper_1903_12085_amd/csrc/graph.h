@@ -76,7 +76,7 @@ struct ResShape {
 };
 ResShape resident_shape(const sssp_graph *g);
 int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
-                   uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran);
+                   uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran, uint32_t cap = 0);
 // What the static stage of a learned checkpoint solve leaves: counts, and minD and the OUT-STATIC
 // threshold of the phase after it (INF64: the solve is finished).
 struct ResLearned {
@@ -91,5 +91,5 @@ bool resident_batch_takes(const sssp_graph *g);
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
                    bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran);
 // A resident solve where the graph and its launch options allow one (phased.hip).
-int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
-                 uint64_t *dist_out, uint32_t *phases_out, bool *ran);
+int resident_try(sssp_graph *g, uint32_t source, int in, int out, uint64_t delta, uint64_t *dist_out,
+                 uint32_t *phases_out, bool *ran);

@@ -3225,8 +3225,8 @@ int resident_scratch(sssp_graph *g, uint64_t bytes) {
 // A resident solve where the graph and the launch options allow one, with the graph's scratch
 // (kept between solves). *ran = false: not run, or not finished; the phase kernels then do it
 // (they also do timed solves: per-kernel timing is about them).
-int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
-                 uint64_t *dist_out, uint32_t *phases_out, bool *ran) {
+int resident_try(sssp_graph *g, uint32_t source, int in, int out, uint64_t delta, uint64_t *dist_out,
+                 uint32_t *phases_out, bool *ran) {
     *ran = false;
     const ResShape r = resident_shape(g);
     if (!r.fits || g->prof) return SSSP_OK;
@@ -3239,7 +3239,7 @@ int resident_try(sssp_graph *g, hipStream_t s, uint32_t source, int in, int out,
     if (rc == SSSP_OK) rc = resident_scratch(g, r.bytes);
     if (rc) return rc;
     uint32_t phases = 0;
-    rc = resident_solve(g, r, s, source, in, out, delta, dist_out, g->res, &phases, ran);
+    rc = resident_solve(g, r, g->stream, source, in, out, delta, dist_out, g->res, &phases, ran);
     if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
     return rc;
 }
@@ -3256,7 +3256,7 @@ extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, ui
             // the whole solve in one workgroup (the batched kernel)
             if (g->cfg.single && static_modes(in, out)) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
             bool ran = false;
-            const int rc = resident_try(g, g->stream, source, in, out, 0, dist_out, phases_out, &ran);
+            const int rc = resident_try(g, source, in, out, 0, dist_out, phases_out, &ran);
             if (rc || ran) return rc;
         }
     }
@@ -3278,7 +3278,7 @@ extern "C" int sssp_delta_step(sssp_graph *g, uint32_t source, uint64_t delta, u
     if (g && dist_out && source < g->n && g->cfg.single != kPhaseKernels) {
         HIP_OK(hipSetDevice(g->device));
         bool ran = false;
-        const int rc = resident_try(g, g->stream, source, IN_NONE, OUT_NONE, delta, dist_out, phases_out, &ran);
+        const int rc = resident_try(g, source, IN_NONE, OUT_NONE, delta, dist_out, phases_out, &ran);
         if (rc || ran) return rc;
     }
     sssp_stats st;

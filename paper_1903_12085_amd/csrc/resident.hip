@@ -118,6 +118,7 @@ struct ResArgs {
     uint32_t quota;      // segments a wavefront keeps for itself in a phase
     uint32_t share;      // rows beyond the quota become records relaxed by all workgroups
     uint32_t lgK;        // vertices per group
+    uint32_t max_phases; // a solve that takes more ends with an error
     unsigned long long delta;  // Delta-stepping: bucket width
     // SIMPLE criteria: the reverse adjacency and, per vertex, the lightest edge of each row whose other
     // end had not settled when the owner last looked, with its place in the row
@@ -646,7 +647,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
                     }
             }
             if (pm == INF64) return k;  // nothing is queued
-            if (k > n) {  // every phase settles the queue minimum
+            if (k > a.max_phases) {
                 if (tid == 0) atomicOr(a.error, 2u);
                 return INF32;
             }
@@ -1082,8 +1083,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             minD = pm != INF64 ? pm / a.delta * a.delta : INF64;
             hi = sadd64(minD, a.delta);
         }
-        // a phase settles at least the queue minimum; a bucket's light rounds each remove or lower
-        if (DELTA ? k / 4 > n + 16 : k > n) {
+        if (k > a.max_phases) {
             if (tid == 0) atomicOr(a.error, 2u);
             return INF32;
         }
@@ -1283,6 +1283,7 @@ static ResArgs resident_args(const sssp_graph *g, const ResShape &r, uint32_t so
     a.share = g->max_deg > kShareDeg;
     a.quota = kQuota;
     a.n = g->n;
+    a.max_phases = g->n;  // a phase settles at least the queue minimum
     a.m = g->m;
     a.src = source;
     a.wmax = g->wmax;
@@ -1320,10 +1321,12 @@ static int resident_launch(rfn k, const ResShape &r, hipStream_t s, ResArgs a, R
 }
 
 int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
-                   uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran) {
+                   uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran, uint32_t cap) {
     ResCtl *ctl;
     ResArgs a = resident_args(g, r, source, dist_out, scratch, &ctl);
     a.delta = delta;
+    if (delta) a.max_phases = 4 * (g->n + 17);  // a bucket's light rounds each remove or lower
+    if (cap) a.max_phases = cap;
     if (in == IN_SIMPLE_M || out == OUT_SIMPLE_M)
         hipLaunchKernelGGL(k_res_init_simple, vertex_grid(g->n), dim3(256), 0, s, a, ctl, (int)(in == IN_SIMPLE_M));
     else hipLaunchKernelGGL(k_res_init, vertex_grid(g->n), dim3(256), 0, s, a, ctl);
@@ -1500,6 +1503,7 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
             a.lgWv = lgWv;
             a.lgK = 3;
             a.quota = kQuota;
+            a.max_phases = a.n;
             a.delta = 0;
             const uint32_t groups = (a.n - 1) / K + 1;
             a.wslots = 64 * ((groups - 1) / (W * BS) + 1);

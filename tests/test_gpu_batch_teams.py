@@ -50,3 +50,47 @@ def test_team_shares_records_again_after_a_query_without(B, length):
     first, middle, last = hub(32000, 3000, 1), path(24000, length), hub(17000, 2000, 2)
     assert O.phased(middle, 0, O.STATIC_OR).phases == length
     run(B, [(first, 260), (middle, 260), (last, 260)])
+
+
+def median_ms(fn, reps=3):
+    import time
+    fn()  # scratch is allocated
+    t = []
+    for _ in range(reps):
+        t0 = time.perf_counter()
+        fn()
+        t.append(1e3 * (time.perf_counter() - t0))
+    return sorted(t)[reps // 2]
+
+
+@pytest.mark.parametrize("count", [1, 2, 3, 12])
+def test_large_grids_are_no_slower_than_in_one_launch(B, count):
+    """Graphs too large for a team, with many phases: at no number of queries slower than with the launch
+    shape given (12 one after the other took 2.1 times as long; a solve that is given up is 2 to 3 %)."""
+    g = G.grid(1030, 515, 1, 1 << 16, 2)
+    dg = B.DeviceGraph.from_graph(g)
+    srcs = [int(s) for s in G.sources(g, count, 9)]
+    dists = [B.new_dist(g.n) for _ in srcs]
+    ours = median_ms(lambda: B.solve_batch([dg] * count, srcs, B.STATIC_OR, dists))
+    one = median_ms(lambda: B.solve_batch([dg] * count, srcs, B.STATIC_OR, dists, cfg=dict(split=64)))
+    print("grid of %d, %d queries: %.1f ms, in one launch %.1f ms" % (g.n, count, ours, one), flush=True)
+    assert ours <= 1.15 * one
+    dg.close()
+
+
+def test_large_graphs_of_few_and_many_phases_with_small_ones(B):
+    """Each way through a batch of large graphs: two in turn; three of few phases in turn; with a grid among
+    them, alone and after others, the batch goes to the one launch; more than the device takes in turn."""
+    random, grid, small = G.er(530003, 4, 1, 1 << 20, 11), G.grid(1029, 512, 1, 1 << 16, 12), G.er(3000, 5, 1, 500, 13)
+    run(B, [(grid, 1), (random, 1), (small, 3)])
+    run(B, [(random, 3), (small, 3)])
+    run(B, [(random, 2), (grid, 2), (small, 3)])
+    run(B, [(random, 17), (small, 2)])
+
+
+def test_large_grids_of_unknown_shape_follow_solved_graphs(B):
+    """A graph of many phases whose degree does not tell so comes after others of its batch, which stay
+    solved; the rest goes to the one launch."""
+    sparse = G.er(530003, 3, 1, 1 << 20, 14)
+    grid = G.grid(1029, 512, 1, 1 << 16, 15)   # nearly 4 edges a vertex
+    run(B, [(sparse, 2), (grid, 1)])
