@@ -1529,8 +1529,8 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
             if (W > 1) {  // the team's set-up is done
                 unsigned long long *words = bar + bar_words(nb, W);
                 const unsigned long long tag = bar_tag(nb);
+                if (tid == 0) bar_put_empty(nb, W, wg, [&](uint32_t i, unsigned long long x) { st_agent(&bar[i], x); });
                 ++nb;
-                if (tid == 0) st_agent(&words[wg * kSlotStride], tag | kVal);
                 if (tid < W) {
                     uint32_t spins = 0;
                     while ((ld64(&words[tid * kSlotStride]) & kTag) != tag && ++spins < kResSpin) {}

@@ -16,6 +16,13 @@ constexpr uint32_t kSlotStride = 8;    // u64 between two workgroups' words (64 
 constexpr unsigned long long kVal = (1ull << 60) - 1, kTag = ~kVal;
 constexpr unsigned long long bar_tag(uint32_t b) { return (unsigned long long)((b >> 1) % 15u + 1u) << 60; }
 constexpr uint32_t bar_words(uint32_t b, uint32_t W) { return (b & 1u) * W * kSlotStride; }
+// Workgroup wg's words at a barrier without values (a team's set-up): both, since after a run of
+// queries of one phase each, whose set-ups are the only barriers of their parity, a word left out
+// would carry the tag of a later phase.
+template <class Put>
+constexpr void bar_put_empty(uint32_t b, uint32_t W, uint32_t wg, Put put) {
+    for (uint32_t i = 0; i < 2; ++i) put(bar_words(b, W) + wg * kSlotStride + i, bar_tag(b) | kVal);
+}
 
 // Counts of shared records are written by solves that share only, so that a word may be older than
 // any number of barriers: it holds the whole number of the barrier that follows it (never 0, which is

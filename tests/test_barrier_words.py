@@ -22,6 +22,8 @@ def words(tmp_path_factory):
                    "unsigned long long t_count(uint32_t next, uint32_t c) { return count_word(next, c); }\n"
                    "int t_is_for(unsigned long long w, uint32_t next) { return count_is_for(w, next); }\n"
                    "uint32_t t_count_words(uint32_t W) { return count_words(W); }\n"
+                   "void t_empty(unsigned long long *bar, uint32_t b, uint32_t W, uint32_t wg) {\n"
+                   "    bar_put_empty(b, W, wg, [&](uint32_t i, unsigned long long x) { bar[i] = x; }); }\n"
                    "uint32_t t_team(uint32_t W) { return team_words(W); }\n}\n")
     lib = str(d / "libwords.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
@@ -69,3 +71,29 @@ def test_words_of_a_team_do_not_overlap(words):
     for W in (1, 2, 32, 256):
         starts = {words.t_words(b, W) for b in range(8)} | {words.t_count_words(W)}
         assert sorted(starts) == [0, 8 * W, 16 * W] and words.t_team(W) == 24 * W
+
+
+def stale_values(w, phases, W=2):
+    """(query, phase, workgroup, word) where the minD (0) or threshold (1) word of a barrier carries its
+    tag before it is written, over the queries of one team. A phase writes a workgroup's two words; what a
+    set-up writes is bar_put_empty's."""
+    bar, nb, bad = (U64 * w.t_team(W))(), 0, []
+    for q, count in enumerate(phases):
+        for wg in range(W):
+            w.t_empty(bar, nb, W, wg)
+        nb += 1
+        for k in range(count):
+            for wg in range(W):
+                for i in (0, 1):
+                    at = w.t_words(nb, W) + 8 * wg + i
+                    if bar[at] & w.t_tag_mask() == w.t_tag(nb):
+                        bad.append((q, k, wg, i))
+                    bar[at] = w.t_tag(nb) | 77
+            nb += 1
+    return bad
+
+
+def test_values_of_an_earlier_query_are_never_current(words):
+    for ones in range(70):  # sources without out-edges: one phase each
+        assert not stale_values(words, [4] + [1] * ones + [4, 2, 9]), ones
+    assert not stale_values(words, [1 + q * 5 % 17 for q in range(400)] + [1] * 100 + [3] * 50)

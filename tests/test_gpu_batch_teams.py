@@ -94,3 +94,10 @@ def test_large_grids_of_unknown_shape_follow_solved_graphs(B):
     sparse = G.er(530003, 3, 1, 1 << 20, 14)
     grid = G.grid(1029, 512, 1, 1 << 16, 15)   # nearly 4 edges a vertex
     run(B, [(sparse, 2), (grid, 1)])
+
+
+@pytest.mark.parametrize("ones", [13, 28])
+def test_team_after_many_queries_of_one_phase(B, ones):
+    """Sources without out-edges between queries of several phases, on teams of two."""
+    lone = G.from_edges(20000, [(1, 2, 5)])
+    run(B, [(path(32000, 6), 256), (lone, 256 * ones), (path(17000, 9), 256)])
