@@ -329,9 +329,10 @@ int sssp_set_launch(sssp_graph *g, const sssp_launch_cfg *cfg);
  * Autotuner for the plain solver: times sssp_solve(g, source, criterion) with
  * HIP events for a set of launch shapes (scan grid, relax grid, chunk size,
  * graph replay, the dense scan or queue arrays; for static criteria also keyed
- * queue arrays, the one-workgroup option and the resident solve), keeps the
- * fastest on g and returns it in best (may be NULL)
- * with its time in best_ms (may be NULL). Distances are never affected.
+ * queue arrays and the one-workgroup option; where sssp_solve has one, the
+ * resident solve), keeps the fastest on g and returns it in best (may be NULL)
+ * with its time in best_ms (may be NULL). `single` is kept as it is for criteria
+ * that always run the phase kernels. Distances are never affected.
  */
 int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion, sssp_launch_cfg *best,
                   float *best_ms);

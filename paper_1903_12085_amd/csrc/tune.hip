@@ -98,7 +98,7 @@ extern "C" int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion,
         if (rc) break;
         if (ms < win_ms) { win_ms = ms; win = c; }
     }
-    if (rc == SSSP_OK && static_modes(in, out)) {
+    if (rc == SSSP_OK && in <= IN_SIMPLE_M && out <= OUT_SIMPLE_M) {
         // the resident solve has no shape to choose; the phase kernels' best shape is kept beside
         // it for the solves that always use them
         sssp_launch_cfg c = win;
@@ -107,6 +107,8 @@ extern "C" int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion,
         float ms = 0;
         if (rc == SSSP_OK) rc = time_call(g->stream, 3, [&] { return sssp_solve(g, source, criterion, dist, nullptr); }, &ms);
         if (rc == SSSP_OK && ms < win_ms) { win_ms = ms; win = c; }
+    } else {
+        win.single = keep.single;  // the other criteria always run the phase kernels: not theirs to choose
     }
     sssp_free(dist);
     if (rc) { sssp_set_launch(g, &keep); return rc; }
