@@ -1261,9 +1261,6 @@ ResShape resident_shape(const sssp_graph *g) {
     return r;
 }
 
-// Runs a resident solve (delta > 0: Delta-stepping) with `scratch` (r.bytes, 256-byte aligned).
-// *ran = false: the device cannot hold the workgroups at once, or one waited too long for another
-// (the device is shared with other work); the distances are unfinished.
 static ResArgs resident_args(const sssp_graph *g, const ResShape &r, uint32_t source, uint64_t *dist_out, void *scratch,
                              ResCtl **ctl) {
     ResArgs a;
@@ -1320,6 +1317,18 @@ static int resident_launch(rfn k, const ResShape &r, hipStream_t s, ResArgs a, R
     return SSSP_OK;
 }
 
+// What a launch's error word says. 1: a workgroup waited too long for another, the solve is not
+// finished (*ran = false). 2: more phases than there can be, unless the caller set the bound.
+static int resident_verdict(unsigned int error, bool capped, bool *ran) {
+    *ran = error == 0;
+    if ((error & 2u) && !capped) return sssp_set_error(SSSP_ERR_INTERNAL, "a resident solve exceeded its phase bound");
+    return SSSP_OK;
+}
+
+// Runs a resident solve (delta > 0: Delta-stepping) with `scratch` (r.bytes, 256-byte aligned).
+// *ran = false: the device cannot hold the workgroups at once, one waited too long for another (the
+// device is shared with other work), or it took more than `cap` phases (0: no cap); the distances are
+// unfinished.
 int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran, uint32_t cap) {
     ResCtl *ctl;
@@ -1337,8 +1346,7 @@ int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32
     HIP_OK(hipMemcpyAsync(h, &ctl->error, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     *phases = h[1];
-    *ran = h[0] == 0;
-    return SSSP_OK;
+    return resident_verdict(h[0], cap != 0, ran);
 }
 
 // The static stage of a learned checkpoint solve, with scratch of resident_learn_bytes. Where the
@@ -1373,8 +1381,8 @@ int resident_learn(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32
     } h;
     HIP_OK(hipMemcpyAsync(&h, &ctl->error, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    *ran = h.error == 0;
-    if (!*ran) return SSSP_OK;
+    const int rv = resident_verdict(h.error, false, ran);
+    if (rv || !*ran) return rv;
     *out = h.learn.out;
     out->reached += 1;  // the source
     out->phases = h.phases;
@@ -1660,9 +1668,8 @@ int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uin
     std::vector<uint32_t> down((o_bar - o_heads) / 4);
     HIP_OK(hipMemcpyAsync(down.data(), base + o_heads, o_bar - o_heads, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    if (down[kGangLog + 1]) return SSSP_OK;
-    if (phases_out)
+    const int rv = resident_verdict(down[kGangLog + 1], false, ran);
+    if (rv == SSSP_OK && *ran && phases_out)
         for (uint32_t i = 0; i < nq; ++i) phases_out[ids[i]] = down[(o_phases - o_heads) / 4 + i];
-    *ran = true;
-    return SSSP_OK;
+    return rv;
 }

@@ -1,0 +1,104 @@
+"""The library's host code on a HIP runtime without a device (hip_host.cpp): what it does when an
+allocation or a launch fails, or when a resident solve reports that it could not finish."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+OK, OOM, DEVICE, INTERNAL = 0, -2, -3, -5
+MiB = 1 << 20
+STATIC_OR, SIMPLE_OR = 6, 24
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    from paper_1903_12085_amd import build
+    objs = [os.path.join(build.HERE, "_build", s.replace(".hip", ".o")) for s in build.SOURCES]
+    newest = max(os.path.getmtime(os.path.join(build.CSRC, f)) for f in os.listdir(build.CSRC))
+    if any(not os.path.exists(o) or os.path.getmtime(o) < newest for o in objs):
+        build.build()
+    d = tmp_path_factory.mktemp("host")
+    rt, so = str(d / "hip_host.o"), str(d / "libhost.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c",
+                    os.path.join(HERE, "hip_host.cpp"), "-o", rt], check=True)
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,-z,defs", "-o", so] + objs + [rt], check=True)
+    L = ctypes.CDLL(so)
+    L.host_reset.argtypes = [ctypes.c_size_t]
+    L.host_used.restype = ctypes.c_size_t
+    L.host_log.restype = L.sssp_last_error.restype = ctypes.c_char_p
+    L.sssp_graph_create.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_void_p] * 3 + [
+        ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    L.sssp_delta_step.argtypes = [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p, ctypes.c_void_p]
+    L.host_reset(1 << 40)
+    return L
+
+
+def ptr(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+class Host:
+    """A graph of n vertices and m edges on the host runtime, and calls on it."""
+
+    def __init__(self, lib, n=9, m=16):
+        rng = np.random.default_rng(1)
+        self.lib, self.n = lib, n
+        rp = (np.arange(n + 1, dtype=np.uint64) * m) // n
+        col, w = rng.integers(0, n, m).astype(np.uint32), np.ones(m, np.uint32)
+        self.h = ctypes.c_void_p()
+        self.rc = lib.sssp_graph_create(n, m, ptr(rp), ptr(col), ptr(w), 0, None, ctypes.byref(self.h))
+        self.dist, self.phases = np.zeros(n, np.uint64), ctypes.c_uint32(99)
+
+    def solve(self, crit=STATIC_OR, call="sssp_solve"):
+        return getattr(self.lib, call)(self.h, 0, crit, ptr(self.dist), ctypes.byref(self.phases))
+
+    def delta(self):
+        return self.lib.sssp_delta_step(self.h, 0, 100, ptr(self.dist), ctypes.byref(self.phases))
+
+    def batch(self, nq=2):
+        hs = (ctypes.c_void_p * nq)(*[self.h.value] * nq)
+        ds = [np.zeros(self.n, np.uint64) for _ in range(nq)]
+        outs = (ctypes.c_void_p * nq)(*[ptr(d).value for d in ds])
+        src = np.zeros(nq, np.uint32)
+        return self.lib.sssp_solve_batch(hs, ptr(src), nq, STATIC_OR, outs, None)
+
+    def learned(self):
+        w, sel, none = np.zeros(5382, np.float32), ctypes.c_void_p(), ctypes.c_void_p()
+        assert self.lib.sssp_selector_create(ptr(w), ctypes.byref(sel)) == OK
+        rc = self.lib.sssp_solve_learned_checkpoint(self.h, 0, sel, ptr(self.dist), none, none, none, 0, none)
+        self.lib.sssp_selector_destroy(sel)
+        return rc
+
+    def log(self):
+        return self.lib.host_log().decode().split()
+
+    def message(self):
+        return self.lib.sssp_last_error().decode()
+
+    def close(self):
+        self.lib.sssp_graph_destroy(self.h)
+
+
+SOLVES = {"static": lambda g: g.solve(), "simple": lambda g: g.solve(SIMPLE_OR), "delta": lambda g: g.delta(),
+          "noalloc": lambda g: g.solve(call="sssp_solve_noalloc"), "batch": lambda g: g.batch(),
+          "learned": lambda g: g.learned()}
+
+
+@pytest.mark.parametrize("name", list(SOLVES))
+def test_broken_phase_bound_is_an_error(lib, name):
+    """A resident solve that ran for more phases than there can be has broken an invariant: that is
+    reported, not covered up by a second solve with other kernels."""
+    g = Host(lib)
+    assert g.rc == OK
+    lib.host_reset(1 << 40)
+    lib.host_coop(0, 2, 5, 6 if name == "batch" else 0)
+    assert SOLVES[name](g) == INTERNAL and "phase bound" in g.message()
+    assert "kernel" not in g.log()[g.log().index("coop"):]
+    if name != "learned":  # its second stage would need the kernels
+        lib.host_coop(0, 0, 5, 6 if name == "batch" else 0)
+        assert SOLVES[name](g) == OK and (name == "batch" or g.phases.value == 5)
+    g.close()
