@@ -97,7 +97,8 @@ def test_broken_phase_bound_is_an_error(lib, name):
     lib.host_reset(1 << 40)
     lib.host_coop(0, 2, 5, 6 if name == "batch" else 0)
     assert SOLVES[name](g) == INTERNAL and "phase bound" in g.message()
-    assert "kernel" not in g.log()[g.log().index("coop"):]
+    after = g.log()[g.log().index("coop"):]
+    assert after.count("kernel") == (name == "learned")  # its counts are queued before the read-back
     if name != "learned":  # its second stage would need the kernels
         lib.host_coop(0, 0, 5, 6 if name == "batch" else 0)
         assert SOLVES[name](g) == OK and (name == "batch" or g.phases.value == 5)
