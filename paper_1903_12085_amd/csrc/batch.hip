@@ -686,10 +686,10 @@ int batch_solve_one(sssp_graph *g, uint32_t source, int in, bool out_static, uin
         g->one_fl = nullptr;
         g->one_fm = nullptr;
         g->one_aux = nullptr;
-        HIP_OK(hipMalloc(&g->one_st, ((uint64_t)g->n + 255) & ~255ull));
-        HIP_OK(hipMalloc(&g->one_fl, 3ull * g->n * sizeof(uint32_t)));
-        HIP_OK(hipMalloc(&g->one_fm, 2ull * g->n * sizeof(uint2)));
-        HIP_OK(hipMalloc(&g->one_aux, sizeof(OneAux)));
+        HIP_OK(sssp_malloc(&g->one_st, ((uint64_t)g->n + 255) & ~255ull));
+        HIP_OK(sssp_malloc(&g->one_fl, 3ull * g->n * sizeof(uint32_t)));
+        HIP_OK(sssp_malloc(&g->one_fm, 2ull * g->n * sizeof(uint2)));
+        HIP_OK(sssp_malloc(&g->one_aux, sizeof(OneAux)));
     }
     OneAux h;
     memset(&h, 0, sizeof h);
@@ -771,18 +771,18 @@ static int batch_launch(sssp_graph *const *graphs, const uint32_t *sources, uint
     int rc = SSSP_OK;
 #define TRY(call) do { hipError_t _e = (call); if (_e != hipSuccess) { \
         rc = sssp_set_error(_e == hipErrorOutOfMemory ? SSSP_ERR_OOM : SSSP_ERR_DEVICE, "%s: %s", #call, hipGetErrorString(_e)); goto done; } } while (0)
-    TRY(hipMalloc(&st, st_total));
-    TRY(hipMalloc(&fl, fl_total * sizeof(uint32_t)));
-    TRY(hipMalloc(&fm, fm_total * sizeof(uint2)));
+    TRY(sssp_malloc(&st, st_total));
+    TRY(sssp_malloc(&fl, fl_total * sizeof(uint32_t)));
+    TRY(sssp_malloc(&fm, fm_total * sizeof(uint2)));
     for (uint32_t i = 0; i < nq; ++i) {
         hq[i].st = st + st_off[i];
         hq[i].fl = fl + fl_off[i];
         hq[i].fm = fm + fm_off[i];
     }
-    TRY(hipMalloc(&dq, nq * sizeof(BatchQuery)));
-    TRY(hipMalloc(&dorder, nq * sizeof(uint32_t)));
-    TRY(hipMalloc(&dph, nq * sizeof(uint32_t)));
-    TRY(hipMalloc(&dctl, sizeof(BatchCtl)));
+    TRY(sssp_malloc(&dq, nq * sizeof(BatchQuery)));
+    TRY(sssp_malloc(&dorder, nq * sizeof(uint32_t)));
+    TRY(sssp_malloc(&dph, nq * sizeof(uint32_t)));
+    TRY(sssp_malloc(&dctl, sizeof(BatchCtl)));
     TRY(hipMemcpyAsync(dq, hq.data(), nq * sizeof(BatchQuery), hipMemcpyHostToDevice, s));
     TRY(hipMemsetAsync(dctl, 0, sizeof(BatchCtl), s));
     {
@@ -813,8 +813,8 @@ static int batch_launch(sssp_graph *const *graphs, const uint32_t *sources, uint
                 if (single_blocks > nsmall) single_blocks = nsmall;
                 if (team_blocks + single_blocks > resident) single_blocks = resident - team_blocks;
                 uint32_t grid = (uint32_t)(team_blocks + single_blocks);
-                TRY(hipMalloc(&dlarge, nlarge * sizeof(uint32_t)));
-                TRY(hipMalloc(&dteams, nteams * sizeof(TeamCtl)));
+                TRY(sssp_malloc(&dlarge, nlarge * sizeof(uint32_t)));
+                TRY(sssp_malloc(&dteams, nteams * sizeof(TeamCtl)));
                 TRY(hipMemcpyAsync(dlarge, large.data(), nlarge * sizeof(uint32_t), hipMemcpyHostToDevice, s));
                 TRY(hipMemsetAsync(dteams, 0, nteams * sizeof(TeamCtl), s));
                 if (nsmall) TRY(hipMemcpyAsync(dorder, small.data(), nsmall * sizeof(uint32_t), hipMemcpyHostToDevice, s));

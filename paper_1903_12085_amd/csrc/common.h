@@ -182,6 +182,14 @@ struct SolveBufs {
 
 int sssp_set_error(int code, const char *fmt, ...);
 
+// hipMalloc for everything the library allocates: when memory runs out, what it keeps of destroyed
+// graphs is given back first (graph.hip).
+hipError_t sssp_malloc_bytes(void **p, uint64_t bytes);
+template <typename T>
+static inline hipError_t sssp_malloc(T **p, uint64_t bytes) {
+    return sssp_malloc_bytes((void **)p, bytes);
+}
+
 // Release helpers for clean-up paths, where a failure has nothing left to undo.
 static inline void sssp_free(void *p) {
     if (p) (void)hipFree(p);

@@ -55,7 +55,6 @@ struct sssp_graph {
 
 DevGraph dev_view(const sssp_graph *g);
 int graph_ensure_csc(sssp_graph *g);
-void blocks_give_back();           // frees what is kept of destroyed graphs
 int resident_scratch(sssp_graph *g, uint64_t bytes);
 int graph_ensure_sorted(sssp_graph *g);
 void graph_default_cfg(sssp_graph *g);

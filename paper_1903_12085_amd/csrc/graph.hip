@@ -231,7 +231,7 @@ static int radix_sort(unsigned long long *&k0, unsigned long long *&k1, uint32_t
     if (rocprim::radix_sort_pairs(nullptr, tmp_bytes, k0, k1, v0, v1, (size_t)m, 0, end_bit, s) != hipSuccess)
         return sssp_set_error(SSSP_ERR_DEVICE, "radix_sort_pairs size query failed");
     void *tmp = nullptr;
-    HIP_OK(hipMalloc(&tmp, tmp_bytes ? tmp_bytes : 1));
+    HIP_OK(sssp_malloc(&tmp, tmp_bytes ? tmp_bytes : 1));
     hipError_t e = rocprim::radix_sort_pairs(tmp, tmp_bytes, k0, k1, v0, v1, (size_t)m, 0, end_bit, s);
     hipError_t e2 = hipStreamSynchronize(s);
     sssp_free(tmp);
@@ -267,14 +267,8 @@ static hipError_t block_alloc(int dev, uint64_t bytes, void **p, uint64_t *got) 
             return hipSuccess;
         }
     }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory) {
-        blocks_give_back();
-        (void)hipGetLastError();
-        e = hipMalloc(p, bytes);
-    }
     *got = bytes;
-    return e;
+    return sssp_malloc_bytes(p, bytes);
 }
 
 static void block_free(int dev, void *p, uint64_t bytes) {
@@ -286,12 +280,22 @@ static void block_free(int dev, void *p, uint64_t bytes) {
     sssp_free(p);
 }
 
-void blocks_give_back() {
+static void blocks_give_back() {
     std::lock_guard<std::mutex> lock(g_keep_mu);
     for (auto &k : g_keep) {
         sssp_free(k.p);
         k.p = nullptr;
     }
+}
+
+hipError_t sssp_malloc_bytes(void **p, uint64_t bytes) {
+    hipError_t e = hipMalloc(p, bytes ? bytes : 1);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    blocks_give_back();
+    e = hipMalloc(p, bytes ? bytes : 1);
+    if (e == hipErrorOutOfMemory) (void)hipGetLastError();  // reported here, not by the next launch
+    return e;
 }
 
 static uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
@@ -314,7 +318,7 @@ static int create_impl(uint32_t n, uint64_t m, const uint64_t *row_ptr, const ui
     CallBuffer stage;  // host input on the device
     if (!device_ptrs) {
         const uint64_t o_col = up256((n + 1ull) * sizeof(uint64_t)), o_w = up256(o_col + m * sizeof(uint32_t));
-        HIP_OK(hipMalloc(&stage.p, o_w + m * sizeof(uint32_t)));
+        HIP_OK(sssp_malloc(&stage.p, o_w + m * sizeof(uint32_t)));
         uint8_t *st = (uint8_t *)stage.p;
         HIP_OK(hipMemcpyAsync(st, row_ptr, (n + 1ull) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
         if (m) {
@@ -437,10 +441,10 @@ int graph_ensure_sorted(sssp_graph *g) {
     int rc = SSSP_OK;
 #define TRY(call) do { hipError_t _e = (call); if (_e != hipSuccess) { \
         rc = sssp_set_error(_e == hipErrorOutOfMemory ? SSSP_ERR_OOM : SSSP_ERR_DEVICE, "%s: %s", #call, hipGetErrorString(_e)); goto done; } } while (0)
-    TRY(hipMalloc(&k0, m * sizeof(unsigned long long)));
-    TRY(hipMalloc(&k1, m * sizeof(unsigned long long)));
-    TRY(hipMalloc(&v0, m * sizeof(uint32_t)));
-    TRY(hipMalloc(&v1, m * sizeof(uint32_t)));
+    TRY(sssp_malloc(&k0, m * sizeof(unsigned long long)));
+    TRY(sssp_malloc(&k1, m * sizeof(unsigned long long)));
+    TRY(sssp_malloc(&v0, m * sizeof(uint32_t)));
+    TRY(sssp_malloc(&v1, m * sizeof(uint32_t)));
     hipLaunchKernelGGL(k_row_keys_e, dim3(grid_for(m)), dim3(256), 0, s, g->n, m, g->rp, g->edges, k0, v0);
     rc = radix_sort(k0, k1, v0, v1, m, 32 + bits_for(g->n), s);
     if (rc != SSSP_OK) goto done;
@@ -459,9 +463,9 @@ done:
 int graph_ensure_csc(sssp_graph *g) {
     if (g->ip || g->m == 0) {
         if (!g->ip) {  // edgeless graph: all-zero in_ptr
-            HIP_OK(hipMalloc(&g->ip, (g->n + 1) * sizeof(uint32_t)));
+            HIP_OK(sssp_malloc(&g->ip, (g->n + 1) * sizeof(uint32_t)));
             HIP_OK(hipMemsetAsync(g->ip, 0, (g->n + 1) * sizeof(uint32_t), g->stream));
-            HIP_OK(hipMalloc(&g->in_edges, sizeof(uint2)));
+            HIP_OK(sssp_malloc(&g->in_edges, sizeof(uint2)));
         }
         return SSSP_OK;
     }
@@ -470,10 +474,10 @@ int graph_ensure_csc(sssp_graph *g) {
     unsigned long long *k0 = nullptr, *k1 = nullptr;
     uint32_t *v0 = nullptr, *v1 = nullptr;
     int rc = SSSP_OK;
-    if (hipMalloc(&k0, m * 8) != hipSuccess || hipMalloc(&k1, m * 8) != hipSuccess ||
-        hipMalloc(&v0, m * 4) != hipSuccess || hipMalloc(&v1, m * 4) != hipSuccess ||
-        hipMalloc(&g->ip, (g->n + 1) * sizeof(uint32_t)) != hipSuccess ||
-        hipMalloc(&g->in_edges, m * sizeof(uint2)) != hipSuccess) {
+    if (sssp_malloc(&k0, m * 8) != hipSuccess || sssp_malloc(&k1, m * 8) != hipSuccess ||
+        sssp_malloc(&v0, m * 4) != hipSuccess || sssp_malloc(&v1, m * 4) != hipSuccess ||
+        sssp_malloc(&g->ip, (g->n + 1) * sizeof(uint32_t)) != hipSuccess ||
+        sssp_malloc(&g->in_edges, m * sizeof(uint2)) != hipSuccess) {
         rc = sssp_set_error(SSSP_ERR_OOM, "CSC allocation failed");
     } else {
         hipLaunchKernelGGL(k_col_keys, dim3(grid_for(m)), dim3(256), 0, s, m, g->edges, g->rp, g->n, k0, v0);

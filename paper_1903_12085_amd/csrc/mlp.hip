@@ -110,11 +110,11 @@ struct MlpWork {
     int cap = 0;
     int alloc(int rows) {
         cap = rows;
-        HIP_OK(hipMalloc(&a1, rows * kMlpH * 4)); HIP_OK(hipMalloc(&h1, rows * kMlpH * 4));
-        HIP_OK(hipMalloc(&a2, rows * kMlpH * 4)); HIP_OK(hipMalloc(&h2, rows * kMlpH * 4));
-        HIP_OK(hipMalloc(&z, rows * kMlpOut * 4)); HIP_OK(hipMalloc(&dz, rows * kMlpOut * 4));
-        HIP_OK(hipMalloc(&d2, rows * kMlpH * 4)); HIP_OK(hipMalloc(&d1, rows * kMlpH * 4));
-        HIP_OK(hipMalloc(&loss, rows * 4)); HIP_OK(hipMalloc(&grad, kMlpParams * 4));
+        HIP_OK(sssp_malloc(&a1, rows * kMlpH * 4)); HIP_OK(sssp_malloc(&h1, rows * kMlpH * 4));
+        HIP_OK(sssp_malloc(&a2, rows * kMlpH * 4)); HIP_OK(sssp_malloc(&h2, rows * kMlpH * 4));
+        HIP_OK(sssp_malloc(&z, rows * kMlpOut * 4)); HIP_OK(sssp_malloc(&dz, rows * kMlpOut * 4));
+        HIP_OK(sssp_malloc(&d2, rows * kMlpH * 4)); HIP_OK(sssp_malloc(&d1, rows * kMlpH * 4));
+        HIP_OK(sssp_malloc(&loss, rows * 4)); HIP_OK(sssp_malloc(&grad, kMlpParams * 4));
         return SSSP_OK;
     }
     ~MlpWork() {
@@ -150,8 +150,8 @@ extern "C" int sssp_selector_create(const float *weights, sssp_selector **out) {
     *out = nullptr;
     sssp_selector *s = new (std::nothrow) sssp_selector();
     if (!s) return sssp_set_error(SSSP_ERR_OOM, "host allocation failed");
-    if (hipGetDevice(&s->device) != hipSuccess || hipMalloc(&s->w, kMlpParams * 4) != hipSuccess ||
-        hipMalloc(&s->m, kMlpParams * 4) != hipSuccess || hipMalloc(&s->v, kMlpParams * 4) != hipSuccess) {
+    if (hipGetDevice(&s->device) != hipSuccess || sssp_malloc(&s->w, kMlpParams * 4) != hipSuccess ||
+        sssp_malloc(&s->m, kMlpParams * 4) != hipSuccess || sssp_malloc(&s->v, kMlpParams * 4) != hipSuccess) {
         sssp_selector_destroy(s);
         return sssp_set_error(SSSP_ERR_OOM, "selector allocation failed");
     }
@@ -192,12 +192,12 @@ extern "C" int sssp_selector_set_weights(sssp_selector *s, const float *host_in)
 const float *selector_device_weights(const sssp_selector *s) { return s ? s->w : nullptr; }
 
 static int upload_xy(const float *x, const int32_t *y, uint32_t n, float **dx, int **dy) {
-    HIP_OK(hipMalloc(dx, (uint64_t)n * kMlpIn * 4));
+    HIP_OK(sssp_malloc(dx, (uint64_t)n * kMlpIn * 4));
     HIP_OK(hipMemcpy(*dx, x, (uint64_t)n * kMlpIn * 4, hipMemcpyHostToDevice));
     if (y) {
         for (uint32_t i = 0; i < n; ++i)
             if (y[i] < 0 || y[i] >= kMlpOut) return sssp_set_error(SSSP_ERR_INVALID, "label %d out of range", y[i]);
-        HIP_OK(hipMalloc(dy, (uint64_t)n * 4));
+        HIP_OK(sssp_malloc(dy, (uint64_t)n * 4));
         HIP_OK(hipMemcpy(*dy, y, (uint64_t)n * 4, hipMemcpyHostToDevice));
     }
     return SSSP_OK;
@@ -263,8 +263,8 @@ extern "C" int sssp_selector_train(sssp_selector *s, const float *x, const int32
     MlpWork k;
     const uint32_t B = batch < n ? batch : n;
     if (!rc) rc = k.alloc((int)B);
-    if (!rc && (hipMalloc(&xb, (uint64_t)B * kMlpIn * 4) != hipSuccess || hipMalloc(&yb, B * 4) != hipSuccess ||
-                hipMalloc(&didx, (uint64_t)n * 4) != hipSuccess))
+    if (!rc && (sssp_malloc(&xb, (uint64_t)B * kMlpIn * 4) != hipSuccess || sssp_malloc(&yb, B * 4) != hipSuccess ||
+                sssp_malloc(&didx, (uint64_t)n * 4) != hipSuccess))
         rc = sssp_set_error(SSSP_ERR_OOM, "training buffers");
     std::vector<uint32_t> perm(n);
     double last = 0;

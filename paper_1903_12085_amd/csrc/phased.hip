@@ -2420,12 +2420,7 @@ static uint32_t shard_capacity(uint32_t n, int G) {
 // call starts the group afresh.
 static int alloc_group(void **const *ptr, const uint64_t *bytes, int k) {
     for (int i = 0; i < k; ++i) {
-        hipError_t e = hipMalloc(ptr[i], bytes[i] ? bytes[i] : 1);
-        if (e == hipErrorOutOfMemory) {
-            blocks_give_back();
-            (void)hipGetLastError();
-            e = hipMalloc(ptr[i], bytes[i] ? bytes[i] : 1);
-        }
+        const hipError_t e = sssp_malloc(ptr[i], bytes[i]);
         if (e != hipSuccess) {
             for (int j = 0; j < k; ++j) {
                 sssp_free(*ptr[j]);
@@ -2470,7 +2465,7 @@ int solve_bufs_ensure(sssp_graph *g, bool cursors, bool stamps, bool queue, bool
         int rc = alloc_group(p, z, 4);
         if (rc) return rc;
     }
-    if (stamps && !b.stamp) HIP_OK(hipMalloc(&b.stamp, n * 4));
+    if (stamps && !b.stamp) HIP_OK(sssp_malloc(&b.stamp, n * 4));
     if (queue && !(b.qd && b.qv && b.qm && b.qr && b.qcnt)) {
         const uint64_t G = (uint64_t)g->cfg.scan_blocks;
         const uint64_t span = scan_span(g->n, g->cfg.scan_blocks, 16);
@@ -3031,7 +3026,7 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     if (delta_mode && g->delta_cap < n_deltas) {
         sssp_free(g->b.deltas);
         g->b.deltas = nullptr;
-        HIP_OK(hipMalloc(&g->b.deltas, n_deltas * sizeof(unsigned long long)));
+        HIP_OK(sssp_malloc(&g->b.deltas, n_deltas * sizeof(unsigned long long)));
         g->delta_cap = n_deltas;
     }
     hipStream_t s = g->stream;
@@ -3060,11 +3055,11 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     a.b.trace_cf = nullptr;
     CallBuffer trace_buf, feat_buf, cf_buf;  // freed on every return below
     if (trace_cap) {
-        HIP_OK(hipMalloc(&trace_buf.p, (uint64_t)trace_cap * sizeof(PhaseRec)));
+        HIP_OK(sssp_malloc(&trace_buf.p, (uint64_t)trace_cap * sizeof(PhaseRec)));
         a.b.trace = (PhaseRec *)trace_buf.p;
         a.b.trace_cap = trace_cap;
-        if (feat_host) HIP_OK(hipMalloc(&feat_buf.p, (uint64_t)trace_cap * kMlpIn * sizeof(float)));
-        if (cf_host) HIP_OK(hipMalloc(&cf_buf.p, (uint64_t)trace_cap * 3 * sizeof(uint32_t)));
+        if (feat_host) HIP_OK(sssp_malloc(&feat_buf.p, (uint64_t)trace_cap * kMlpIn * sizeof(float)));
+        if (cf_host) HIP_OK(sssp_malloc(&cf_buf.p, (uint64_t)trace_cap * 3 * sizeof(uint32_t)));
         a.b.trace_feat = (float *)feat_buf.p;
         a.b.trace_cf = (uint32_t *)cf_buf.p;
     }
@@ -3211,13 +3206,7 @@ int resident_scratch(sssp_graph *g, uint64_t bytes) {
     sssp_free(g->res);
     g->res = nullptr;
     g->res_bytes = 0;
-    hipError_t e = hipMalloc(&g->res, bytes);
-    if (e == hipErrorOutOfMemory) {
-        blocks_give_back();
-        (void)hipGetLastError();
-        e = hipMalloc(&g->res, bytes);
-    }
-    HIP_OK(e);
+    HIP_OK(sssp_malloc(&g->res, bytes));
     g->res_bytes = bytes;
     return SSSP_OK;
 }

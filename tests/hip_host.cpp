@@ -9,7 +9,7 @@
 #include <string>
 
 static std::map<void *, size_t> g_mem;
-static size_t g_used, g_limit;
+static size_t g_used, g_limit, g_base, g_peak;  // bytes: now, at most, at the last reset, most since
 static std::string g_log;
 static hipError_t g_last, g_coop = hipSuccess;
 static bool g_report;
@@ -19,12 +19,14 @@ static int g_fail_events;
 extern "C" {
 void host_reset(size_t limit) {
     g_limit = limit;
+    g_base = g_peak = g_used;
     g_log.clear();
     g_coop = hipSuccess;
     g_report = false;
     g_fail_events = 0;
 }
 size_t host_used() { return g_used; }
+size_t host_peak() { return g_peak - g_base; }
 const char *host_log() { return g_log.c_str(); }
 // The next cooperative launch returns e; the first read-back after it holds error and phases from word
 // `at` on.
@@ -48,6 +50,7 @@ hipError_t hipMalloc(void **p, size_t n) {
     *p = calloc(n ? n : 1, 1);
     g_mem[*p] = n;
     g_used += n;
+    if (g_used > g_peak) g_peak = g_used;
     return hipSuccess;
 }
 hipError_t hipFree(void *p) {

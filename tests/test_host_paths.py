@@ -28,7 +28,7 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,-z,defs", "-o", so] + objs + [rt], check=True)
     L = ctypes.CDLL(so)
     L.host_reset.argtypes = [ctypes.c_size_t]
-    L.host_used.restype = ctypes.c_size_t
+    L.host_used.restype = L.host_peak.restype = ctypes.c_size_t
     L.host_log.restype = L.sssp_last_error.restype = ctypes.c_char_p
     L.sssp_graph_create.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_void_p] * 3 + [
         ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
@@ -103,3 +103,80 @@ def test_broken_phase_bound_is_an_error(lib, name):
         lib.host_coop(0, 0, 5, 6 if name == "batch" else 0)
         assert SOLVES[name](g) == OK and (name == "batch" or g.phases.value == 5)
     g.close()
+
+
+def keep_block(lib):
+    """Destroys a graph of about 80 MB, whose block the library keeps."""
+    lib.host_reset(1 << 40)
+    lib.sssp_graph_destroy(None)
+    big = Host(lib, 1 << 20, 6 << 20)
+    assert big.rc == OK
+    before = lib.host_used()
+    big.close()
+    assert before - lib.host_used() < MiB  # still held
+
+
+def create(lib, g):
+    made = Host(lib, 5, 7)
+    made.close()
+    return made.rc
+
+
+def one_workgroup(lib, g):
+    cfg = (ctypes.c_uint32 * 6)()
+    lib.sssp_get_launch(g.h, cfg)
+    cfg[5] = 1
+    assert lib.sssp_set_launch(g.h, cfg) == OK
+    return g.solve()
+
+
+def batch_shape(lib, g):
+    h, src, out = (ctypes.c_void_p * 1)(g.h.value), np.zeros(1, np.uint32), (ctypes.c_void_p * 1)(ptr(g.dist).value)
+    return lib.sssp_solve_batch_ex(h, ptr(src), 1, STATIC_OR, out, None, (ctypes.c_uint32 * 5)(256, 0, 0, 0, 0))
+
+
+def traced(lib, g):
+    trace, st = np.zeros(64, np.uint64), np.zeros(64, np.uint64)
+    return lib.sssp_solve_ex(g.h, 0, SIMPLE_OR, ptr(g.dist), ptr(st), None, ptr(trace), 2)
+
+
+def selector(lib, g):
+    sel = ctypes.c_void_p()
+    rc = lib.sssp_selector_create(ptr(np.zeros(5382, np.float32)), ctypes.byref(sel))
+    if rc == OK:
+        x, y = np.zeros((4, 12), np.float32), np.zeros((4, 6), np.float32)
+        rc = lib.sssp_selector_forward(sel, ptr(x), 4, ptr(y))
+        lib.sssp_selector_destroy(sel)
+    return rc
+
+
+ALLOCATING = {"create": create, "static": (lambda lib, g: g.solve()), "simple": (lambda lib, g: g.solve(SIMPLE_OR)),
+              "delta": (lambda lib, g: g.delta()), "batch": (lambda lib, g: g.batch()), "batch_shape": batch_shape,
+              "one_workgroup": one_workgroup, "traced": traced, "learned": (lambda lib, g: g.learned()),
+              "selector": selector}
+
+
+@pytest.mark.parametrize("name", list(ALLOCATING))
+def test_kept_block_is_given_back_whichever_allocation_fails(lib, name):
+    """With memory for all but the last k bytes of what a call allocates, k from 1 to all of it: one of its
+    allocations fails first, the kept block goes, and the call succeeds as with memory to spare. (Solves
+    that need the phase kernels end in their phase bound here, since kernels do nothing.)"""
+    def attempt(slack):
+        g = Host(lib)
+        assert g.rc == OK
+        lib.host_reset(lib.host_used() + slack)
+        rc = ALLOCATING[name](lib, g)
+        log, msg, peak = g.log(), g.message(), lib.host_peak()
+        lib.host_reset(1 << 40)
+        g.close()
+        return rc, log, msg, peak
+
+    keep_block(lib)
+    expect, log, _, need = attempt(1 << 30)
+    assert expect in (OK, INTERNAL) and "oom" not in log and need > 0
+    for i in range(24):
+        keep_block(lib)
+        rc, log, msg, _ = attempt((need - 1) * i // 24)
+        assert rc == expect, (i, rc, msg)
+        assert log.count("oom") == 1, (i, log[:20])
+    lib.sssp_graph_destroy(None)
