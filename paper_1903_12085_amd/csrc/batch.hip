@@ -723,8 +723,8 @@ extern "C" int sssp_batch_get_config(sssp_batch_cfg *cfg) {
 }
 
 // The queries by one launch of persistent workgroups and teams, in the given shape, on g0's stream.
-static int batch_launch(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq, int in, bool out_static,
-                        uint64_t *const *dist_outs, uint32_t *phases_out, const sssp_batch_cfg &cfg, const sssp_graph *g0) {
+static int batch_once(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq, int in, bool out_static,
+                      uint64_t *const *dist_outs, uint32_t *phases_out, const sssp_batch_cfg &cfg, sssp_graph *g0) {
     std::vector<BatchQuery> hq(nq);
     std::vector<uint64_t> st_off(nq), fl_off(nq), fm_off(nq);
     uint64_t st_total = 0, fl_total = 0, fm_total = 0;
@@ -849,6 +849,16 @@ done:
     return rc;
 }
 
+// It needs no resident scratch: what the graphs hold of it goes when its own buffers do not fit.
+static int batch_launch(sssp_graph *const *graphs, const uint32_t *sources, uint32_t nq, int in, bool out_static,
+                        uint64_t *const *dist_outs, uint32_t *phases_out, const sssp_batch_cfg &cfg, sssp_graph *g0) {
+    const int rc = batch_once(graphs, sources, nq, in, out_static, dist_outs, phases_out, cfg, g0);
+    if (rc != SSSP_ERR_OOM) return rc;
+    bool released = resident_release(g0);
+    for (uint32_t i = 0; i < nq; ++i) released = resident_release(graphs[i]) || released;
+    return released ? batch_once(graphs, sources, nq, in, out_static, dist_outs, phases_out, cfg, g0) : rc;
+}
+
 // The default form: queries of graphs that a resident team takes run on teams, larger ones and a query
 // alone on the whole device, one after the other. *left: the queries that were not solved.
 //
@@ -878,7 +888,13 @@ static int batch_default(sssp_graph *const *graphs, const uint32_t *sources, uin
         scratch = std::max(scratch, r.bytes);
         turns += graphs[i]->m >= (1u << 25) ? 0 : graphs[i]->n < (1u << 20) ? 5 : 4;
     }
-    if (!fits || (large.size() > 2 && turns > kTurns)) {
+    if (large.size() > 2 && turns > kTurns) fits = false;
+    if (fits && !large.empty()) {
+        const int rc = resident_scratch(graphs[0], scratch);
+        if (rc && rc != SSSP_ERR_OOM) return rc;
+        fits = rc == SSSP_OK;
+    }
+    if (!fits) {
         for (uint32_t i = 0; i < nq; ++i) left->push_back(i);
         return SSSP_OK;
     }
@@ -886,10 +902,6 @@ static int batch_default(sssp_graph *const *graphs, const uint32_t *sources, uin
     std::stable_sort(large.begin(), large.end(), [&](uint32_t x, uint32_t y) {
         return graphs[x]->m * (double)graphs[y]->n < graphs[y]->m * (double)graphs[x]->n;
     });
-    if (!large.empty()) {
-        const int rc = resident_scratch(graphs[0], scratch);
-        if (rc) return rc;
-    }
     for (size_t j = 0; j < large.size(); ++j) {
         const uint32_t i = large[j];
         const uint32_t cap = large.size() > 2 ? (uint32_t)sqrt((double)graphs[i]->n) : 0;

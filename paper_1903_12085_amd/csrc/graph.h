@@ -56,6 +56,7 @@ struct sssp_graph {
 DevGraph dev_view(const sssp_graph *g);
 int graph_ensure_csc(sssp_graph *g);
 int resident_scratch(sssp_graph *g, uint64_t bytes);
+bool resident_release(sssp_graph *g);
 int graph_ensure_sorted(sssp_graph *g);
 void graph_default_cfg(sssp_graph *g);
 int solve_bufs_ensure(sssp_graph *g, bool cursors, bool stamps, bool queue, bool approx = false, bool store = false);

@@ -2946,7 +2946,7 @@ struct SwitchReq {
     int mode = 0;
 };
 
-static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_t crit,
+static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_t crit,
                         const uint64_t *deltas, uint32_t n_deltas, uint64_t *dist_out,
                         sssp_stats *stats, uint32_t *phase_of, sssp_phase_rec *trace,
                         uint32_t trace_cap, const sssp_selector *sel = nullptr, float *feat_host = nullptr,
@@ -3072,7 +3072,8 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     if (ckpt && rs.fits && !trace_cap && !phase_of && g->cfg.single != kPhaseKernels) {
         rc = resident_scratch(g, resident_learn_bytes(g, rs));
         if (rc == SSSP_OK) rc = resident_learn(g, rs, s, source, a.mlp_w, a.wm, dist_out, g->res, &stage, &staged);
-        if (rc) return rc;
+        if (rc && rc != SSSP_ERR_OOM) return rc;
+        rc = SSSP_OK;
     }
     if (!staged)
         hipLaunchKernelGGL(k_init_state, dim3(ib), dim3(256), 0, s, g->n, source, a.b.dist, a.b.st, a.b.phase_of,
@@ -3200,7 +3201,16 @@ static int solve_common(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     return rc;
 }
 
-// The graph's scratch for resident solves and batches, kept between them.
+// A solve by the phase kernels. They need no resident scratch: what the graph holds of it goes when
+// their own buffers do not fit.
+template <typename... A>
+static int solve_common(sssp_graph *g, A... args) {
+    const int rc = solve_phased(g, args...);
+    return rc == SSSP_ERR_OOM && resident_release(g) ? solve_phased(g, args...) : rc;
+}
+
+// The graph's scratch for resident solves and batches, kept between them. Without the memory for it
+// (SSSP_ERR_OOM) callers use the kernels that need none.
 int resident_scratch(sssp_graph *g, uint64_t bytes) {
     if (g->res_bytes >= bytes) return SSSP_OK;
     sssp_free(g->res);
@@ -3211,9 +3221,18 @@ int resident_scratch(sssp_graph *g, uint64_t bytes) {
     return SSSP_OK;
 }
 
-// A resident solve where the graph and the launch options allow one, with the graph's scratch
-// (kept between solves). *ran = false: not run, or not finished; the phase kernels then do it
-// (they also do timed solves: per-kernel timing is about them).
+// Gives that scratch back; true if there was any.
+bool resident_release(sssp_graph *g) {
+    if (!g || !g->res) return false;
+    sssp_free(g->res);
+    g->res = nullptr;
+    g->res_bytes = 0;
+    return true;
+}
+
+// A resident solve where the graph, its launch options and the memory left allow one, with the
+// graph's scratch (kept between solves). *ran = false: not run, or not finished; the phase kernels
+// then do it (they also do timed solves: per-kernel timing is about them).
 int resident_try(sssp_graph *g, uint32_t source, int in, int out, uint64_t delta, uint64_t *dist_out,
                  uint32_t *phases_out, bool *ran) {
     *ran = false;
@@ -3226,7 +3245,7 @@ int resident_try(sssp_graph *g, uint32_t source, int in, int out, uint64_t delta
         if (rc == SSSP_OK) rc = solve_bufs_ensure(g, true, false, false);
     }
     if (rc == SSSP_OK) rc = resident_scratch(g, r.bytes);
-    if (rc) return rc;
+    if (rc) return rc == SSSP_ERR_OOM ? SSSP_OK : rc;
     uint32_t phases = 0;
     rc = resident_solve(g, r, g->stream, source, in, out, delta, dist_out, g->res, &phases, ran);
     if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
@@ -3243,7 +3262,11 @@ extern "C" int sssp_solve(sssp_graph *g, uint32_t source, uint32_t criterion, ui
             if (source >= g->n) return sssp_set_error(SSSP_ERR_INVALID, "source %u >= n = %u", source, g->n);
             HIP_OK(hipSetDevice(g->device));
             // the whole solve in one workgroup (the batched kernel)
-            if (g->cfg.single && static_modes(in, out)) return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
+            if (g->cfg.single && static_modes(in, out)) {
+                const int rc = batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
+                if (rc != SSSP_ERR_OOM || !resident_release(g)) return rc;
+                return batch_solve_one(g, source, in, out == OUT_STATIC_M, dist_out, phases_out);
+            }
             bool ran = false;
             const int rc = resident_try(g, source, in, out, 0, dist_out, phases_out, &ran);
             if (rc || ran) return rc;

@@ -1572,7 +1572,7 @@ static uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
 bool resident_batch_takes(const sssp_graph *g) { return g->n <= (uint64_t)kGang * kWgVertices; }
 
 // Solves the queries ids[0 .. nq) (each of a graph that resident_batch_takes) in one cooperative
-// launch on graphs[0]'s stream and scratch. *ran = false: as in resident_solve.
+// launch on graphs[0]'s stream and scratch. *ran = false: as in resident_solve, or no memory for it.
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
                    bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran) {
     *ran = false;
@@ -1632,7 +1632,7 @@ int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uin
                    o_mark = up256(o_box + blocks * wgv * 16), total = o_mark + blocks * 2 * slots;
     // kept on graphs[0]: allocating and freeing it took 0.4 to 8 ms a call
     const int rc = resident_scratch(graphs[0], total);
-    if (rc) return rc;
+    if (rc) return rc == SSSP_ERR_OOM ? SSSP_OK : rc;
     uint8_t *base = (uint8_t *)graphs[0]->res;
     std::vector<uint8_t> up(o_heads);
     ResQuery *hq = (ResQuery *)up.data();

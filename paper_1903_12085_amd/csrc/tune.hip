@@ -47,7 +47,9 @@ extern "C" int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion,
     if (!g) return sssp_set_error(SSSP_ERR_INVALID, "graph is NULL");
     if (source >= g->n) return sssp_set_error(SSSP_ERR_INVALID, "source %u >= n", source);
     uint64_t *dist = nullptr;
-    HIP_OK(sssp_malloc(&dist, (uint64_t)g->n * sizeof(uint64_t)));
+    hipError_t e = sssp_malloc(&dist, (uint64_t)g->n * sizeof(uint64_t));
+    if (e == hipErrorOutOfMemory && resident_release(g)) e = sssp_malloc(&dist, (uint64_t)g->n * sizeof(uint64_t));
+    HIP_OK(e);
     const int cus = device_cus();
     const uint64_t quads = ((uint64_t)g->n + 3) / 4;
     int in = IN_NONE, out = OUT_NONE;

@@ -23,6 +23,7 @@ void host_reset(size_t limit) {
     g_log.clear();
     g_coop = hipSuccess;
     g_report = false;
+    g_verdict[0] = g_verdict[1] = g_at = 0;
     g_fail_events = 0;
 }
 size_t host_used() { return g_used; }

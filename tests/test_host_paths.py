@@ -59,12 +59,12 @@ class Host:
     def delta(self):
         return self.lib.sssp_delta_step(self.h, 0, 100, ptr(self.dist), ctypes.byref(self.phases))
 
-    def batch(self, nq=2):
+    def batch(self, nq=2, shape=(0, 0, 0, 0, 0)):
         hs = (ctypes.c_void_p * nq)(*[self.h.value] * nq)
         ds = [np.zeros(self.n, np.uint64) for _ in range(nq)]
         outs = (ctypes.c_void_p * nq)(*[ptr(d).value for d in ds])
         src = np.zeros(nq, np.uint32)
-        return self.lib.sssp_solve_batch(hs, ptr(src), nq, STATIC_OR, outs, None)
+        return self.lib.sssp_solve_batch_ex(hs, ptr(src), nq, STATIC_OR, outs, None, (ctypes.c_uint32 * 5)(*shape))
 
     def learned(self):
         w, sel, none = np.zeros(5382, np.float32), ctypes.c_void_p(), ctypes.c_void_p()
@@ -130,9 +130,8 @@ def one_workgroup(lib, g):
     return g.solve()
 
 
-def batch_shape(lib, g):
-    h, src, out = (ctypes.c_void_p * 1)(g.h.value), np.zeros(1, np.uint32), (ctypes.c_void_p * 1)(ptr(g.dist).value)
-    return lib.sssp_solve_batch_ex(h, ptr(src), 1, STATIC_OR, out, None, (ctypes.c_uint32 * 5)(256, 0, 0, 0, 0))
+def batch_shape(lib, g, nq=1):
+    return g.batch(nq, (256, 0, 0, 0, 0))
 
 
 def traced(lib, g):
@@ -180,3 +179,50 @@ def test_kept_block_is_given_back_whichever_allocation_fails(lib, name):
         assert rc == expect, (i, rc, msg)
         assert log.count("oom") == 1, (i, log[:20])
     lib.sssp_graph_destroy(None)
+
+
+def phase_kernels(lib, g):
+    cfg = (ctypes.c_uint32 * 6)()
+    lib.sssp_get_launch(g.h, cfg)
+    cfg[5] = 2
+    assert lib.sssp_set_launch(g.h, cfg) == OK
+
+
+# the call, and the same work by kernels without resident scratch
+WITHOUT = {"static": (ALLOCATING["static"], phase_kernels, ALLOCATING["static"]),
+           "simple": (ALLOCATING["simple"], phase_kernels, ALLOCATING["simple"]),
+           "delta": (ALLOCATING["delta"], phase_kernels, ALLOCATING["delta"]),
+           "learned": (ALLOCATING["learned"], phase_kernels, ALLOCATING["learned"]),
+           "batch": (lambda lib, g: g.batch(), lambda lib, g: None, lambda lib, g: batch_shape(lib, g, 2)),
+           "single": (lambda lib, g: g.batch(1), lambda lib, g: None, batch_shape),
+           "one_workgroup": (one_workgroup, lambda lib, g: None, one_workgroup),
+           "traced": (traced, lambda lib, g: None, traced)}
+
+
+@pytest.mark.parametrize("name", list(WITHOUT))
+@pytest.mark.parametrize("held", [False, True])
+def test_no_memory_for_resident_scratch_is_no_refusal(lib, name, held):
+    """With the memory that the other kernels need and no more, and (held) with scratch on the handle from
+    an earlier resident solve: the call is served by them."""
+    call, choose, other = WITHOUT[name]
+    lib.host_reset(1 << 40)
+    lib.sssp_graph_destroy(None)
+    g = Host(lib, 4000, 9000)
+    choose(lib, g)
+    lib.host_reset(1 << 40)
+    expect, need = other(lib, g), lib.host_peak()
+    g.close()
+    assert expect in (OK, INTERNAL) and need > 0
+    g = Host(lib, 4000, 9000)
+    base = lib.host_used()
+    if held:
+        assert g.solve() == OK
+        assert lib.host_used() > base
+    lib.host_reset(base + need)
+    rc = call(lib, g)
+    assert rc != OOM, g.message()
+    if name in (("one_workgroup", "traced", "batch") if held else ("simple", "learned", "batch", "single")):
+        assert "oom" in g.log()
+    assert rc == expect or name in ("static", "simple", "delta", "learned"), (rc, g.message())
+    lib.host_reset(1 << 40)
+    g.close()
