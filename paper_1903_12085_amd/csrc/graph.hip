@@ -384,7 +384,12 @@ extern "C" int sssp_graph_create(uint32_t n, uint64_t m, const uint64_t *row_ptr
     g->stream = (hipStream_t)hip_stream;
     if (hipGetDevice(&g->device) != hipSuccess) { delete g; return sssp_set_error(SSSP_ERR_DEVICE, "no HIP device"); }
     int rc = create_impl(n, m, row_ptr, col, weight, device_ptrs, g->stream, g);
-    if (rc != SSSP_OK) { sssp_graph_destroy(g); return rc; }
+    if (rc != SSSP_OK) {
+        // what was queued before the failure may write to the block, which the next graph can get
+        if (g->base) (void)hipStreamSynchronize(g->stream);
+        sssp_graph_destroy(g);
+        return rc;
+    }
     graph_default_cfg(g);
     *out = g;
     return SSSP_OK;

@@ -226,3 +226,26 @@ def test_no_memory_for_resident_scratch_is_no_refusal(lib, name, held):
     assert rc == expect or name in ("static", "simple", "delta", "learned"), (rc, g.message())
     lib.host_reset(1 << 40)
     g.close()
+
+
+@pytest.mark.parametrize("what", ["staging", "event"])
+def test_failed_creation_waits_before_its_block_is_kept(lib, what):
+    """Creation that fails after work was queued on its block: the block may serve the next graph, on
+    another stream, so that work has to be over."""
+    lib.host_reset(1 << 40)
+    lib.sssp_graph_destroy(None)
+    n, m = 1 << 20, 6 << 20
+    base = lib.host_used()
+    whole = Host(lib, n, m)
+    block = lib.host_used() - base
+    whole.close()
+    lib.sssp_graph_destroy(None)
+    lib.host_reset(lib.host_used() + block + (MiB if what == "staging" else 1 << 30))
+    lib.host_fail_events(1 if what == "event" else 0)
+    failed = Host(lib, n, m)
+    assert failed.rc == (OOM if what == "staging" else DEVICE)
+    log = failed.log()
+    queued = max(i for i, x in enumerate(log) if x in ("set", "kernel"))
+    assert "wait" in log[queued:], log
+    lib.host_reset(1 << 40)
+    lib.sssp_graph_destroy(None)
