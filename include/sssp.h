@@ -268,6 +268,23 @@ int sssp_solve_oracle(sssp_graph *g, uint32_t source, const uint64_t *dist_ref, 
 int sssp_solve_approx(sssp_graph *g, uint32_t source, uint32_t criterion, uint32_t k, uint64_t *dist_out,
                       sssp_stats *stats, uint32_t *phase_of, sssp_phase_rec *trace, uint32_t trace_cap);
 
+/* Which kernels served the last solve on g that succeeded: SSSP_FORM_RESIDENT the
+ * resident solve (of a checkpoint solve its static phases), SSSP_FORM_PHASES the
+ * kernels of one phase each, SSSP_FORM_WORKGROUPS a persistent workgroup or team
+ * per query. Of a batch graphs[0] tells; SSSP_FORM_WORKGROUPS if any query needed
+ * them. */
+#define SSSP_FORM_NONE 0u
+#define SSSP_FORM_PHASES 1u
+#define SSSP_FORM_RESIDENT 2u
+#define SSSP_FORM_WORKGROUPS 3u
+int sssp_last_form(const sssp_graph *g, uint32_t *form);
+
+/* How often a workgroup of a resident solve on g (of a batch: graphs[0]) looks for
+ * another before all give up and other kernels do the solve: the device may be
+ * shared with work that keeps them apart. 0, the default: 2^21 times, about a
+ * second. Answers never depend on it. */
+int sssp_set_wait_limit(sssp_graph *g, uint32_t polls);
+
 /* Turn per-kernel event timing on (enable != 0) or off for later solves on g. */
 int sssp_profile_enable(sssp_graph *g, int enable);
 

@@ -34,7 +34,9 @@ SYMBOLS = ["sssp_graph_create", "sssp_graph_destroy", "sssp_set_stream", "sssp_g
            "sssp_solve_learned", "sssp_delta_step_learned", "sssp_trace_learned",
            "sssp_solve_learned_commit", "sssp_measure_atomic_min", "sssp_solve_switch",
            "sssp_solve_learned_switch", "sssp_solve_approx", "sssp_solve_noalloc",
-           "sssp_solve_schedule", "sssp_solve_learned_checkpoint"]
+           "sssp_solve_schedule", "sssp_solve_learned_checkpoint", "sssp_last_form", "sssp_set_wait_limit"]
+
+FORMS = ["none", "phases", "resident", "workgroups"]  # SSSP_FORM_*
 
 ERRORS = {-1: "SSSP_ERR_INVALID", -2: "SSSP_ERR_OOM", -3: "SSSP_ERR_DEVICE", -4: "SSSP_ERR_UNSUPPORTED",
           -5: "SSSP_ERR_INTERNAL"}
@@ -116,6 +118,8 @@ def load(path: str = LIB_PATH):
     lib.sssp_profile_phases.argtypes = [P, P, u32, ctypes.POINTER(ctypes.c_uint32)]
     lib.sssp_get_launch.argtypes = [P, ctypes.POINTER(LaunchCfg)]
     lib.sssp_set_launch.argtypes = [P, ctypes.POINTER(LaunchCfg)]
+    lib.sssp_last_form.argtypes = [P, ctypes.POINTER(u32)]
+    lib.sssp_set_wait_limit.argtypes = [P, u32]
     lib.sssp_solve_batch_ex.argtypes = [P, P, u32, u32, P, P, ctypes.POINTER(BatchCfg)]
     lib.sssp_batch_set_config.argtypes = [ctypes.POINTER(BatchCfg)]
     lib.sssp_batch_get_config.argtypes = [ctypes.POINTER(BatchCfg)]
@@ -210,6 +214,16 @@ class DeviceGraph:
         p = KernelProfile()
         _check(load().sssp_profile_get(self._h, ctypes.byref(p)))
         return p.as_dict()
+
+    def last_form(self) -> str:
+        """Which kernels served the last solve (one of FORMS)."""
+        f = ctypes.c_uint32(0)
+        _check(load().sssp_last_form(self._h, ctypes.byref(f)))
+        return FORMS[f.value]
+
+    def set_wait_limit(self, polls: int):
+        """sssp_set_wait_limit: how long resident workgroups wait for one another (0: the default)."""
+        _check(load().sssp_set_wait_limit(self._h, polls))
 
     def phase_times(self) -> np.ndarray:
         """Per-phase kernel milliseconds of the last phased solve run with profile(True)."""

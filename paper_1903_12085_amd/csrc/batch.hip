@@ -704,6 +704,7 @@ int batch_solve_one(sssp_graph *g, uint32_t source, int in, bool out_static, uin
     HIP_OK(hipMemcpyAsync(&r, d, sizeof r, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     if (r.ctl.error) return sssp_set_error(SSSP_ERR_INTERNAL, "the query exceeded its phase bound");
+    g->form = SSSP_FORM_WORKGROUPS;
     if (phases_out) *phases_out = r.phases;
     return SSSP_OK;
 }
@@ -846,6 +847,7 @@ done:
 #undef TRY
     sssp_free(st); sssp_free(fl); sssp_free(fm); sssp_free(dq); sssp_free(dorder); sssp_free(dph); sssp_free(dctl);
     sssp_free(dlarge); sssp_free(dteams);
+    if (rc == SSSP_OK) g0->form = SSSP_FORM_WORKGROUPS;
     return rc;
 }
 
@@ -953,6 +955,7 @@ extern "C" int sssp_solve_batch_ex(sssp_graph *const *graphs, const uint32_t *so
         HIP_OK(hipSetDevice(graphs[0]->device));
         std::vector<uint32_t> left;
         const int rc = batch_default(graphs, sources, nq, in, out == OUT_STATIC_M, dist_outs, phases_out, &left);
+        if (rc == SSSP_OK && left.empty()) graphs[0]->form = SSSP_FORM_RESIDENT;
         if (rc || left.empty()) return rc;
         if (left.size() < nq) {
             std::vector<sssp_graph *> lg;

@@ -48,6 +48,8 @@ struct sssp_graph {
     uint32_t *one_fl = nullptr;    // two fringe lists and the settled list, 3 * n
     uint2 *one_fm = nullptr;       // (minIn, minOut) of the two fringe lists' entries, 2 * n
     void *one_aux = nullptr;       // query record, order, phase count, work-queue control
+    uint32_t wait_polls = 0;       // longest wait of a resident workgroup (0: the default)
+    uint32_t form = SSSP_FORM_NONE;  // what served the last solve
     // resident solves: barrier words and group marks
     void *res = nullptr;
     uint64_t res_bytes = 0;

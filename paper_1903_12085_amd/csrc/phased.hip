@@ -3198,6 +3198,7 @@ static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) rc = sssp_set_error(SSSP_ERR_DEVICE, "trace copy failed: %s", hipGetErrorString(e));
     }
+    if (rc == SSSP_OK) g->form = staged ? SSSP_FORM_RESIDENT : SSSP_FORM_PHASES;
     return rc;
 }
 
@@ -3248,7 +3249,10 @@ int resident_try(sssp_graph *g, uint32_t source, int in, int out, uint64_t delta
     if (rc) return rc == SSSP_ERR_OOM ? SSSP_OK : rc;
     uint32_t phases = 0;
     rc = resident_solve(g, r, g->stream, source, in, out, delta, dist_out, g->res, &phases, ran);
-    if (rc == SSSP_OK && *ran && phases_out) *phases_out = phases;
+    if (rc == SSSP_OK && *ran) {
+        g->form = SSSP_FORM_RESIDENT;
+        if (phases_out) *phases_out = phases;
+    }
     return rc;
 }
 
@@ -3317,6 +3321,18 @@ extern "C" int sssp_solve_approx(sssp_graph *g, uint32_t source, uint32_t criter
                                  uint32_t trace_cap) {
     return solve_common(g, source, false, criterion, nullptr, 0, dist_out, stats, phase_of, trace, trace_cap,
                         nullptr, nullptr, nullptr, nullptr, 0, nullptr, &k);
+}
+
+extern "C" int sssp_set_wait_limit(sssp_graph *g, uint32_t polls) {
+    if (!g) return sssp_set_error(SSSP_ERR_INVALID, "graph is NULL");
+    g->wait_polls = polls;
+    return SSSP_OK;
+}
+
+extern "C" int sssp_last_form(const sssp_graph *g, uint32_t *form) {
+    if (!g || !form) return sssp_set_error(SSSP_ERR_INVALID, "NULL argument");
+    *form = g->form;
+    return SSSP_OK;
 }
 
 extern "C" int sssp_profile_enable(sssp_graph *g, int enable) {
@@ -3530,6 +3546,7 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
         rc = resident_solve(g, r, g->stream, source, in, out, 0, dist_out, base, &phases, &ran);
         if (rc) return rc;
         if (ran) {
+            g->form = SSSP_FORM_RESIDENT;
             if (phases_out) *phases_out = phases;
             return SSSP_OK;
         }
@@ -3580,6 +3597,7 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
     if (shard_sum(reached) != h.settled)
         return sssp_set_error(SSSP_ERR_INTERNAL, "solve ended in an inconsistent state (reached=%llu settled=%llu)",
                               shard_sum(reached), h.settled);
+    g->form = SSSP_FORM_PHASES;
     if (phases_out) *phases_out = h.phases;
     return SSSP_OK;
 }

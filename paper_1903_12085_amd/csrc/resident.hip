@@ -81,7 +81,7 @@ constexpr uint32_t kShareEdges = 256;  // edges of a shared record (more for a h
 constexpr uint32_t kShareCap = 1024;   // shared records per workgroup and phase
 constexpr uint32_t kShareDeg = 128;    // graphs with a longer row share records (see `share` in ResArgs)
 constexpr uint32_t kQuota = 64;        // segments a list takes in a phase before further rows are shared
-constexpr uint32_t kResSpin = 1u << 21;
+constexpr uint32_t kResSpin = 1u << 21;  // polls of a wait (about 0.5 us each) before all give up
 
 // Learned checkpoint solves.
 struct ResLearn {
@@ -119,6 +119,7 @@ struct ResArgs {
     uint32_t share;      // rows beyond the quota become records relaxed by all workgroups
     uint32_t lgK;        // vertices per group
     uint32_t max_phases; // a solve that takes more ends with an error
+    uint32_t polls;      // of a wait for another workgroup
     unsigned long long delta;  // Delta-stepping: bucket width
     // SIMPLE criteria: the reverse adjacency and, per vertex, the lightest edge of each row whose other
     // end had not settled when the owner last looked, with its place in the row
@@ -465,7 +466,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
                         pm = ld64(w);
                         if (OUT) pt2 = ld64(w + 1);
                         if ((pm & kTag) == tag && (!OUT || (pt2 & kTag) == tag)) break;
-                        if (++spins >= kResSpin) {
+                        if (++spins >= a.polls) {
                             atomicOr(&s_flags, 1u);
                             break;
                         }
@@ -951,7 +952,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             if (tid < W) {
                 uint32_t spins = 0;
                 unsigned long long v;
-                while (!count_is_for(v = ld64(&bar_b[tid * kSlotStride]), nb) && ++spins < kResSpin) {}
+                while (!count_is_for(v = ld64(&bar_b[tid * kSlotStride]), nb) && ++spins < a.polls) {}
                 s_sh[tid] = (uint32_t)v;
                 if (!count_is_for(v, nb)) atomicOr(&s_flags, 1u);
                 else if ((uint32_t)v) atomicOr(&s_flags, 2u);
@@ -1044,7 +1045,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
                 pm = ld64(w);
                 if (OUT) pt2 = ld64(w + 1);
                 if ((pm & kTag) == tag && (!OUT || (pt2 & kTag) == tag)) break;
-                if (++spins >= kResSpin) {
+                if (++spins >= a.polls) {
                     atomicOr(&s_flags, 1u);
                     break;
                 }
@@ -1108,7 +1109,7 @@ __global__ __launch_bounds__(BS) void k_resident(ResArgs a, ResCtl *ctl, uint32_
             const uint32_t r = atomicAdd(&ctl->rank[x * 32], 1u);
             if (r == a.W - 1) atomicCAS(&ctl->team, 0u, x + 1);
             uint32_t t = 0, spins = 0;
-            while (!(t = __hip_atomic_load(&ctl->team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < kResSpin)
+            while (!(t = __hip_atomic_load(&ctl->team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) && ++spins < a.polls)
                 __builtin_amdgcn_s_sleep(1);
             if (!t) atomicOr(a.error, 1u);
             s_wg = t == x + 1 && r < a.W ? r : INF32;
@@ -1281,6 +1282,7 @@ static ResArgs resident_args(const sssp_graph *g, const ResShape &r, uint32_t so
     a.quota = kQuota;
     a.n = g->n;
     a.max_phases = g->n;  // a phase settles at least the queue minimum
+    a.polls = g->wait_polls ? g->wait_polls : kResSpin;
     a.m = g->m;
     a.src = source;
     a.wmax = g->wmax;
@@ -1439,6 +1441,7 @@ struct ResBatch {
     unsigned long long *rec, *box;    // per workgroup: kShareCap records, 2 * wgv boxes
     uint8_t *mark;                    // per workgroup: 2 * slots
     uint32_t wgv, slots;
+    uint32_t polls;                   // as in ResArgs
 };
 
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
@@ -1473,7 +1476,7 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
                     if (W > 1) st_agent(qword, ((unsigned long long)turn << 32) | q);
                 } else {
                     unsigned long long x = 0;
-                    for (uint32_t spins = 0; spins < kResSpin; ++spins) {
+                    for (uint32_t spins = 0; spins < b.polls; ++spins) {
                         x = ld64(qword);
                         if ((uint32_t)(x >> 32) == turn) { q = (uint32_t)x; break; }
                         __builtin_amdgcn_s_sleep(1);
@@ -1512,6 +1515,7 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
             a.lgK = 3;
             a.quota = kQuota;
             a.max_phases = a.n;
+            a.polls = b.polls;
             a.delta = 0;
             const uint32_t groups = (a.n - 1) / K + 1;
             a.wslots = 64 * ((groups - 1) / (W * BS) + 1);
@@ -1541,8 +1545,8 @@ __global__ __launch_bounds__(kBatchBs, 4) void k_resident_batch(ResBatch b) {
                 ++nb;
                 if (tid < W) {
                     uint32_t spins = 0;
-                    while ((ld64(&words[tid * kSlotStride]) & kTag) != tag && ++spins < kResSpin) {}
-                    if (spins >= kResSpin) s_bad = 1;
+                    while ((ld64(&words[tid * kSlotStride]) & kTag) != tag && ++spins < b.polls) {}
+                    if (spins >= b.polls) s_bad = 1;
                 }
                 __syncthreads();
                 if (s_bad) {  // block-uniform
@@ -1655,6 +1659,7 @@ int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uin
     b.mark = base + o_mark;
     b.wgv = wgv;
     b.slots = slots;
+    b.polls = graphs[0]->wait_polls ? graphs[0]->wait_polls : kResSpin;
     const size_t lds = res_lds(slots, kBatchBs);
     if (lds > 65536) HIP_OK(hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *args[] = {&b};

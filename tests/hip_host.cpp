@@ -19,6 +19,7 @@ static int g_fail_events;
 extern "C" {
 void host_reset(size_t limit) {
     g_limit = limit;
+    g_last = hipSuccess;
     g_base = g_peak = g_used;
     g_log.clear();
     g_coop = hipSuccess;

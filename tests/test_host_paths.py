@@ -249,3 +249,20 @@ def test_failed_creation_waits_before_its_block_is_kept(lib, what):
     assert "wait" in log[queued:], log
     lib.host_reset(1 << 40)
     lib.sssp_graph_destroy(None)
+
+
+@pytest.mark.parametrize("name", list(SOLVES))
+def test_launch_that_does_not_fit_falls_back(lib, name):
+    """The device cannot hold the workgroups at once (error 720): the other kernels are launched. Here they
+    do nothing, so that all but the batch end in their phase bound."""
+    g = Host(lib)
+    lib.host_reset(1 << 40)
+    lib.host_coop(720, 0, 0, 0)
+    rc = SOLVES[name](g)
+    assert rc == (OK if name == "batch" else INTERNAL), g.message()
+    assert "terminate" in g.message() or rc == OK
+    assert "kernel" in g.log()[g.log().index("coop"):]
+    lib.host_reset(1 << 40)
+    form = ctypes.c_uint32(9)
+    assert lib.sssp_last_form(g.h, ctypes.byref(form)) == OK and form.value == (3 if name == "batch" else 0)
+    g.close()
