@@ -392,7 +392,8 @@ def bench_learned(B, torch, G, dg, src, m_reach, plain_ms):
     the headline graph and on the held-out evaluation graphs (random 2^23, R-MAT 23, grid 4096^2):
     the network-only checkpoint solve against the plain static solve, the hand-set switch and the
     stronger criteria from the start; the per-phase learned solve; learned Delta-stepping against
-    every fixed width. Distances of every learned form are checked against the plain solver's."""
+    every fixed width, all on the phase kernels; the plain static and the checkpoint solve also with
+    the default launch options (*_default: resident). Distances of every learned form are checked against the plain solver's."""
     from paper_1903_12085_amd import selector as S
     sel = S.load_trained()
     res = {"weights": "selector_weights.npy (trained on random 2^16..2^21, R-MAT 16..20, grids 256^2..1024^2; "

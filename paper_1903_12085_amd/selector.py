@@ -15,10 +15,13 @@ labelled X* if 16 (j + 2) >= c*, else 0 (all 0 when no schedule beats the plain 
 label is the choice that leads to the fastest remaining solve among those that switch at or after
 it. The checkpoint features come from a checkpoint solve whose network always answers 0. For
 Delta-stepping, every bucket start of a graph is labelled with the width (2^12, 2^14 or 2^16) whose
-fixed run was fastest on that graph.
+fixed run was fastest on that graph. All of these times are of the phase kernels, the only ones that
+run every criterion and schedule: by them a switch pays; the resident solve that sssp_solve takes by
+default is faster on random graphs than any schedule.
 """
 from __future__ import annotations
 
+import contextlib
 import os
 import time
 
@@ -72,15 +75,32 @@ def candidate_checkpoints(phases: int, most: int = 24) -> list:
     return [int(x) for x in pts]
 
 
+@contextlib.contextmanager
+def phase_kernels(dg):
+    """Solves on dg run the phase kernels within, whatever resident form they have (launch option
+    `single` = 2): the one kind of kernels that every criterion, the schedules, switched and learned
+    solves have, so that what is compared is the choice of the criterion and not the kernels."""
+    keep = dg.launch()["single"]
+    dg.set_launch(single=2)
+    try:
+        yield
+    finally:
+        dg.set_launch(single=keep)
+
+
 def measure(dg, src: int, reps: int = 2) -> dict:
     """Plain static time and phases, the checkpoint features of the static solve, the times of the
-    two-stage schedules at the candidate checkpoints, and the fixed Delta-stepping times. The static
-    time is solve_ex's, which runs the phase kernels that the learned solves and schedules run:
-    sssp_solve's resident kernel is faster than any of them, whatever the criterion chosen."""
+    two-stage schedules at the candidate checkpoints, and the fixed Delta-stepping times, all on the
+    phase kernels."""
+    with phase_kernels(dg):
+        return _measure(dg, src, reps)
+
+
+def _measure(dg, src: int, reps: int) -> dict:
     dist = B.new_dist(dg.n)
     static = B.STATIC_OR
-    t_static = _timed(lambda: B.solve_ex(dg, src, static, dist), reps)
-    phases = B.solve_ex(dg, src, static, dist).phases
+    t_static = _timed(lambda: B.solve(dg, src, static, dist), reps)
+    phases = B.solve(dg, src, static, dist).phases
     r, feat = B.solve_checkpoint(dg, src, B.Selector(constant_weights(0)), dist, trace_cap=phases // 16 + 2,
                                  features=True)
     if r.phases != phases:
@@ -194,10 +214,12 @@ SWITCH = (B.IN_SIMPLE | B.OUT_STATIC, 1, 2)
 
 
 def evaluate(sel, dg, src: int, reps: int = 2, per_phase: bool = True) -> dict:
-    """On one graph (times in ms, best of reps): the network-only checkpoint solve against the plain
-    static solve on the same phase kernels (solve_ex), the hand-set switch (SWITCH) and the two stronger criteria from the start; the
-    per-phase learned solve and learned Delta-stepping against the fixed widths. The switch phase
-    of the checkpoint solve comes from one more, traced run (tracing is outside the timed runs)."""
+    """On one graph (times in ms, best of reps), all on the phase kernels: the network-only checkpoint
+    solve against the plain static solve, the hand-set switch (SWITCH) and the two stronger criteria
+    from the start; the per-phase learned solve and learned Delta-stepping against the fixed widths.
+    The switch phase of the checkpoint solve comes from one more, traced run (tracing is outside the
+    timed runs). The *_default entries are the plain static and the checkpoint solve as a call with the
+    default launch options runs them, which is resident (of the checkpoint solve the static phases)."""
     dist = B.new_dist(dg.n)
     res = {}
 
@@ -207,7 +229,19 @@ def evaluate(sel, dg, src: int, reps: int = 2, per_phase: bool = True) -> dict:
         res[name + "_phases"] = box[-1].phases
         return box[-1]
 
-    t("static_or", lambda: B.solve_ex(dg, src, B.STATIC_OR, dist))
+    with phase_kernels(dg):
+        _evaluate(sel, dg, src, reps, per_phase, dist, res, t)
+    keep = dg.launch()["single"]
+    dg.set_launch(single=0)
+    t("static_or_default", lambda: B.solve(dg, src, B.STATIC_OR, dist))
+    t("checkpoint_default", lambda: B.solve_checkpoint(dg, src, sel, dist))
+    dg.set_launch(single=keep)
+    res["checkpoint_over_static_default"] = res["checkpoint_default_ms"] / res["static_or_default_ms"]
+    return res
+
+
+def _evaluate(sel, dg, src, reps, per_phase, dist, res, t):
+    t("static_or", lambda: B.solve(dg, src, B.STATIC_OR, dist))
     t("hand_switch", lambda: B.solve_switch(dg, src, B.STATIC_OR, SWITCH[0], SWITCH[1:], dist))
     t("simple_or", lambda: B.solve(dg, src, B.SIMPLE_OR, dist))
     t("in_simple_out_static", lambda: B.solve(dg, src, B.CHOICE_CRIT[2], dist))
@@ -224,7 +258,6 @@ def evaluate(sel, dg, src: int, reps: int = 2, per_phase: bool = True) -> dict:
         res["delta_%d_ms" % delta] = 1e3 * _timed(lambda: B.delta_step(dg, src, delta, dist), reps)
     res["checkpoint_over_static"] = res["checkpoint_ms"] / res["static_or_ms"]
     res["checkpoint_over_hand_switch"] = res["checkpoint_ms"] / res["hand_switch_ms"]
-    return res
 
 
 WEIGHTS_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "selector_weights.npy")
