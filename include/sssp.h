@@ -178,7 +178,8 @@ int sssp_delta_step_ex(sssp_graph *g, uint32_t source, const uint64_t *deltas, u
  * graph, or a query alone, is solved on the whole device as by sssp_solve, one
  * after the other. Many large graphs, large graphs of many phases (grids) from
  * three on, and graphs of more than 2^24 vertices run with the whole batch as
- * with a launch shape given (see sssp_batch_cfg).
+ * with a launch shape given (see sssp_batch_cfg); so do queries of many phases,
+ * or all, when more of them are given than teams fit and that is faster.
  * Device scratch: about 16 bytes per vertex that the workgroups hold (at most
  * 16384 each, 150 MB in all) or of the largest graph, kept on graphs[0]; with a
  * launch shape given about 29 bytes per vertex of each query, freed before

@@ -861,8 +861,86 @@ static int batch_launch(sssp_graph *const *graphs, const uint32_t *sources, uint
     return released ? batch_once(graphs, sources, nq, in, out_static, dist_outs, phases_out, cfg, g0) : rc;
 }
 
-// The default form: queries of graphs that a resident team takes run on teams, larger ones and a query
-// alone on the whole device, one after the other. *left: the queries that were not solved.
+// Of the queries that resident teams take, *ids, moves those to *left which the launch above serves
+// better. A team holds 1 to 32 of the 512 workgroups that fit at once, the launch a query on each of
+// 1024 (graphs of 2^20 edges, on teams of its own, apart). Solves of few phases gain from teams at
+// any number (random and R-MAT queries of the batch below: 25 ms and 126), and so do those of many
+// phases (resident_probe) while all fit at once (32 grids of 250 k vertices 28 ms and 36); more wait
+// for one another (192 such grids 154 ms and 41, 512 of 47 k 34 and 13). Three ways are compared by
+// what was measured: all on teams; those of many phases left to the launch, the others on teams
+// before it; or all left to it. A grid solve takes about 7 sqrt(n) phases of 6.5 us on a team
+// while the device is full and of 8.5 us in the launch; at full load the launch takes 0.13 ns an edge
+// of sparse graphs and 0.1 of denser ones, teams 0.13 and 0.035. 512 queries of 64 graphs up to 2^18
+// vertices, a third grids: 76 ms on teams, 129 in the launch, 64 split.
+static int batch_split(sssp_graph *const *graphs, const uint32_t *sources, std::vector<uint32_t> *ids,
+                       std::vector<uint32_t> *left) {
+    int dev = 0, cus = 0;
+    HIP_OK(hipGetDevice(&dev));
+    HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const double room = 2.0 * cus;
+    std::vector<uint32_t> asked, many;
+    double wgs = 0;
+    for (uint32_t i : *ids) {
+        const uint32_t c = resident_batch_class(graphs[i]);
+        wgs += 1u << c;
+        if (c > 0) asked.push_back(i);  // up to 16384 vertices a single workgroup is never slower
+    }
+    if (wgs <= room || asked.empty()) return SSSP_OK;
+    const int rc = resident_probe(graphs, sources, asked, &many);
+    if (rc == SSSP_ERR_OOM) return SSSP_OK;  // nor will there be memory for the teams
+    if (rc) return rc;
+    // us: queries of many phases on teams (and the largest of them alone, in rounds) and in the launch
+    // (the longest, and the work of all); work of the others in the launch and on teams
+    double teams_many = 0, longest = 0, top_wgs = 0, launch_many = 0, launch_few = 0, teams_few = 0;
+    std::vector<uint32_t> slow, few;
+    // random graphs of degree 2 and up to 2^16 vertices are even on teams while few, and 6 to 14 % slower
+    // past 4 times the room (2048 of 17 k vertices 9.9 ms and 8.7; 256 of 132 k 17.2 and 17.2)
+    auto thin = [&](const sssp_graph *g) { return g->m < 3ull * g->n && g->n <= (1u << 16); };
+    double thin_wgs = 0;
+    for (size_t j = 0; j < asked.size(); ++j)
+        if (!many[j] && thin(graphs[asked[j]])) thin_wgs += 1u << resident_batch_class(graphs[asked[j]]);
+    size_t a = 0;
+    for (uint32_t i : *ids) {
+        const sssp_graph *g = graphs[i];
+        const bool on_team = a < asked.size() && asked[a] == i, is_many = on_team && many[a++];
+        const bool sparse = g->m < 6ull * g->n;
+        if (on_team && !is_many && thin(g) && thin_wgs >= 4 * room) {
+            slow.push_back(i);
+            teams_many += 1.45e-4 * (double)g->m;
+            launch_many += 1.3e-4 * (double)g->m;
+            continue;
+        }
+        (is_many ? slow : few).push_back(i);
+        if (is_many) {
+            const double phases = 7 * sqrt((double)g->n), w = 1u << resident_batch_class(g);
+            teams_many += 6.5 * phases * w / room;
+            launch_many += 1.3e-4 * (double)g->m;
+            if (phases > longest) longest = phases;
+            top_wgs = std::max(top_wgs, w);
+        } else {
+            launch_few += (sparse ? 1.3e-4 : 1e-4) * (double)g->m;
+            teams_few += (sparse ? 1.3e-4 : 3.5e-5) * (double)g->m;
+        }
+    }
+    if (slow.empty()) return SSSP_OK;
+    double top = 0;  // workgroups of those on the largest teams
+    for (uint32_t i : slow)
+        if (1u << resident_batch_class(graphs[i]) == (uint32_t)top_wgs) top += top_wgs;
+    teams_many = std::max(teams_many, 6.5 * longest * ceil(top / room));
+    const double alone = std::max(launch_many, 8.5 * longest), all = std::max(launch_many + launch_few, 8.5 * longest);
+    if (teams_many <= alone) return SSSP_OK;
+    if (alone + teams_few >= all) {
+        slow.insert(slow.end(), few.begin(), few.end());
+        few.clear();
+    }
+    left->insert(left->end(), slow.begin(), slow.end());
+    *ids = few;
+    return SSSP_OK;
+}
+
+// The default form: queries of graphs that a resident team takes run on teams (but see batch_split),
+// larger ones and a query alone on the whole device, one after the other. *left: the queries that
+// were not solved.
 //
 // Larger graphs, up to two: each takes the device in turn, which is faster than both at once by the
 // launch above, whatever the graph (two grids of 1 M vertices 104 ms and 222, two paths of 525 k 3.2 s
@@ -919,11 +997,11 @@ static int batch_default(sssp_graph *const *graphs, const uint32_t *sources, uin
         }
         if (phases_out) phases_out[i] = phases;
     }
-    if (small.empty()) return SSSP_OK;
+    int rc = batch_split(graphs, sources, &small, left);
+    if (rc || small.empty()) return rc;
     bool ran = false;
-    const int rc = resident_batch(graphs, sources, small.data(), (uint32_t)small.size(), in, out_static, dist_outs,
-                                  phases_out, &ran);
-    if (rc == SSSP_OK && !ran) *left = small;
+    rc = resident_batch(graphs, sources, small.data(), (uint32_t)small.size(), in, out_static, dist_outs, phases_out, &ran);
+    if (rc == SSSP_OK && !ran) left->insert(left->end(), small.begin(), small.end());
     return rc;
 }
 

@@ -90,6 +90,9 @@ int resident_learn(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32
                    uint64_t *dist_out, void *scratch, ResLearned *out, bool *ran);
 int resident_learn_state(const sssp_graph *g, const ResShape &r, hipStream_t s, uint64_t *dist_out, void *scratch);
 bool resident_batch_takes(const sssp_graph *g);
+uint32_t resident_batch_class(const sssp_graph *g);
+int resident_probe(sssp_graph *const *graphs, const uint32_t *sources, const std::vector<uint32_t> &ids,
+                   std::vector<uint32_t> *many);
 int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uint32_t *ids, uint32_t nq, int in,
                    bool out_static, uint64_t *const *dist_outs, uint32_t *phases_out, bool *ran);
 // A resident solve where the graph and its launch options allow one (phased.hip).

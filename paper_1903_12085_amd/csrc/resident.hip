@@ -1574,6 +1574,88 @@ static bafn pick_res_batch(int in, bool out) {
 static uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
 
 bool resident_batch_takes(const sssp_graph *g) { return g->n <= (uint64_t)kGang * kWgVertices; }
+// The class of the least team whose lists hold the graph: it has 1 << class workgroups.
+uint32_t resident_batch_class(const sssp_graph *g) {
+    uint32_t c = 0;
+    while (((uint64_t)kWgVertices << c) < g->n) ++c;
+    return c;
+}
+
+// Whether a query's solve will take many phases, from what its source reaches in few hops: one
+// workgroup per query walks up to kProbeHops hops and says so when they reached at most kProbeSeen
+// vertices and did not run out. Grids and meshes of up to eight neighbours reach at most 1089 and take 5 to
+// 21 sqrt(n) phases; random and R-MAT graphs, or grids in three dimensions, reach more and take at
+// most 2.6 sqrt(n). A row of more than kProbeRow edges also means few phases. About 60 us for 512
+// queries, with loads that wait for one another.
+constexpr uint32_t kProbeHops = 16, kProbeSeen = 2048, kProbeRow = 256, kProbeSlots = 4 * kProbeSeen;
+__global__ __launch_bounds__(256) void k_batch_probe(const ResQuery *q, uint32_t *many) {
+    __shared__ uint32_t table[kProbeSlots], front[2][kProbeSeen];  // vertices seen (INF32: none), by hash; a hop's
+    __shared__ uint32_t s_seen, s_next, s_few;
+    const uint32_t tid = threadIdx.x;
+    const ResQuery rq = q[blockIdx.x];
+    for (uint32_t i = tid; i < kProbeSlots; i += 256) table[i] = INF32;
+    if (tid == 0) {
+        front[0][0] = rq.src;
+        s_seen = 1;
+        s_few = 0;
+    }
+    __syncthreads();
+    // true if v was not there; at most kProbeSeen + 256 get in, so that there are free slots
+    auto insert = [&](uint32_t v) {
+        uint32_t i = v * 2654435769u >> 19;
+        for (;;) {
+            const uint32_t old = atomicCAS(&table[i], INF32, v);
+            if (old == INF32 || old == v) return old == INF32;
+            i = (i + 1) % kProbeSlots;
+        }
+    };
+    static_assert(kProbeSlots == 1u << (32 - 19), "hash");
+    if (tid == 0) insert(rq.src);
+    uint32_t nf = 1;
+    for (uint32_t hop = 0; hop < kProbeHops && nf; ++hop) {  // block-uniform
+        __syncthreads();
+        if (tid == 0) s_next = 0;
+        __syncthreads();
+        bool few = false;
+        for (uint32_t j = tid; j < nf && !few; j += 256) {
+            const uint32_t u = front[hop & 1][j], r0 = rq.rp[u], r1 = rq.rp[u + 1];
+            few = r1 - r0 > kProbeRow;
+            for (uint32_t e = r0; e < r1 && !few; ++e) {
+                const uint32_t v = rq.edges[e].x;
+                if (!insert(v)) continue;
+                few = atomicAdd(&s_seen, 1u) >= kProbeSeen;  // each thread's last insertion then
+                if (!few) front[(hop & 1) ^ 1][atomicAdd(&s_next, 1u)] = v;
+            }
+        }
+        if (few) s_few = 1;
+        __syncthreads();
+        nf = s_few ? 0 : s_next;
+    }
+    if (tid == 0) many[blockIdx.x] = nf != 0;
+}
+
+// many[j] = the probe of query ids[j], with graphs[0]'s scratch on its stream.
+int resident_probe(sssp_graph *const *graphs, const uint32_t *sources, const std::vector<uint32_t> &ids,
+                   std::vector<uint32_t> *many) {
+    const uint32_t nq = (uint32_t)ids.size();
+    const uint64_t o_many = up256(nq * sizeof(ResQuery));
+    const int rc = resident_scratch(graphs[0], o_many + 4ull * nq);
+    if (rc) return rc;
+    hipStream_t s = graphs[0]->stream;
+    uint8_t *base = (uint8_t *)graphs[0]->res;
+    std::vector<ResQuery> hq(nq);
+    for (uint32_t j = 0; j < nq; ++j) {
+        const sssp_graph *g = graphs[ids[j]];
+        hq[j] = ResQuery{g->rp, g->edges, g->vmin, g->emin, nullptr, g->n, sources[ids[j]], g->wmax, 0u};
+    }
+    many->resize(nq);
+    HIP_OK(hipMemcpyAsync(base, hq.data(), nq * sizeof(ResQuery), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_batch_probe, dim3(nq), dim3(256), 0, s, (const ResQuery *)base, (uint32_t *)(base + o_many));
+    HIP_OK(hipGetLastError());
+    HIP_OK(hipMemcpyAsync(many->data(), base + o_many, 4ull * nq, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    return SSSP_OK;
+}
 
 // Solves the queries ids[0 .. nq) (each of a graph that resident_batch_takes) in one cooperative
 // launch on graphs[0]'s stream and scratch. *ran = false: as in resident_solve, or no memory for it.
@@ -1590,7 +1672,7 @@ int resident_batch(sssp_graph *const *graphs, const uint32_t *sources, const uin
     uint64_t wgs = 0;
     uint32_t slots = 0, wgv = 0;
     for (uint32_t i = 0; i < nq; ++i) {
-        while (((uint64_t)kWgVertices << cls[i]) < graphs[ids[i]]->n) ++cls[i];
+        cls[i] = resident_batch_class(graphs[ids[i]]);
         wgs += 1u << cls[i];
     }
     auto lds_slots = [&](uint32_t n, uint32_t c) { return kBatchBs * ((((n - 1) / 8 + 1) - 1) / (kBatchBs << c) + 1); };

@@ -101,3 +101,50 @@ def test_team_after_many_queries_of_one_phase(B, ones):
     """Sources without out-edges between queries of several phases, on teams of two."""
     lone = G.from_edges(20000, [(1, 2, 5)])
     run(B, [(path(32000, 6), 256), (lone, 256 * ones), (path(17000, 9), 256)])
+
+
+def mesh8(a, b, seed):
+    """a x b mesh in which a vertex has its up to eight neighbours."""
+    rng = np.random.default_rng(seed)
+    x = np.arange(a * b).reshape(a, b)
+    e = [np.stack([x[max(0, -dx):a - max(0, dx), max(0, -dy):b - max(0, dy)].ravel(),
+                   x[max(0, dx):a - max(0, -dx), max(0, dy):b - max(0, -dy)].ravel()])
+         for dx in (-1, 0, 1) for dy in (-1, 0, 1) if dx or dy]
+    u, v = np.concatenate(e, 1)
+    order = np.argsort(u, kind="stable")
+    rp = np.concatenate([[0], np.cumsum(np.bincount(u, minlength=a * b))]).astype(np.uint64)
+    return G.Graph(a * b, rp, v[order].astype(np.uint32), rng.integers(1, 1 << 16, u.size).astype(np.uint32), "mesh8")
+
+
+KINDS = {"grid": lambda: G.grid(190, 181, 1, 1 << 16, 20), "long_grid": lambda: G.grid(16, 2100, 1, 1 << 16, 21),
+         "mesh8": lambda: mesh8(190, 181, 22), "random_2": lambda: G.er(33003, 2, 1, 1 << 20, 23),
+         "random_8": lambda: G.er(33003, 8, 1, 1 << 20, 24), "rmat": lambda: G.rmat(15, 16, 1, 1 << 20, 25),
+         "path": lambda: path(33003, 3000), "isolated": lambda: G.from_edges(33003, [(1, 2, 3)]),
+         "hub": lambda: hub(33003, 20000, 26)}
+
+
+@pytest.mark.parametrize("name", list(KINDS))
+def test_many_queries_of_mid_sized_graphs_are_no_slower_than_in_one_launch(B, name):
+    """More queries than teams of four fit (128). Those of many phases took up to 2.5 times as long on teams."""
+    g = KINDS[name]()
+    dg = B.DeviceGraph.from_graph(g)
+    srcs = [int(s) for s in G.sources(g, 1, 27)] + [0, g.n - 1]
+    refs = {s: O.phased(g, s, O.STATIC_OR) for s in srcs}
+    for count in (120, 500):
+        q = [srcs[i % 3 if count == 120 else 0] for i in range(count)]
+        dists = [B.new_dist(g.n) for _ in q]
+        one = median_ms(lambda: B.solve_batch([dg] * count, q, B.STATIC_OR, dists, cfg=dict(split=64)))
+        ours = median_ms(lambda: B.solve_batch([dg] * count, q, B.STATIC_OR, dists))
+        _, phases = B.solve_batch([dg] * count, q, B.STATIC_OR, dists)
+        print("%s, %d queries: %.2f ms (%s), in one launch %.2f ms" % (name, count, ours, dg.last_form(), one), flush=True)
+        if count == 500 and name not in ("path", "isolated", "hub"):  # (from a leaf, the hub graph is a ring of 50)
+            assert dg.last_form() == ("workgroups" if name in ("grid", "long_grid", "mesh8") else "resident")
+        assert ours <= 1.15 * one + 0.1, (name, count)
+        for s, d, p in zip(q, dists, phases):
+            assert np.array_equal(B.to_u64(d), refs[s].dist) and p == refs[s].phases, (name, count, s)
+    dg.close()
+
+
+def test_batch_split_between_teams_and_the_launch(B):
+    """Grids left to the launch and random graphs on teams, in one call."""
+    run(B, [(G.grid(190, 181, 1, 1 << 16, 28), 300), (G.er(60001, 24, 1, 1 << 20, 29), 100), (G.er(900, 4, 1, 50, 30), 40)])
