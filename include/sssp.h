@@ -329,8 +329,10 @@ typedef struct {
                                no stronger member: 0 and 1 resident, 2 the phase kernels).
                                0 (default): resident, the whole solve in one cooperative launch whose
                                workgroups meet at a barrier once per phase (graphs of at most 2^24
-                               vertices; larger ones, and solves with per-kernel timing on, use the
-                               phase kernels, whose shape the fields above give). 1: in one workgroup
+                               vertices; larger ones, solves with per-kernel timing on, and solves
+                               that promise few and very large phases, by the graph's size, mean
+                               weight and longest row and by the bucket width, use the phase
+                               kernels, whose shape the fields above give). 1: in one workgroup
                                of the batched kernel (sssp_solve_batch with one query). 2: the phase
                                kernels. Same distances and phase count. sssp_solve_ex and every other
                                solver ignore it. Values above 2 mean 2. */

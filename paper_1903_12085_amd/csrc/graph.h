@@ -77,6 +77,7 @@ struct ResShape {
     uint64_t bytes;       // device scratch
 };
 ResShape resident_shape(const sssp_graph *g);
+bool resident_pays(const sssp_graph *g, int in, int out, uint64_t delta, bool learn);
 int resident_solve(const sssp_graph *g, const ResShape &r, hipStream_t s, uint32_t source, int in, int out, uint64_t delta,
                    uint64_t *dist_out, void *scratch, uint32_t *phases, bool *ran, uint32_t cap = 0);
 // What the static stage of a learned checkpoint solve leaves: counts, and minD and the OUT-STATIC

@@ -3069,7 +3069,7 @@ static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     bool staged = false;
     ResLearned stage{};
     const ResShape rs = resident_shape(g);
-    if (ckpt && rs.fits && !trace_cap && !phase_of && g->cfg.single != kPhaseKernels) {
+    if (ckpt && rs.fits && !trace_cap && !phase_of && g->cfg.single != kPhaseKernels && resident_pays(g, in, out, 0, true)) {
         rc = resident_scratch(g, resident_learn_bytes(g, rs));
         if (rc == SSSP_OK) rc = resident_learn(g, rs, s, source, a.mlp_w, a.wm, dist_out, g->res, &stage, &staged);
         if (rc && rc != SSSP_ERR_OOM) return rc;
@@ -3238,7 +3238,7 @@ int resident_try(sssp_graph *g, uint32_t source, int in, int out, uint64_t delta
                  uint32_t *phases_out, bool *ran) {
     *ran = false;
     const ResShape r = resident_shape(g);
-    if (!r.fits || g->prof) return SSSP_OK;
+    if (!r.fits || g->prof || !resident_pays(g, in, out, delta, false)) return SSSP_OK;
     int rc = SSSP_OK;
     if (!static_modes(in, out)) {  // heads, cursors and sorted rows, as the phase kernels need them
         if (in == IN_SIMPLE_M) rc = graph_ensure_csc(g);
@@ -3540,7 +3540,7 @@ extern "C" int sssp_solve_noalloc(sssp_graph *g, uint32_t source, uint32_t crite
     int rc = noalloc_scratch(g->device, &base);
     if (rc) return rc;
     const ResShape r = resident_shape(g);
-    if (r.fits && r.bytes <= kNoAllocBytes) {
+    if (r.fits && r.bytes <= kNoAllocBytes && resident_pays(g, in, out, 0, false)) {
         bool ran = false;
         uint32_t phases = 0;
         rc = resident_solve(g, r, g->stream, source, in, out, 0, dist_out, base, &phases, &ran);

@@ -63,6 +63,7 @@
 //
 // Values that several workgroups touch go through device-scope atomics, loads
 // and stores; everything a workgroup wrote has completed when it publishes.
+#include <math.h>
 #include <string.h>
 
 #include <algorithm>
@@ -1299,6 +1300,49 @@ static ResArgs resident_args(const sssp_graph *g, const ResShape &r, uint32_t so
     a.in_cur = g->b.in_cur;
     a.out_cur = g->b.out_cur;
     return a;
+}
+
+// Whether the resident form is the faster one. It saves about 10 us a phase or round, but relaxes a
+// large set of edges more slowly than the phase kernels do, whose blocks take equal shares of it: where
+// a solve has few and large phases they win. What tells is the mean weight (the smaller the weights,
+// the fewer distances there are and the fewer phases) against the size m + 4 n, and whether a few
+// rows hold many of the edges (`skewed`), which resident workgroups share only by records. Times of
+// the resident form over the phase kernels', weights uniform in [1, w]:
+//   static        R-MAT 22 (65 M edges)  w = 4  1.30, 64  1.07, 256  0.89;   R-MAT 21  w = 4  1.19, 16  0.93
+//                 random, 67 M edges     w = 4  1.03 - 1.06, 16  0.94 - 0.97;   smaller graphs below 1 at any w
+//   SIMPLE        R-MAT 22               w = 64  1.12, 256  0.97;   R-MAT 21  w = 4  1.24, 16  0.98
+//                 random, 67 M edges     w = 16  0.96 - 1.08, 64  0.72 - 1.00;   34 M  w = 1  1.05, 4  0.95
+//   checkpoint    (a pass counts the relaxations, a random load per edge)
+//                 R-MAT 22               w = 2^14  1.06, 2^20  0.91;   R-MAT 20 and 21  w = 2^10  1.05 - 1.17, 2^14  0.96
+//                 R-MAT 18, 8 M edges    w = 256  1.05, 1024  0.94
+//                 random, 67 M edges     w = 64  1.15 - 1.23, 256  0.90 - 1.11;   34 M  w = 16  1.03, 64  0.93
+//                 random of degree 64 and 200, 17 to 20 M edges  w = 16  1.17 - 1.23, 1024  0.73 - 0.87
+//   Delta-stepping, by the width over the largest weight (a wide bucket is one large set)
+//                 R-MAT 22               1/16  1.10, 1/32  0.76;   R-MAT 18 to 21, 4 to 32 M edges  1/4  1.02 - 1.11, 1/8  0.73 - 0.89
+//                 R-MAT 14 and 16, 0.2 to 1 M edges  1/2  1.25, 1/4  0.84 - 0.95;   1  1.03 - 1.9, 1/2  0.84 - 1.25
+//                 random of degree 64 and more, over 4 M edges  1  1.03 - 1.08, 1/2  0.81 - 0.88;   0.6 M edges  1/2  1.09, 1/4  0.85
+bool resident_pays(const sssp_graph *g, int in, int out, uint64_t delta, bool learn) {
+    if (g->m == 0) return true;
+    const double m = (double)g->m, n = g->n, w = 2.0 * (double)g->sum_w / m;  // uniform weights lie in [1, w - 1]
+    const double size = m + 4 * n, million = 1e6;
+    const bool skewed = g->max_deg > kShareDeg && g->max_deg > 8 * m / n, dense = m >= 48 * n;
+    if (delta) {
+        double wide = INFINITY;  // widths from here on, in parts of the largest weight
+        if (skewed) wide = m >= 40 * million ? 0.05 : m >= 1 * million ? 0.2 : m >= 0.25 * million ? 0.4 : m >= 0.12 * million ? 0.75 : INFINITY;
+        else if (dense && w > 16) wide = m >= 4 * million ? 0.75 : m >= 0.5 * million && m < 1 * million ? 0.4 : INFINITY;
+        return (double)delta < wide * w;
+    }
+    double low = 0;  // weights up to here
+    if (learn) {
+        if (skewed) low = size >= 67 * million ? 20000 : size >= 15 * million ? 1500 : m >= 4 * million ? 400 : 0;
+        else if (dense) low = m >= 4 * million ? 300 : 0;
+        else low = size >= 67 * million ? 100 : size >= 25 * million ? 20 : m >= 16 * million ? 4 : 0;
+    } else {
+        const bool simple = in == IN_SIMPLE_M || out == OUT_SIMPLE_M;
+        if (skewed) low = size >= 67 * million ? 100 : size >= 25 * million ? 6 : 0;
+        else low = size >= 67 * million ? (simple ? 20 : 6) : size >= 25 * million && simple ? 2 : 0;
+    }
+    return w > low;
 }
 
 static dim3 vertex_grid(uint32_t n) {
