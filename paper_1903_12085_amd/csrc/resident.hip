@@ -1323,7 +1323,8 @@ static ResArgs resident_args(const sssp_graph *g, const ResShape &r, uint32_t so
 //                 random of degree 64 and more, over 4 M edges  1  1.03 - 1.08, 1/2  0.81 - 0.88;   0.6 M edges  1/2  1.09, 1/4  0.85
 bool resident_pays(const sssp_graph *g, int in, int out, uint64_t delta, bool learn) {
     if (g->m == 0) return true;
-    const double m = (double)g->m, n = g->n, w = 2.0 * (double)g->sum_w / m;  // uniform weights lie in [1, w - 1]
+    // uniform weights lie in [1, w - 1]; all zero count as ones
+    const double m = (double)g->m, n = g->n, w = std::max(2.0 * (double)g->sum_w / m, 1.0);
     const double size = m + 4 * n, million = 1e6;
     const bool skewed = g->max_deg > kShareDeg && g->max_deg > 8 * m / n, dense = m >= 48 * n;
     if (delta) {

@@ -62,3 +62,14 @@ def test_default_is_no_slower_than_the_phase_kernels(B, name):
         assert np.array_equal(B.to_u64(dist), got if ref is None else ref)
         assert ours <= 1.1 * phases + 0.02, (name, what, ours, phases)
     dg.close()
+
+
+def test_zero_weights(B):
+    """All distances are 0: one phase for the source, one for the rest."""
+    g = G.er(3000, 6, 1, 5, 711)
+    g = G.Graph(g.n, g.row_ptr, g.col, np.zeros(g.m, np.uint32), "zero")
+    dg = B.DeviceGraph.from_graph(g)
+    ref = O.dijkstra(g, 0)[0]
+    for call in (lambda: B.solve(dg, 0, B.STATIC_OR), lambda: B.solve(dg, 0, B.SIMPLE_OR), lambda: B.delta_step(dg, 0, 3)):
+        assert np.array_equal(call().dist_u64(), ref) and dg.last_form() == "resident"
+    dg.close()
