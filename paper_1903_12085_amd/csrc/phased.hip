@@ -627,21 +627,35 @@ __device__ __forceinline__ void mark_in_edge(const KArgs &a, uint2 ie, bool sett
     }
 }
 
-// This thread's state bytes of the window [vb, vb + win): four consecutive ones, or one of a short
-// window (bytes past n read as unexplored), and their place in LDS.
-__device__ __forceinline__ uint32_t load_window(const KArgs &a, uint64_t vb) {
-    if (a.win == kBlock) return vb + threadIdx.x < a.g.n ? a.b.st[vb + threadIdx.x] : 0u;
-    const uint64_t q = vb / 4 + threadIdx.x;
-    return 4 * q < a.g.n ? load_st4(a.b.st, (uint32_t)q, a.g.n) : 0u;
+// This thread's state bytes of the window [vb, vb + win): sixteen or four consecutive ones, or one of a
+// short window (bytes past n read as unexplored, unused words as zero), and their place in LDS.
+__device__ __forceinline__ uint4 load_window(const KArgs &a, uint64_t vb) {
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (a.win == kBlock) {
+        if (vb + threadIdx.x < a.g.n) x.x = a.b.st[vb + threadIdx.x];
+    } else if (a.win == 4 * kBlock) {
+        const uint64_t q = vb / 4 + threadIdx.x;
+        if (4 * q < a.g.n) x.x = load_st4(a.b.st, (uint32_t)q, a.g.n);
+    } else {
+        const uint64_t v0 = vb + 16u * threadIdx.x;
+        if (v0 + 16 <= a.g.n) return *reinterpret_cast<const uint4 *>(a.b.st + v0);
+        const uint32_t q = (uint32_t)(v0 / 4);
+        if (v0 < a.g.n) x.x = load_st4(a.b.st, q, a.g.n);
+        if (v0 + 4 < a.g.n) x.y = load_st4(a.b.st, q + 1, a.g.n);
+        if (v0 + 8 < a.g.n) x.z = load_st4(a.b.st, q + 2, a.g.n);
+        if (v0 + 12 < a.g.n) x.w = load_st4(a.b.st, q + 3, a.g.n);
+    }
+    return x;
 }
-__device__ __forceinline__ void store_window(const KArgs &a, uint32_t *s_st, uint32_t x) {
-    if (a.win == kBlock) reinterpret_cast<uint8_t *>(s_st)[threadIdx.x] = (uint8_t)x;
+__device__ __forceinline__ void store_window(const KArgs &a, uint4 *s_st, uint4 x) {
+    if (a.win == kBlock) reinterpret_cast<uint8_t *>(s_st)[threadIdx.x] = (uint8_t)x.x;
+    else if (a.win == 4 * kBlock) reinterpret_cast<uint32_t *>(s_st)[threadIdx.x] = x.x;
     else s_st[threadIdx.x] = x;
 }
 
 template <bool IN_ON, int OUT_M>
 __global__ __launch_bounds__(kBlock) void k_mark(KArgs a, int par) {
-    __shared__ uint32_t s_st[kBlock];
+    __shared__ uint4 s_st[kBlock];
     __shared__ RowList L;
     __shared__ RowList L2[1];  // OUT (full): in-rows to flag
     Ctl *ctl = a.b.ctl;
@@ -652,8 +666,8 @@ __global__ __launch_bounds__(kBlock) void k_mark(KArgs a, int par) {
     if (reached == settled_cnt) return;
     const uint8_t *sw = reinterpret_cast<const uint8_t *>(s_st);
     for (uint64_t vb = (uint64_t)blockIdx.x * a.win; vb < n; vb += (uint64_t)gridDim.x * a.win) {
-        const uint32_t x = load_window(a, vb);
-        const bool any = (x & 0x80808080u) != 0;
+        const uint4 x = load_window(a, vb);
+        const bool any = ((x.x | x.y | x.z | x.w) & 0x80808080u) != 0;
         __syncthreads();  // the previous window's LDS reads are done
         store_window(a, s_st, x);
         if (threadIdx.x == 0) {
@@ -1561,7 +1575,7 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
     constexpr bool kStoreIn = IN == IN_FULL_M, kStoreOut = OUT == OUT_WEAK_M || OUT == OUT_FULL_M;
     constexpr bool kStore = kStoreIn || kStoreOut;
     __shared__ unsigned long long sh[8 * kWaves];
-    __shared__ uint32_t s_st[kBlock];
+    __shared__ uint4 s_st[kBlock];
     // stored terms: the vertices computed in full in this window, and their minima
     __shared__ RowList L;
     __shared__ unsigned long long s_ti[kStore ? kListCap : 1], s_to[kStore ? kListCap : 1];
@@ -1573,7 +1587,7 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
     const uint32_t n = a.g.n;
     const uint64_t step = (uint64_t)gridDim.x * a.win;
     uint64_t vb = (uint64_t)blockIdx.x * a.win;
-    uint32_t x = load_window(a, vb);
+    uint4 x = load_window(a, vb);
     const unsigned long long reached = wave_sum64(r0);
     if (reached == settled) return;
     const unsigned long long minD = wave_min64(m0);
@@ -1590,7 +1604,10 @@ __global__ __launch_bounds__(kBlock) void k_terms_win(KArgs a, int par) {
     for (; vb < n; vb += step) {  // block-uniform
         bool any = false;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) any |= ((x >> (8 * j)) & ST_SET) == ST_F;
+        for (int j = 0; j < 4; ++j) {
+            any |= ((x.x >> (8 * j)) & ST_SET) == ST_F || ((x.y >> (8 * j)) & ST_SET) == ST_F;
+            any |= ((x.z >> (8 * j)) & ST_SET) == ST_F || ((x.w >> (8 * j)) & ST_SET) == ST_F;
+        }
         __syncthreads();  // the previous window's LDS reads are done
         store_window(a, s_st, x);
         if (kStore && threadIdx.x == 0) L.cnt = 0;
@@ -2534,8 +2551,10 @@ static kfn pick_mark(int in, int out) {
 // windows of 4096 / 1024 / 256 vertices: random 2^16, degree 10: IN-SIMPLE|OUT-SIMPLE 50.8 / 31.3 /
 // 25.9, IN|OUT 93.6 / 51.1 / 40.0; grid of 249 k vertices, SIMPLE: 26.9 / 22.7 / 22.0; random, 1 M of
 // degree 10: 52.7 / 35.8 / 35.6 and 77.9 / 56.3 / 65.8; random 2^22, degree 16: 84.0 / 78.0 / 89.1 and
-// 138.6 / 138.8 / 185.9.
-static uint32_t term_window(uint32_t n) { return n <= (1u << 18) ? kBlock : 4 * kBlock; }
+// 138.6 / 138.8 / 185.9. Larger graphs have queued vertices enough for long windows, whose full rows a
+// block shares out better (solves with IN|OUT, 4096 / 1024: random 2^21 of degree 2 10.1 ms / 10.4, 2^22
+// 15.4 / 18.8, 2^24 56 / 79; 2^23 of degree 5 45 / 48; grid 2048^2 511 / 573).
+static uint32_t term_window(uint32_t n) { return n <= (1u << 18) ? kBlock : n <= (1u << 21) ? 4 * kBlock : 16 * kBlock; }
 static uint32_t terms_grid(uint32_t n) {
     const uint32_t w = term_window(n);
     const uint64_t b = ((uint64_t)n + w - 1) / w;
