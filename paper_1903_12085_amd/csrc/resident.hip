@@ -1019,7 +1019,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
         }
         if (tid == 0) {
             s_pend = s_nsh = 0;
-            s_flags &= 1u;
+            atomicAnd(&s_flags, 1u);  // another wavefront may be giving up
             s_shlim = kShareCap;
         }
         if (LEARN && k % 16 == 15 && wave == 0) {
