@@ -806,7 +806,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             if (waiting && lane == 0) s_pend = 1;
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's records are written
             __syncthreads();
-            if (tid == 0) st_agent(&bar_b[wg * kSlotStride], count_word(nb, umin32(s_nsh, s_shlim)));
+            if (tid == 0 && W > 1) st_agent(&bar_b[wg * kSlotStride], count_word(nb, umin32(s_nsh, s_shlim)));
         }
         wave_fence();
         uint32_t nseg = umin32(s_wn[lw], s_wl[lw]);
@@ -950,7 +950,12 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             relax_own();
         }
         if (a.share) {
-            if (tid < W) {
+            if (W == 1) {
+                if (tid == 0) {
+                    s_sh[0] = umin32(s_nsh, s_shlim);
+                    if (s_sh[0]) s_flags |= 2u;
+                }
+            } else if (tid < W) {
                 uint32_t spins = 0;
                 unsigned long long v;
                 while (!count_is_for(v = ld64(&bar_b[tid * kSlotStride]), nb) && ++spins < a.polls) {}
@@ -1035,11 +1040,13 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             x = umin64(x, dpp64<kDppQuadSwap2>(x));
             if (kWv >= 8) x = umin64(x, dpp64<kDppHalfMirror>(x));
             if (kWv >= 16) x = umin64(x, dpp64<kDppMirror>(x));
-            if (lane == 0 || (OUT && lane == kWv))
-                st_agent(&bar_a[wg * kSlotStride + (lane ? 1 : 0)], tag | umin64(x, kVal));
+            if (lane == 0 || (OUT && lane == kWv)) {
+                if (W > 1) st_agent(&bar_a[wg * kSlotStride + (lane ? 1 : 0)], tag | umin64(x, kVal));
+                else s_all[lane ? kResMaxW / 64 : 0] = x;  // a workgroup alone waits for no words
+            }
         }
         unsigned long long pm = kVal, pt2 = kVal;
-        if (tid < W) {
+        if (W > 1 && tid < W) {
             const unsigned long long *w = &bar_a[tid * kSlotStride];
             uint32_t spins = 0;
             for (;;) {
@@ -1054,7 +1061,7 @@ __device__ __forceinline__ uint32_t resident_run(const ResArgs &a, uint32_t wg, 
             pm &= kVal;
             if (OUT) pt2 &= kVal;
         }
-        if (wave * 64 < W) {
+        if (W > 1 && wave * 64 < W) {
             pm = wave_min_rel(pm == kVal ? INF64 : pm, minD);
             if (OUT) pt2 = wave_min_rel(pt2 == kVal ? INF64 : pt2, minD);
             if (lane == 0) {

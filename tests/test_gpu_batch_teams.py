@@ -148,3 +148,24 @@ def test_many_queries_of_mid_sized_graphs_are_no_slower_than_in_one_launch(B, na
 def test_batch_split_between_teams_and_the_launch(B):
     """Grids left to the launch and random graphs on teams, in one call."""
     run(B, [(G.grid(190, 181, 1, 1 << 16, 28), 300), (G.er(60001, 24, 1, 1 << 20, 29), 100), (G.er(900, 4, 1, 50, 30), 40)])
+
+
+@pytest.mark.parametrize("n", [1000, 4000])
+def test_workgroups_alone_are_no_slower_than_in_one_launch(B, n):
+    """A graph with a hub, solved from vertices off it in many phases of one vertex, a workgroup a query:
+    11 % slower than in the launch while the workgroup read its own words back from memory twice a phase, now 9 %
+    faster."""
+    rng = np.random.default_rng(31)
+    rp = np.concatenate([[0], n - 1 + np.arange(n)]).astype(np.uint64)
+    g = G.Graph(n, rp, np.concatenate([np.arange(1, n), rng.integers(0, n, n - 1)]).astype(np.uint32),
+                rng.integers(1, 1000, 2 * (n - 1)).astype(np.uint32), "star")
+    dg = B.DeviceGraph.from_graph(g)
+    srcs = [int(s) for s in G.sources(g, 8, 6)] * 8
+    dists = [B.new_dist(n) for _ in srcs]
+    one = median_ms(lambda: B.solve_batch([dg] * 64, srcs, B.STATIC_OR, dists, cfg=dict(split=64)), 31)
+    ours = median_ms(lambda: B.solve_batch([dg] * 64, srcs, B.STATIC_OR, dists), 31)
+    print("star of %d: %.3f ms, in one launch %.3f ms" % (n, ours, one))
+    assert ours <= 1.03 * one
+    for s, d in zip(srcs[:8], dists):
+        assert np.array_equal(B.to_u64(d), O.dijkstra(g, s)[0])
+    dg.close()
