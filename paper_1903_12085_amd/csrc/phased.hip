@@ -2551,12 +2551,15 @@ static kfn pick_mark(int in, int out) {
 // windows of 4096 / 1024 / 256 vertices: random 2^16, degree 10: IN-SIMPLE|OUT-SIMPLE 50.8 / 31.3 /
 // 25.9, IN|OUT 93.6 / 51.1 / 40.0; grid of 249 k vertices, SIMPLE: 26.9 / 22.7 / 22.0; random, 1 M of
 // degree 10: 52.7 / 35.8 / 35.6 and 77.9 / 56.3 / 65.8; random 2^22, degree 16: 84.0 / 78.0 / 89.1 and
-// 138.6 / 138.8 / 185.9. Larger graphs have queued vertices enough for long windows, whose full rows a
-// block shares out better (solves with IN|OUT, 4096 / 1024: random 2^21 of degree 2 10.1 ms / 10.4, 2^22
-// 15.4 / 18.8, 2^24 56 / 79; 2^23 of degree 5 45 / 48; grid 2048^2 511 / 573).
-static uint32_t term_window(uint32_t n) { return n <= (1u << 18) ? kBlock : n <= (1u << 21) ? 4 * kBlock : 16 * kBlock; }
-static uint32_t terms_grid(uint32_t n) {
-    const uint32_t w = term_window(n);
+// 138.6 / 138.8 / 185.9. Larger graphs have queued vertices enough for long windows, and with stored
+// terms a block shares the full rows of a long one out better (solves with IN|OUT, 4096 / 1024: random
+// 2^21 of degree 2 10.1 ms / 10.4, 2^22 15.4 / 18.8, 2^24 56 / 79; 2^23 of degree 5 45 / 48; grid 2048^2 511 /
+// 573; with SIMPLE: random 2^22 of degree 2, 5 and 16 28.9 / 26.8, 24.2 / 22.6 and 27.3 / 25.2; 2^23 of
+// degree 2 47.5 / 51.7).
+static uint32_t term_window(uint32_t n, bool stored) {
+    return n <= (1u << 18) ? kBlock : n <= (stored ? 3u << 19 : 1u << 22) ? 4 * kBlock : 16 * kBlock;
+}
+static uint32_t terms_grid(uint32_t n, uint32_t w) {
     const uint64_t b = ((uint64_t)n + w - 1) / w;
     return (uint32_t)(b < 1 ? 1 : b > 65535 ? 65535 : b);
 }
@@ -2691,7 +2694,7 @@ static int run_loop_profiled(sssp_graph *g, const KArgs &a, const PhaseKernels &
     sssp_kernel_profile pr{};
     if (k0) pr = g->last_prof;
     else g->phase_ms.clear();
-    const dim3 blk(kBlock), gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n));
+    const dim3 blk(kBlock), gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n, a.win));
     uint64_t k = k0;
     for (;;) {
         const uint64_t kb = k;
@@ -2766,7 +2769,7 @@ static int ensure_phase_graph(sssp_graph *g, const KArgs &a, const PhaseKernels 
     g->graph_key_len = 0;
     if (!g->cap_stream) HIP_OK(hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking));
     hipStream_t cs = g->cap_stream;
-    const dim3 blk(kBlock), gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n));
+    const dim3 blk(kBlock), gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n, a.win));
     HIP_OK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     for (int par = 0; par < kGraphPhases; ++par) {
         if (K.mark) hipLaunchKernelGGL(K.mark, gt, blk, 0, cs, a, par);
@@ -2799,7 +2802,7 @@ static int run_loop(sssp_graph *g, const KArgs &a, const PhaseKernels &K, uint64
     }
     hipStream_t s = g->stream;
     const dim3 blk(kBlock);
-    const dim3 gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n));
+    const dim3 gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n, a.win));
     uint64_t k = k0;
     uint32_t batch = graphs ? kGraphPhases : 4;
     int slot = 0;
@@ -2865,7 +2868,7 @@ static int run_until_drop(sssp_graph *g, const KArgs &a, const PhaseKernels &K, 
                           uint32_t den, uint64_t *k_next, CtlHead *head, uint64_t k0 = 0, bool checkpoint = false,
                           unsigned int *choice = nullptr) {
     hipStream_t s = g->stream;
-    const dim3 blk(kBlock), gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n));
+    const dim3 blk(kBlock), gs(g->cfg.scan_blocks), gr(g->cfg.relax_blocks), gt(terms_grid(g->n, a.win));
     uint64_t k = k0;
     int slot = 0;
     bool have_prev = false;
@@ -3063,7 +3066,7 @@ static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     a.b.trace = nullptr;
     a.b.trace_cap = 0;
     a.crit = crit;
-    a.win = term_window(g->n);
+    a.win = term_window(g->n, stores(in, out));
     a.approx_k = apx ? *apx : 0u;
     a.mark = !learn && !trace_mode && !oracle && !apx && !delta_mode && stores(in, out);
     a.fresh_at = 0;
@@ -3150,6 +3153,7 @@ static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
                     KArgs a3 = a2;
                     a3.crit = sw->crit_then;
                     a3.mark = stores(in2, out2);
+                    a3.win = term_window(g->n, a3.mark);
                     a3.fresh_at = (uint32_t)k_next;
                     rc = run_loop(g, a3, pick_phase(g->cfg.chunk, in2, out2, false, false, false,
                                                     queue_fits),
@@ -3189,6 +3193,7 @@ static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
             int i2 = in2, o2 = out2;
             if (ckpt) crit_modes(a2.crit, &i2, &o2);
             a2.mark = stores(i2, o2);
+            a2.win = term_window(g->n, a2.mark);
             a2.fresh_at = (uint32_t)k_next;
             const bool q2 = queue_later;
             rc = run_loop(g, a2, pick_phase(g->cfg.chunk, i2, o2, false, false, false, q2), max_phases, k_next);

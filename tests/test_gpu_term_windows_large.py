@@ -1,5 +1,5 @@
-"""Dynamic criteria above 2^21 vertices, where the term and dirty-set passes take windows of 4096
-vertices, at the edges of a window and of a thread's sixteen bytes, against the CPU oracle."""
+"""Dynamic criteria above 2^21 vertices, where the term and dirty-set passes of the criteria with stored
+terms take windows of 4096 vertices (the SIMPLE ones above 2^22), at the edges of a window and of a thread's sixteen bytes, against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -19,7 +19,7 @@ def B():
     return binding
 
 
-@pytest.mark.parametrize("n", [(1 << 21) + 1, (1 << 21) + 4096 + 11])
+@pytest.mark.parametrize("n", [(1 << 21) + 1, (1 << 21) + 4096 + 11, (1 << 22) + 13])
 def test_large_windows_match_oracle(B, n):
     g = G.er(n, 2, 1, 40, 402)
     dg = B.DeviceGraph.from_graph(g)
@@ -46,4 +46,20 @@ def test_large_sparse_graphs_keep_their_speed(B):
         t.append(1e3 * (time.perf_counter() - t0))
     print(["%.1f" % x for x in t])
     assert min(t[1:]) < 35
+    dg.close()
+
+
+def test_windows_by_stored_terms_and_switches(B):
+    """SIMPLE criteria keep windows of 1024 up to 2^22 vertices and full ones take 4096: a solve that
+    switches from one kind to the other, and both on one handle with phases replayed from a graph."""
+    n = (1 << 21) + 5000
+    g = G.er(n, 3, 1, 30, 403)
+    dg = B.DeviceGraph.from_graph(g)
+    ref = O.dijkstra(g, 0)[0]
+    for use_graph in (0, 1):
+        dg.set_launch(use_graph=use_graph, single=2)
+        for crit in (B.SIMPLE_OR, B.FULL_OR, B.IN_SIMPLE | B.OUT_STATIC, B.SIMPLE_OR):
+            assert np.array_equal(B.solve(dg, 0, crit).dist_u64(), ref), (use_graph, crit)
+        for then in (B.FULL_OR, B.SIMPLE_OR):
+            assert np.array_equal(B.solve_switch(dg, 0, B.STATIC_OR, then, (1, 2)).dist_u64(), ref), (use_graph, then)
     dg.close()
