@@ -2555,7 +2555,7 @@ static kfn pick_mark(int in, int out) {
 // terms a block shares the full rows of a long one out better (solves with IN|OUT, 4096 / 1024: random
 // 2^21 of degree 2 10.1 ms / 10.4, 2^22 15.4 / 18.8, 2^24 56 / 79; 2^23 of degree 5 45 / 48; grid 2048^2 511 /
 // 573; with SIMPLE: random 2^22 of degree 2, 5 and 16 28.9 / 26.8, 24.2 / 22.6 and 27.3 / 25.2; 2^23 of
-// degree 2 47.5 / 51.7).
+// degree 2 47.5 / 51.7; with the approximate criteria 2^22 of degree 16 610 / 698).
 static uint32_t term_window(uint32_t n, bool stored) {
     return n <= (1u << 18) ? kBlock : n <= (stored ? 3u << 19 : 1u << 22) ? 4 * kBlock : 16 * kBlock;
 }
@@ -3066,7 +3066,7 @@ static int solve_phased(sssp_graph *g, uint32_t source, bool delta_mode, uint32_
     a.b.trace = nullptr;
     a.b.trace_cap = 0;
     a.crit = crit;
-    a.win = term_window(g->n, stores(in, out));
+    a.win = term_window(g->n, stores(in, out) || apx);
     a.approx_k = apx ? *apx : 0u;
     a.mark = !learn && !trace_mode && !oracle && !apx && !delta_mode && stores(in, out);
     a.fresh_at = 0;
