@@ -280,7 +280,7 @@ int sssp_solve_approx(sssp_graph *g, uint32_t source, uint32_t criterion, uint32
 #define SSSP_FORM_WORKGROUPS 3u
 int sssp_last_form(const sssp_graph *g, uint32_t *form);
 
-/* How often a workgroup of a resident solve on g (of a batch: graphs[0]) looks for
+/* How often a workgroup of a resident solve on g (teams of a batch: on graphs[0]) looks for
  * another before all give up and other kernels do the solve: the device may be
  * shared with work that keeps them apart. 0, the default: 2^21 times, about a
  * second. Answers never depend on it. */
@@ -533,20 +533,21 @@ int sssp_measure_atomic_min(uint64_t *buf, uint64_t slots, uint32_t blocks, uint
                             float *ms_out);
 
 /*
- * sssp_solve for callers that cannot allocate device memory (code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same phased solve with a static criterion (a disjunction of SSSP_DIJK,
- * SSSP_IN_STATIC and SSSP_OUT_STATIC), the same kernels (dense-scan identify
- * and relax) and the same distances and phase count, with every per-solve
- * scratch buffer (control block, state bytes, settled-vertex lists) carved
- * from one device array of 64 MiB that the library holds on each device it
- * runs on until the process ends. The call makes no device or pinned host
- * allocation; the graph handle must already exist (sssp_graph_create
- * allocates) and the caller owns dist_out.
+ * sssp_solve for callers that cannot allocate device memory (tight serving
+ * loops, harnesses that forbid hipMalloc): the same phased solve with a static
+ * criterion (a disjunction of SSSP_DIJK, SSSP_IN_STATIC and SSSP_OUT_STATIC)
+ * and the same distances and phase count, with every per-solve scratch buffer
+ * carved from one device array of 64 MiB that the library holds on each device
+ * it runs on until the process ends. It runs resident where sssp_solve would
+ * and that scratch fits into the array, else the phase kernels with the dense
+ * scan; `single` in sssp_launch_cfg has no effect. The call makes no device or
+ * pinned host allocation; the graph handle must already exist
+ * (sssp_graph_create allocates) and the caller owns dist_out. It reads results
+ * back, so it cannot run under stream capture.
  *   dist_out   DEVICE, n uint64: dist(s, v), UINT64_MAX if unreachable.
  *   phases_out HOST, may be NULL: number of phases.
- * Scratch needed: about 17 bytes per vertex plus 2 bytes per edge (the exact
- * figure depends on the graph's scan grid); a graph needing more than the
+ * Scratch needed by the phase kernels: about 17 bytes per vertex plus 2 bytes
+ * per edge (the exact figure depends on the graph's scan grid); a graph needing more than the
  * array holds is rejected with SSSP_ERR_UNSUPPORTED before any device work.
  * All calls on one device share its array and each call overwrites it, so
  * calls on one device are serialised by a per-device lock inside the library;

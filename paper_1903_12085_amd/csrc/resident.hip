@@ -1466,7 +1466,8 @@ int resident_learn_state(const sssp_graph *g, const ResShape &r, hipStream_t s, 
 // longest query bounds a batch (a grid of 2^17 vertices takes 13.8 ms on eight workgroups, 12.5 on
 // sixteen; giving such grids sixteen makes a batch of 192 queries 7 % faster and one of 512 14 %
 // slower). 192 queries over 24 graphs up to 2^17 vertices: 18.2 ms, against 45.1 with one workgroup
-// of 512 threads per query (batch.hip); 512 over 64 up to 2^18: 43.8 against 79.2.
+// of 512 threads per query (batch.hip), 344 random and R-MAT queries up to 2^18 25 against 126. Grids
+// in numbers that do not fit at once are for batch.hip (batch_split).
 constexpr uint32_t kGangLog = 5, kGang = 1u << kGangLog;
 constexpr int kBatchBs = 512;                    // threads: two workgroups per CU
 constexpr uint32_t kBatchNj = 4;                 // slots per thread of a batch workgroup at most

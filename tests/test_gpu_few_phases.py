@@ -39,6 +39,15 @@ GRAPHS = {"rmat22_unit": lambda: G.rmat(22, 16, 1, 1, 701), "rmat21_w4": lambda:
           "er_small_unit": lambda: G.er(8000, 128, 1, 1, 709)}
 
 
+# which kernels have to serve a call, where one side is clearly the faster
+FORMS = {"rmat22_unit": dict(static="phases", simple="phases", checkpoint="phases", delta="phases"),
+         "er_64m_unit": dict(simple="phases", checkpoint="phases"),
+         "rmat20": dict(static="resident", simple="resident", delta="phases"), "rmat20_w256": dict(static="resident"),
+         "rmat16": dict(static="resident", simple="resident", checkpoint="resident", delta="phases"),
+         "er_1m": dict(static="resident", simple="resident", checkpoint="resident", delta="resident", delta_third="resident"),
+         "er_small_unit": dict(static="resident", simple="resident", delta="resident")}
+
+
 @pytest.mark.parametrize("name", list(GRAPHS))
 def test_default_is_no_slower_than_the_phase_kernels(B, name):
     from paper_1903_12085_amd import selector as S
@@ -61,6 +70,7 @@ def test_default_is_no_slower_than_the_phase_kernels(B, name):
         print("%s %s: %.3f ms (%s), phase kernels %.3f ms" % (name, what, ours, dg.last_form(), phases), flush=True)
         assert np.array_equal(B.to_u64(dist), got if ref is None else ref)
         assert ours <= 1.1 * phases + 0.02, (name, what, ours, phases)
+        assert dg.last_form() == FORMS.get(name, {}).get(what, dg.last_form()), (name, what)
     dg.close()
 
 
