@@ -949,7 +949,8 @@ static int batch_split(sssp_graph *const *graphs, const uint32_t *sources, std::
 // sixty-four. The number of phases tells them apart: random and R-MAT graphs of 2^19 to 2^23 vertices
 // took at most 0.6 sqrt(n), grids and meshes of up to eight neighbours at least 8 sqrt(n), so that a
 // solve is given up beyond sqrt(n), after 2 % of the launch's time, and the rest of the batch left to
-// the launch. Nor do many graphs of few phases gain, since a phase does not fill the device (530 k
+// the launch (with IN- or OUT-STATIC alone at most 2.5 and at least 25 sqrt(n), given up beyond 4; eight
+// random graphs of 1 M vertices and degree 16 99 ms in turn and 955). Nor do many graphs of few phases gain, since a phase does not fill the device (530 k
 // vertices, degree 2: 16 queries 38 ms and 54, 32 queries 75 and 36; 1 M vertices, degree 2: 16 queries
 // 52 and 82, 32 queries 105 and 71; R-MAT 21 with 4 edges a vertex: 32 queries 83 and 138, 128 queries
 // 331 and 243), unless they have 2^25 edges (random, 2 M vertices of degree 16: 64 queries 301 and 798;
@@ -958,6 +959,7 @@ static int batch_default(sssp_graph *const *graphs, const uint32_t *sources, uin
                          uint64_t *const *dist_outs, uint32_t *phases_out, std::vector<uint32_t> *left) {
     std::vector<uint32_t> small, large;
     for (uint32_t i = 0; i < nq; ++i) (nq > 1 && resident_batch_takes(graphs[i]) ? small : large).push_back(i);
+    const double turn_phases = in == IN_STATIC_M && out_static ? 1 : 4;
     // shares of what the device takes in turn: 16 graphs under 2^20 vertices, 20 of more
     constexpr uint64_t kTurns = 80;
     uint64_t turns = 0, scratch = 0;
@@ -984,7 +986,7 @@ static int batch_default(sssp_graph *const *graphs, const uint32_t *sources, uin
     });
     for (size_t j = 0; j < large.size(); ++j) {
         const uint32_t i = large[j];
-        const uint32_t cap = large.size() > 2 ? (uint32_t)sqrt((double)graphs[i]->n) : 0;
+        const uint32_t cap = large.size() > 2 ? (uint32_t)(turn_phases * sqrt((double)graphs[i]->n)) : 0;
         uint32_t phases = 0;
         bool ran = false;
         const int rc = resident_solve(graphs[i], resident_shape(graphs[i]), graphs[0]->stream, sources[i], in, out_static, 0,

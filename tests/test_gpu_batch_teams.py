@@ -88,6 +88,23 @@ def test_large_graphs_of_few_and_many_phases_with_small_ones(B):
     run(B, [(random, 17), (small, 2)])
 
 
+@pytest.mark.parametrize("crit", [O.IN_STATIC, O.OUT_STATIC, O.STATIC_OR])
+def test_large_random_graphs_take_turns_with_each_criterion(B, crit):
+    """Criteria alone take several times the phases of their disjunction: not a reason for the launch."""
+    g = G.er(530003, 4, 1, 1 << 20, 16)
+    dg = B.DeviceGraph.from_graph(g)
+    ref = O.phased(g, 0, crit)
+    for count, source, form in ((4, 0, "resident"), (17, 0, "workgroups")):
+        dists, phases = B.solve_batch([dg] * count, [source] * count, crit)
+        assert dg.last_form() == form
+        assert all(np.array_equal(B.to_u64(d), ref.dist) and p == ref.phases for d, p in zip(dists, phases))
+    grid = B.DeviceGraph.from_graph(G.grid(1029, 512, 1, 1 << 16, 17))
+    B.solve_batch([grid] * 3, [0, 5, 9], crit)
+    assert grid.last_form() == "workgroups"
+    dg.close()
+    grid.close()
+
+
 def test_large_grids_of_unknown_shape_follow_solved_graphs(B):
     """A graph of many phases whose degree does not tell so comes after others of its batch, which stay
     solved; the rest goes to the one launch."""
