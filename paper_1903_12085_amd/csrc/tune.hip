@@ -108,7 +108,9 @@ extern "C" int sssp_autotune(sssp_graph *g, uint32_t source, uint32_t criterion,
         rc = sssp_set_launch(g, &c);
         float ms = 0;
         if (rc == SSSP_OK) rc = time_call(g->stream, 3, [&] { return sssp_solve(g, source, criterion, dist, nullptr); }, &ms);
-        if (rc == SSSP_OK && ms < win_ms) { win_ms = ms; win = c; }
+        // where the default takes the phase kernels by itself the two are the same for this criterion
+        // only, and it stays with the default
+        if (rc == SSSP_OK && (ms < win_ms || g->form == SSSP_FORM_PHASES)) { win_ms = ms; win = c; }
     } else {
         win.single = keep.single;  // the other criteria always run the phase kernels: not theirs to choose
     }

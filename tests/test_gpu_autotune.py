@@ -32,6 +32,16 @@ def test_resident_criteria_keep_the_resident_solve(B, crit):
     dg.close()
 
 
+def test_default_that_takes_the_phase_kernels_is_kept(B):
+    """Unit weights on a large skewed graph: static solves run the phase kernels by default, others on the
+    handle still run resident."""
+    dg = B.DeviceGraph.from_graph(G.rmat(21, 16, 1, 1, 403))
+    cfg, _ = B.autotune(dg, 1, B.STATIC_OR)
+    B.solve(dg, 1, B.STATIC_OR)
+    assert dg.last_form() == "phases" and cfg["single"] in (0, 1) and dg.launch()["single"] == cfg["single"]
+    dg.close()
+
+
 @pytest.mark.parametrize("single", [0, 1, 2])
 def test_other_criteria_leave_the_choice_alone(B, single):
     g = G.er(2001, 6, 1, 1000, 402)
